@@ -4,11 +4,12 @@
 // axis, each at least r + margin thick (so the neighbours of an atom lie in
 // the slabs within K_a = floor((r + margin) n_a / h_a) + 1 of its own, with
 // periodic images handled by "virtual" slab indices), atoms are binned by
-// their wrapped fractional coordinates, and one block per atom tests all
-// candidates with the exact fp32 inclusion expression. The accepted (j, n)
-// keys of an atom are then sorted in LDS into the canonical (j, n1, n2, n3)
-// order, so the output does not depend on the order in which atoms landed in
-// their bins. One host wait reads the sizes E, B, A back.
+// their wrapped fractional coordinates into bin-ordered records, and one or
+// four wavefronts per atom test all candidates with the exact fp32 inclusion
+// expression. The accepted (j, n) keys of an atom are then put in LDS into
+// the canonical (j, n1, n2, n3) order, so the output does not depend on the
+// order in which atoms landed in their bins. One host wait reads the sizes
+// E, B, A back.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -122,8 +123,12 @@ __device__ StructInfo struct_info(int s, const int* __restrict__ atom_ptr, const
   for (int a = 0; a < 3; ++a) h[a] = vol / sqrt(cs[a][0] * cs[a][0] + cs[a][1] * cs[a][1] + cs[a][2] * cs[a][2]);
   const double rr = (double)r + kMargin;
   long long nb[3];
+  // slabs half a cutoff thick where the cell is at least one cutoff wide: the
+  // 5 x 5 x 5 slabs around an atom then hold 0.58 times the candidates of
+  // 3 x 3 x 3 slabs of a whole cutoff; in thinner cells, where every image is
+  // searched anyway, more slabs would only make the runs shorter
   for (int a = 0; a < 3; ++a) {
-    double q = floor(h[a] / rr);
+    double q = h[a] >= rr ? floor(2.0 * h[a] / rr) : 1.0;
     nb[a] = q < 1.0 ? 1 : (q > 1024.0 ? 1024 : (long long)q);
   }
   long long cap = n_s > 1 ? n_s : 1;
@@ -145,9 +150,24 @@ __device__ StructInfo struct_info(int s, const int* __restrict__ atom_ptr, const
   return si;
 }
 
-__global__ void __launch_bounds__(1024) k_struct_setup(int S, const int* __restrict__ atom_ptr,
+// More bins than atoms and crystals can only come from a decreasing atom_ptr
+// (refused afterwards): every crystal then takes bin 0, so that no bin index
+// leaves the scratch arrays. Whole block; returns the number of bins.
+__device__ int bins_checked(int nbins, int N, int S, StructInfo* info, GraphInfo* ginfo) {
+  if (nbins <= N + S) return nbins;
+  if (threadIdx.x == 0) atomicOr(&ginfo->err, ERR_PTR);
+  for (int s = threadIdx.x; s < S; s += blockDim.x)
+    for (int a = 0; a < 3; ++a) {
+      info[s].nb[a] = 1;
+      info[s].K[a] = 0;
+      info[s].bin_base = 0;
+    }
+  return 1;
+}
+
+__global__ void __launch_bounds__(1024) k_struct_setup(int N, int S, const int* __restrict__ atom_ptr,
                                                        const float* __restrict__ lattice, float r,
-                                                       StructInfo* __restrict__ info, int* __restrict__ total_bins,
+                                                       StructInfo* info, int* __restrict__ total_bins,
                                                        GraphInfo* ginfo) {
   __shared__ int scan[1024];
   int carry = 0;  // bins of the structures of earlier rounds
@@ -172,28 +192,38 @@ __global__ void __launch_bounds__(1024) k_struct_setup(int S, const int* __restr
     carry += scan[1023];
     __syncthreads();
   }
+  __threadfence_block();
+  __syncthreads();
+  carry = bins_checked(carry, N, S, info, ginfo);
   if (threadIdx.x == 0) *total_bins = carry;
 }
 
-__global__ void k_atom_bin(int N, int S, const int* __restrict__ atom_ptr, const float* __restrict__ pos,
-                           const int* __restrict__ Z, const StructInfo* __restrict__ info, int* __restrict__ atom_struct,
-                           int* __restrict__ atom_bin, int* __restrict__ atom_cell, int* __restrict__ atom_wrap,
-                           int* __restrict__ bin_count, GraphInfo* ginfo) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  int s = find_struct(atom_ptr, S, i);
-  atom_struct[i] = s;
-  int z = Z[i];
-  if (z < 1 || z > 94) atomicOr(&ginfo->err, ERR_Z);
+// An atom's structure, bin, cell (10 bits an axis: at most 1024 slabs) and
+// wrap (floor of the fractional coordinate, |w| <= kMaxWrap, 10 bits an axis
+// with a bias of 512).
+struct AtomMeta {
+  int s, bin, cell, wrap;
+};
+constexpr int kWrapBias = 512;
+__device__ __forceinline__ int pack3(int a, int b, int c) { return a | (b << 10) | (c << 20); }
+__device__ __forceinline__ void unpack3(int p, int bias, int (&v)[3]) {
+  v[0] = (p & 1023) - bias;
+  v[1] = ((p >> 10) & 1023) - bias;
+  v[2] = ((p >> 20) & 1023) - bias;
+}
+
+__device__ __forceinline__ AtomMeta atom_meta(int i, int s, const float* __restrict__ pos, const int* __restrict__ Z,
+                                              const StructInfo* __restrict__ info, GraphInfo* ginfo) {
+  const int z = Z[i];
+  int err = z < 1 || z > 94 ? ERR_Z : 0;
   const StructInfo& si = info[s];
-  float p[3] = {pos[i * 3 + 0], pos[i * 3 + 1], pos[i * 3 + 2]};
-  int err = 0;
+  const float p[3] = {pos[i * 3 + 0], pos[i * 3 + 1], pos[i * 3 + 2]};
   int c[3], w[3];
   for (int a = 0; a < 3; ++a) {
     if (!(fabsf(p[a]) <= kMaxCoord)) err |= ERR_FAR;
     double f = (double)p[0] * si.Linv[0 * 3 + a] + (double)p[1] * si.Linv[1 * 3 + a] + (double)p[2] * si.Linv[2 * 3 + a];
     double fl = floor(f);
-    if (!(fabs(fl) <= kMaxWrap)) { err |= ERR_FAR; fl = 0.0; }
+    if (!(fabs(fl) <= kMaxWrap)) { err |= ERR_FAR; f = fl = 0.0; }
     double fr = f - fl;
     int ca = (int)floor(fr * si.nb[a]);
     ca = ca < 0 ? 0 : (ca >= si.nb[a] ? si.nb[a] - 1 : ca);
@@ -201,13 +231,18 @@ __global__ void k_atom_bin(int N, int S, const int* __restrict__ atom_ptr, const
     w[a] = (int)fl;
   }
   if (err) atomicOr(&ginfo->err, err);
-  int bin = si.bin_base + (c[0] * si.nb[1] + c[1]) * si.nb[2] + c[2];
-  atom_bin[i] = bin;
-  for (int a = 0; a < 3; ++a) {
-    atom_cell[i * 3 + a] = c[a];
-    atom_wrap[i * 3 + a] = w[a];
-  }
-  atomicAdd(&bin_count[bin], 1);
+  return AtomMeta{s, si.bin_base + (c[0] * si.nb[1] + c[1]) * si.nb[2] + c[2], pack3(c[0], c[1], c[2]),
+                  pack3(w[0] + kWrapBias, w[1] + kWrapBias, w[2] + kWrapBias)};
+}
+
+__global__ void k_atom_bin(int N, int S, const int* __restrict__ atom_ptr, const float* __restrict__ pos,
+                           const int* __restrict__ Z, const StructInfo* __restrict__ info, AtomMeta* __restrict__ meta,
+                           int* __restrict__ bin_count, GraphInfo* ginfo) {
+  int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  const AtomMeta m = atom_meta(i, find_struct(atom_ptr, S, i), pos, Z, info, ginfo);
+  meta[i] = m;
+  atomicAdd(&bin_count[m.bin], 1);
 }
 
 // Scans in a fixed order: a wavefront's inclusive scan by lane shuffles,
@@ -267,13 +302,112 @@ __global__ void __launch_bounds__(1024) k_scan_single(int n, const int* __restri
   if (threadIdx.x == 0) out[n] = carry;
 }
 
-__global__ void k_bin_fill(int N, const int* __restrict__ atom_bin, const int* __restrict__ bin_start,
-                           int* __restrict__ bin_cursor, int* __restrict__ bin_atoms) {
+// Bin-ordered record of an atom: position and index, and its wrap.
+__device__ __forceinline__ void put_record(int slot, int i, int wrap, const float* __restrict__ pos,
+                                           float4* __restrict__ bin_xyzj, int* __restrict__ bin_wrap) {
+  bin_xyzj[slot] = make_float4(pos[i * 3 + 0], pos[i * 3 + 1], pos[i * 3 + 2], __int_as_float(i));
+  bin_wrap[slot] = wrap;
+}
+
+__global__ void k_bin_fill(int N, const AtomMeta* __restrict__ meta, const int* __restrict__ bin_start,
+                           int* __restrict__ bin_cursor, const float* __restrict__ pos, float4* __restrict__ bin_xyzj,
+                           int* __restrict__ bin_wrap) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
-  int b = atom_bin[i];
-  int slot = atomicAdd(&bin_cursor[b], 1);
-  bin_atoms[bin_start[b] + slot] = i;
+  const AtomMeta m = meta[i];
+  const int slot = atomicAdd(&bin_cursor[m.bin], 1);
+  put_record(bin_start[m.bin] + slot, i, m.wrap, pos, bin_xyzj, bin_wrap);
+}
+
+// The whole binning (structure setup, bin counts, their scan, the records) in
+// one block, with the counters in LDS, for batches whose bins fit there: each
+// step is latency-bound at these sizes, and the five launches it takes the
+// place of (each a few microseconds at least, kept below for larger batches)
+// summed to 46 us on 128 crystals of 5,541 atoms, now 20 us, and to 29 us on
+// one crystal of 4,096, now 15 us (kernel time under the profiler).
+constexpr int kBinMax = 16384;      // bins (at most N + S)
+constexpr int kBinAtomsPer = 8;     // atoms a thread at most
+constexpr int kBinStructs = 2048;   // crystals whose offsets are searched in LDS
+__global__ void __launch_bounds__(1024) k_bin(int N, int S, const int* __restrict__ atom_ptr,
+                                              const float* __restrict__ pos, const int* __restrict__ Z,
+                                              const float* __restrict__ lattice, float r, StructInfo* info,
+                                              AtomMeta* __restrict__ meta, int* __restrict__ bin_start,
+                                              float4* __restrict__ bin_xyzj, int* __restrict__ bin_wrap,
+                                              GraphInfo* ginfo) {
+  __shared__ int cnt[kBinMax];
+  __shared__ int ptr_lds[kBinStructs + 1];
+  __shared__ int sh[17];
+  const int tid = threadIdx.x;
+  if (S <= kBinStructs)
+    for (int s = tid; s <= S; s += 1024) ptr_lds[s] = atom_ptr[s];
+  if (tid == 0) *ginfo = GraphInfo{};
+  __threadfence_block();
+  __syncthreads();
+  int nbins = 0;
+  for (int s0 = 0; s0 < S; s0 += 1024) {
+    const int s = s0 + tid;
+    int bins = 0;
+    StructInfo si{};
+    if (s < S) {
+      si = struct_info(s, atom_ptr, lattice, r, ginfo);
+      bins = si.nb[0] * si.nb[1] * si.nb[2];
+    }
+    int total;
+    const int base = nbins + block_excl_scan(bins, sh, total);
+    if (s < S) {
+      si.bin_base = base;
+      info[s] = si;
+    }
+    nbins += total;
+  }
+  __threadfence_block();
+  __syncthreads();
+  nbins = bins_checked(nbins, N, S, info, ginfo);
+  for (int b = tid; b < nbins; b += 1024) cnt[b] = 0;
+  __threadfence_block();
+  __syncthreads();
+  int bin[kBinAtomsPer], slot[kBinAtomsPer], wrap[kBinAtomsPer];
+#pragma unroll
+  for (int q = 0; q < kBinAtomsPer; ++q) {
+    const int i = tid + 1024 * q;
+    bin[q] = -1;
+    if (i < N) {
+      const int st = S <= kBinStructs ? find_struct(ptr_lds, S, i) : find_struct(atom_ptr, S, i);
+      const AtomMeta m = atom_meta(i, st, pos, Z, info, ginfo);
+      meta[i] = m;
+      bin[q] = m.bin;
+      wrap[q] = m.wrap;
+      slot[q] = atomicAdd(&cnt[m.bin], 1);
+    }
+  }
+  __syncthreads();
+  // exclusive scan of the counts, in place
+  int carry = 0;
+  for (int base = 0; base < nbins; base += 1024 * kScanPer) {
+    const int i0 = base + tid * kScanPer;
+    int v[kScanPer], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      v[q] = i0 + q < nbins ? cnt[i0 + q] : 0;
+      sum += v[q];
+    }
+    int total;
+    int run = carry + block_excl_scan(sum, sh, total);
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      if (i0 + q < nbins) {
+        cnt[i0 + q] = run;
+        bin_start[i0 + q] = run;
+      }
+      run += v[q];
+    }
+    carry += total;
+  }
+  if (tid == 0) bin_start[nbins] = carry;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kBinAtomsPer; ++q)
+    if (bin[q] >= 0) put_record(cnt[bin[q]] + slot[q], tid + 1024 * q, wrap[q], pos, bin_xyzj, bin_wrap);
 }
 
 struct SearchArgs {
@@ -281,146 +415,198 @@ struct SearchArgs {
   float rc2_atom, rc2_bond;
   const float* pos;
   const StructInfo* info;
-  const int* atom_struct;
-  const int* atom_cell;
-  const int* atom_wrap;
+  const AtomMeta* meta;
   const int* bin_start;
-  const int* bin_atoms;
+  const float4* bin_xyzj;
+  const int* bin_wrap;
 };
 
-// One 256-thread block per atom. The candidates of atom i are the atoms of
-// its (2K+1)^3 virtual slabs; the block takes the virtual slabs 256 at a
-// time, scans their atom counts, and then spreads the flattened candidate
-// list over all threads (a thread finds its slab by binary search over the
-// scanned counts), so small slabs do not leave lanes idle.
-constexpr int kSearchThreads = 256;
-struct SearchShared {
-  int pre[kSearchThreads];  // exclusive prefix of the slabs' atom counts
-  int lo[kSearchThreads];   // first bin_atoms slot of each slab
-  int m[kSearchThreads][3];  // lattice translation of each virtual slab
-  int wsum[kSearchThreads / 64];
-};
-
-// Calls f(j, n1, n2, n3, d2) on the thread that holds candidate (j, n) of
-// atom i, for every candidate that passes the atom cutoff.
-template <class F>
-__device__ __forceinline__ void block_search(const SearchArgs& A, int i, SearchShared& sh, F&& f) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int s = A.atom_struct[i];
-  const StructInfo& si = A.info[s];
+// Calls f(j, n1, n2, n3, d2, pass) on the lane that holds candidate (j, n) of
+// atom i, once per 64 candidates of the calling wavefront (pass: it is within
+// the atom cutoff; lanes past the end call with pass = false). The candidates
+// are the atoms of the (2K+1)^3 virtual slabs around the atom's own. Bins of
+// one (slab 0, slab 1) pair that lie in one image along axis 2 are contiguous
+// in the bin order, so they form one run of records; a lane sizes one run, a
+// wavefront scans 64 of them, and the flattened candidates are dealt 64 at a
+// time: each run's lane sends its number to the lane that holds the run's
+// first candidate, and a lane's run is the nearest such mark at or below it.
+// Bound by the latency of its chain of loads: one 16-byte record a candidate
+// (in place of three dependent loads through the atom's index) and two groups
+// in flight (counting 4,096 atoms: 45 us with a block an atom, 22 us with a
+// group at a time, 13 us so, with the finer slabs of struct_info).
+// The W wavefronts of an atom take every W-th group of 64. No block barrier.
+template <int W, class F>
+__device__ __forceinline__ void wave_search(const SearchArgs& A, int i, int w, F&& f) {
+  const int lane = threadIdx.x & 63;
+  const AtomMeta me = A.meta[i];
+  const StructInfo& si = A.info[me.s];
   float L[9];
+#pragma unroll
   for (int k = 0; k < 9; ++k) L[k] = si.L[k];
   const float ri[3] = {A.pos[i * 3 + 0], A.pos[i * 3 + 1], A.pos[i * 3 + 2]};
-  const int ci[3] = {A.atom_cell[i * 3 + 0], A.atom_cell[i * 3 + 1], A.atom_cell[i * 3 + 2]};
-  const int wi[3] = {A.atom_wrap[i * 3 + 0], A.atom_wrap[i * 3 + 1], A.atom_wrap[i * 3 + 2]};
-  const int w0 = 2 * si.K[0] + 1, w1 = 2 * si.K[1] + 1, w2 = 2 * si.K[2] + 1;
-  const int nv = w0 * w1 * w2;
-  for (int v0 = 0; v0 < nv; v0 += kSearchThreads) {
-    const int v = v0 + t;
-    int cnt = 0;
-    if (v < nv) {
-      const int d2 = v % w2 - si.K[2], d1 = (v / w2) % w1 - si.K[1], d0 = v / (w2 * w1) - si.K[0];
-      const int x0 = ci[0] + d0, b0 = floor_mod(x0, si.nb[0]);
-      const int x1 = ci[1] + d1, b1 = floor_mod(x1, si.nb[1]);
-      const int x2 = ci[2] + d2, b2 = floor_mod(x2, si.nb[2]);
-      const int bin = si.bin_base + (b0 * si.nb[1] + b1) * si.nb[2] + b2;
-      const int lo = A.bin_start[bin];
-      cnt = A.bin_start[bin + 1] - lo;
-      sh.lo[t] = lo;
-      sh.m[t][0] = (x0 - b0) / si.nb[0];
-      sh.m[t][1] = (x1 - b1) / si.nb[1];
-      sh.m[t][2] = (x2 - b2) / si.nb[2];
+  int ci[3], wi[3];
+  unpack3(me.cell, 0, ci);
+  unpack3(me.wrap, kWrapBias, wi);
+  const int nb0 = si.nb[0], nb1 = si.nb[1], nb2 = si.nb[2], K0 = si.K[0], K1 = si.K[1], K2 = si.K[2];
+  const int w1 = 2 * K1 + 1;
+  const int zlo = ci[2] - K2, zhi = ci[2] + K2;
+  const int m2lo = (zlo - floor_mod(zlo, nb2)) / nb2, m2hi = (zhi - floor_mod(zhi, nb2)) / nb2;
+  const int nz = m2hi - m2lo + 1;
+  const int nruns = (2 * K0 + 1) * w1 * nz;
+  for (int v0 = 0; v0 < nruns; v0 += 64) {
+    const int v = v0 + lane;
+    int cnt = 0, lo = 0, mp = 0;
+    if (v < nruns) {
+      const int pl = v / nz, m2 = m2lo + v % nz;
+      const int x0 = ci[0] + pl / w1 - K0, b0 = floor_mod(x0, nb0);
+      const int x1 = ci[1] + pl % w1 - K1, b1 = floor_mod(x1, nb1);
+      const int base = si.bin_base + (b0 * nb1 + b1) * nb2;
+      lo = A.bin_start[base + max(zlo - m2 * nb2, 0)];
+      cnt = A.bin_start[base + min(zhi - m2 * nb2, nb2 - 1) + 1] - lo;
+      // |m| is at most K / nb + 1 <= 65 along an axis
+      mp = pack3((x0 - b0) / nb0 + kWrapBias, (x1 - b1) / nb1 + kWrapBias, m2 + kWrapBias);
     }
-    // block exclusive scan of the counts
     int incl = cnt;
+#pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const int y = __shfl_up(incl, off, 64);
       if (lane >= off) incl += y;
     }
-    if (lane == 63) sh.wsum[w] = incl;
-    __syncthreads();
-    int base = 0, total = 0;
-    for (int k = 0; k < kSearchThreads / 64; ++k) {
-      base += k < w ? sh.wsum[k] : 0;
-      total += sh.wsum[k];
-    }
-    sh.pre[t] = base + incl - cnt;
-    __syncthreads();
-    for (int c = t; c < total; c += kSearchThreads) {
-      int lo = 0, hi = kSearchThreads - 1;  // last slab u with pre[u] <= c
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (sh.pre[mid] <= c) lo = mid;
-        else hi = mid - 1;
+    const int total = __shfl(incl, 63, 64), pre = incl - cnt;
+    // two groups of 64 at a time, so that their loads overlap
+    for (int c0 = 64 * w; c0 < total; c0 += 128 * W) {
+      int idx[2], mq[2], wr[2];
+      float4 q[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int cu = c0 + 64 * W * u;
+        // run that holds candidate cu: the last non-empty one starting at or below it
+        const unsigned long long below = __ballot(cnt > 0 && pre <= cu);
+        int run = 63 - __clzll((long long)below);
+        const bool marked = cnt > 0 && pre > cu && pre < cu + 64;
+        // sent to lane pre - cu; a lane that nothing is sent to reads 0 (every
+        // lane without a mark sends 0 to lane 0, whose run is `run` anyway)
+        const int rec = __builtin_amdgcn_ds_permute(marked ? 4 * (pre - cu) : 0, marked ? lane + 1 : 0);
+        const unsigned long long marks =
+            __ballot(rec != 0 && lane > 0) & (lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1ull);
+        const int other = __shfl(rec, marks ? 63 - __clzll((long long)marks) : 0, 64) - 1;
+        if (marks) run = other;
+        const int off = __shfl(lo - pre, run, 64);
+        mq[u] = __shfl(mp, run, 64);
+        // clamped, so that both groups' loads are issued at once
+        idx[u] = off + cu + lane;
+        if (cu + lane >= total) idx[u] = -1;
+        const int at = max(idx[u], 0);
+        q[u] = A.bin_xyzj[at];
+        wr[u] = A.bin_wrap[at];
       }
-      const int j = A.bin_atoms[sh.lo[lo] + (c - sh.pre[lo])];
-      const int n1 = sh.m[lo][0] - A.atom_wrap[j * 3 + 0] + wi[0];
-      const int n2 = sh.m[lo][1] - A.atom_wrap[j * 3 + 1] + wi[1];
-      const int n3 = sh.m[lo][2] - A.atom_wrap[j * 3 + 2] + wi[2];
-      const float rj[3] = {A.pos[j * 3 + 0], A.pos[j * 3 + 1], A.pos[j * 3 + 2]};
-      const float dd = pair_d2(i, j, ri, rj, n1, n2, n3, L);
-      if (dd < A.rc2_atom && !(j == i && n1 == 0 && n2 == 0 && n3 == 0)) f(j, n1, n2, n3, dd);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (c0 + 64 * W * u >= total) break;  // uniform over the wavefront
+        int wj[3], n[3];
+        unpack3(wr[u], kWrapBias, wj);
+        unpack3(mq[u], kWrapBias, n);
+        const int j = __float_as_int(q[u].w);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) n[k] += wi[k] - wj[k];
+        const float rj[3] = {q[u].x, q[u].y, q[u].z};
+        const float dd = pair_d2(i, j, ri, rj, n[0], n[1], n[2], L);
+        const bool pass = idx[u] >= 0 && dd < A.rc2_atom && !(j == i && n[0] == 0 && n[1] == 0 && n[2] == 0);
+        f(j, n[0], n[1], n[2], dd, pass);
+      }
     }
-    __syncthreads();
   }
 }
 
-// Block-wide sum of one int per thread (256 threads); every thread gets it.
-__device__ __forceinline__ int block_sum(int v, int* wsum) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int t = 0;
-  for (int k = 0; k < kSearchThreads / 64; ++k) t += wsum[k];
-  return t;
-}
+constexpr int kSearchThreads = 256;
 
-// Count edges and bonds of atom blockIdx.x.
+// Edges and bonds of each atom: W wavefronts an atom (four where few atoms
+// would leave the chip idle), 4 / W atoms a block.
+template <int W>
 __global__ void __launch_bounds__(kSearchThreads) k_count(SearchArgs A, int* __restrict__ edge_count,
                                                           int* __restrict__ bond_count) {
-  __shared__ SearchShared sh;
-  const int i = blockIdx.x;
-  int ne = 0, nb = 0;
-  block_search(A, i, sh, [&](int, int, int, int, float dd) {
-    ++ne;
-    nb += dd < A.rc2_bond ? 1 : 0;
-  });
-  ne = block_sum(ne, sh.wsum);
-  nb = block_sum(nb, sh.wsum);
-  if (threadIdx.x == 0) {
+  __shared__ int part[4][2];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = blockIdx.x * (4 / W) + wave / W;
+  int ne = 0, nb = 0;  // of the wavefront
+  if (i < A.N)
+    wave_search<W>(A, i, wave % W, [&](int, int, int, int, float dd, bool pass) {
+      ne += __popcll(__ballot(pass));
+      nb += __popcll(__ballot(pass && dd < A.rc2_bond));
+    });
+  if (W > 1) {
+    if ((threadIdx.x & 63) == 0) {
+      part[wave][0] = ne;
+      part[wave][1] = nb;
+    }
+    __syncthreads();
+    if (wave % W != 0) return;
+    for (int q = 1; q < W; ++q) {
+      ne += part[wave + q][0];
+      nb += part[wave + q][1];
+    }
+  }
+  if (i < A.N && (threadIdx.x & 63) == 0) {
     edge_count[i] = ne;
     bond_count[i] = nb;
   }
 }
 
-// Exclusive scans of edge counts, bond counts and k(k-1); totals into ginfo.
+// Exclusive scans of edge counts, bond counts and k(k-1); totals, the largest
+// edge count and (MD) the largest of the N squared displacements in `disp2`
+// into ginfo and, if given, its host copy. One block; an atom has fewer than
+// 2^18 edges and bonds here or the whole build is refused, so the 8,192 atoms
+// of a pass sum to less than 2^31 and one 64-bit scan holds both counts.
 __global__ void __launch_bounds__(1024) k_scan_counts(int N, const int* __restrict__ edge_count,
                                                      const int* __restrict__ bond_count, int* __restrict__ edge_ptr,
                                                      int* __restrict__ bond_ptr, long long* __restrict__ angle_base,
-                                                     GraphInfo* ginfo) {
-  __shared__ long long sh[17];
-  __shared__ int mx[1024];
+                                                     const float* __restrict__ disp2, GraphInfo* ginfo,
+                                                     GraphInfo* host) {
+  __shared__ unsigned long long sh_eb[17], sh_a[17];
+  __shared__ int mx[16];
+  __shared__ float md[16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   long long ce = 0, cb = 0, ca = 0;
   int my_max = 0;
-  for (int base = 0; base < N; base += (int)blockDim.x * kScanPer) {
+  float my_d2 = 0.f;
+  for (int base = 0; base < N; base += 1024 * kScanPer) {
     const int i0 = base + (int)threadIdx.x * kScanPer;
     int ve[kScanPer], vb[kScanPer];
-    long long se = 0, sb = 0, sa = 0;
+    unsigned long long seb = 0, sa = 0;
 #pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
       const bool in = i0 + q < N;
-      ve[q] = in ? edge_count[i0 + q] : 0;
-      vb[q] = in ? bond_count[i0 + q] : 0;
-      se += ve[q];
-      sb += vb[q];
-      sa += (long long)vb[q] * (vb[q] - 1);
+      // (a count past the limit is refused below through max_count)
+      ve[q] = in ? min(edge_count[i0 + q], 1 << 18) : 0;
+      vb[q] = in ? min(bond_count[i0 + q], 1 << 18) : 0;
+      if (disp2 && in) my_d2 = fmaxf(my_d2, disp2[i0 + q]);
+      seb += ((unsigned long long)vb[q] << 32) | (unsigned)ve[q];
+      sa += (unsigned long long)vb[q] * (vb[q] - 1);
       my_max = max(my_max, ve[q]);
     }
-    long long te, tb, ta;
-    long long e0 = ce + block_excl_scan(se, sh, te);
-    long long b0 = cb + block_excl_scan(sb, sh, tb);
-    long long a0 = ca + block_excl_scan(sa, sh, ta);
+    // block scan of both, two barriers
+    const unsigned long long ieb = wave_incl_scan(seb, lane), ia = wave_incl_scan(sa, lane);
+    if (lane == 63) {
+      sh_eb[w] = ieb;
+      sh_a[w] = ia;
+    }
+    __syncthreads();
+    if (w == 0) {
+      const unsigned long long t = lane < 16 ? sh_eb[lane] : 0, u = lane < 16 ? sh_a[lane] : 0;
+      const unsigned long long ti = wave_incl_scan(t, lane), ui = wave_incl_scan(u, lane);
+      if (lane < 16) {
+        sh_eb[lane] = ti - t;
+        sh_a[lane] = ui - u;
+      }
+      if (lane == 15) {
+        sh_eb[16] = ti;
+        sh_a[16] = ui;
+      }
+    }
+    __syncthreads();
+    const unsigned long long xeb = sh_eb[w] + ieb - seb, teb = sh_eb[16], ta = sh_a[16];
+    long long e0 = ce + (long long)(xeb & 0xffffffffu), b0 = cb + (long long)(xeb >> 32);
+    long long a0 = ca + (long long)(sh_a[w] + ia - sa);
 #pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
       if (i0 + q < N) {
@@ -432,24 +618,37 @@ __global__ void __launch_bounds__(1024) k_scan_counts(int N, const int* __restri
       b0 += vb[q];
       a0 += (long long)vb[q] * (vb[q] - 1);
     }
-    ce += te;
-    cb += tb;
-    ca += ta;
-  }
-  mx[threadIdx.x] = my_max;
-  __syncthreads();
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) mx[threadIdx.x] = max(mx[threadIdx.x], mx[threadIdx.x + off]);
+    ce += (long long)(teb & 0xffffffffu);
+    cb += (long long)(teb >> 32);
+    ca += (long long)ta;
     __syncthreads();
   }
+  for (int off = 32; off > 0; off >>= 1) {
+    my_max = max(my_max, __shfl_xor(my_max, off, 64));
+    my_d2 = fmaxf(my_d2, __shfl_xor(my_d2, off, 64));
+  }
+  if (lane == 0) {
+    mx[w] = my_max;
+    md[w] = my_d2;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
+    for (int q = 1; q < 16; ++q) {
+      my_max = max(my_max, mx[q]);
+      my_d2 = fmaxf(my_d2, md[q]);
+    }
     edge_ptr[N] = (int)(ce < INT_MAX ? ce : INT_MAX);
     bond_ptr[N] = (int)(cb < INT_MAX ? cb : INT_MAX);
     angle_base[N] = ca;
-    ginfo->n_edges = ce;
-    ginfo->n_bonds = cb;
-    ginfo->n_angles = ca;
-    ginfo->max_count = mx[0];
+    GraphInfo r{};
+    r.n_edges = ce;
+    r.n_bonds = cb;
+    r.n_angles = ca;
+    r.max_count = my_max;
+    r.err = disp2 ? 0 : ginfo->err;
+    r.max_disp2 = __float_as_uint(my_d2);  // non-negative floats order as their bits
+    *ginfo = r;
+    if (host) *host = r;
   }
 }
 
@@ -459,23 +658,109 @@ __device__ __forceinline__ unsigned long long make_key(int j, int n1, int n2, in
          (bond ? 1ull : 0ull);
 }
 
-// One block per atom: gather the accepted keys into LDS (slots taken with an
-// LDS counter; the order is fixed by the sort that follows), bitonic sort,
-// write the edges in canonical order and the atom's bond list.
+// The canonical place of a key among the `count` keys of its atom, and the
+// bonds before it (keys are distinct; the bond flag is a key's lowest bit).
+__device__ __forceinline__ void write_edge(unsigned long long key, int rank, int brank, int e0, int b0,
+                                           int* __restrict__ edge_dst, int* __restrict__ edge_img,
+                                           int* __restrict__ bond_edge) {
+  const int e = e0 + rank;
+  edge_dst[e] = (int)(key >> 31);
+  edge_img[e * 3 + 0] = (int)((key >> 21) & 1023) - kImgBias;
+  edge_img[e * 3 + 1] = (int)((key >> 11) & 1023) - kImgBias;
+  edge_img[e * 3 + 2] = (int)((key >> 1) & 1023) - kImgBias;
+  if (key & 1ull) bond_edge[b0 + brank] = e;
+}
+
+// Gathers the accepted keys of an atom into LDS (in any order) and writes the
+// edges in canonical order and the atom's bond list. A key's place is the
+// number of smaller keys, counted against every key (broadcast LDS reads, no
+// barrier between steps): about 80-100 keys an atom, where the bitonic
+// network in its place ran 28 block barriers. With the search by wavefronts
+// the launch went from 61 to 23 us on one crystal of 4,096 atoms. Past
+// kRankMax keys the network's n log^2 n work is the smaller one and it is
+// kept.
+// W = 1: four atoms a block, at most kWaveKeys keys each. W = 4: a block an
+// atom, `sort_size` (a power of two) keys in dynamic LDS.
+constexpr int kWaveKeys = 256, kRankMax = 1024;
+template <int W>
 __global__ void __launch_bounds__(kSearchThreads) k_fill(SearchArgs A, int sort_size, const int* __restrict__ edge_ptr,
                                                          const int* __restrict__ bond_ptr, int* __restrict__ edge_dst,
                                                          int* __restrict__ edge_img, int* __restrict__ bond_edge) {
-  extern __shared__ unsigned long long keys[];
-  __shared__ SearchShared sh;
-  __shared__ int nkeys;
-  const int i = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  extern __shared__ __attribute__((aligned(16))) unsigned long long keys_all[];
+  __shared__ int nkeys, wsum[4];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const unsigned long long below = (1ull << lane) - 1ull;
+  if constexpr (W == 1) {
+    const int i = blockIdx.x * 4 + wave;
+    if (i >= A.N) return;
+    unsigned long long* keys = keys_all + wave * kWaveKeys;
+    const int e0 = edge_ptr[i], b0 = bond_ptr[i];
+    int n = 0;
+    wave_search<1>(A, i, 0, [&](int j, int n1, int n2, int n3, float dd, bool pass) {
+      const unsigned long long m = __ballot(pass);
+      const int slot = n + __popcll(m & below);
+      if (pass && slot < kWaveKeys) keys[slot] = make_key(j, n1, n2, n3, dd < A.rc2_bond);
+      n += __popcll(m);
+    });
+    n = min(n, kWaveKeys);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // two keys a lane at a time
+    for (int k0 = 0; k0 < n; k0 += 128) {
+      unsigned long long mine[2];
+      int rank[2] = {0, 0}, brank[2] = {0, 0};
+#pragma unroll
+      for (int q = 0; q < 2; ++q) mine[q] = k0 + 64 * q + lane < n ? keys[k0 + 64 * q + lane] : 0ull;
+#pragma unroll 4
+      for (int u = 0; u < n; ++u) {
+        const unsigned long long k = keys[u];
+        const int bond = (int)(k & 1ull);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const bool lt = k < mine[q];
+          rank[q] += lt ? 1 : 0;
+          brank[q] += lt ? bond : 0;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (k0 + 64 * q + lane < n) write_edge(mine[q], rank[q], brank[q], e0, b0, edge_dst, edge_img, bond_edge);
+    }
+    return;
+  }
+  unsigned long long* keys = keys_all;
+  const int i = blockIdx.x;
+  const int e0 = edge_ptr[i], b0 = bond_ptr[i];
   if (t == 0) nkeys = 0;
   __syncthreads();
-  block_search(A, i, sh, [&](int j, int n1, int n2, int n3, float dd) {
-    const int slot = atomicAdd(&nkeys, 1);
-    if (slot < sort_size) keys[slot] = make_key(j, n1, n2, n3, dd < A.rc2_bond);
+  wave_search<4>(A, i, wave, [&](int j, int n1, int n2, int n3, float dd, bool pass) {
+    const unsigned long long m = __ballot(pass);
+    if (m == 0) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&nkeys, __popcll(m));
+    base = __builtin_amdgcn_readfirstlane(base);
+    const int slot = base + __popcll(m & below);
+    if (pass && slot < sort_size) keys[slot] = make_key(j, n1, n2, n3, dd < A.rc2_bond);
   });
+  __syncthreads();
   const int count = min(nkeys, sort_size);
+  if (count <= kRankMax) {
+    for (int k = t; k < count; k += kSearchThreads) {
+      const unsigned long long mine = keys[k];
+      int rank = 0, brank = 0;
+#pragma unroll 4
+      for (int u = 0; u < count; ++u) {
+        const unsigned long long x = keys[u];
+        const bool lt = x < mine;
+        rank += lt ? 1 : 0;
+        brank += lt ? (int)(x & 1ull) : 0;
+      }
+      write_edge(mine, rank, brank, e0, b0, edge_dst, edge_img, bond_edge);
+    }
+    return;
+  }
   for (int k = count + t; k < sort_size; k += kSearchThreads) keys[k] = ~0ull;
   __syncthreads();
   // bitonic sort of sort_size (power of two) keys
@@ -491,27 +776,17 @@ __global__ void __launch_bounds__(kSearchThreads) k_fill(SearchArgs A, int sort_
       __syncthreads();
     }
   }
-  const int e0 = edge_ptr[i];
-  const int b0 = bond_ptr[i];
   int nb = 0;  // bonds written before this round of kSearchThreads keys
   for (int base = 0; base < count; base += kSearchThreads) {
     const int k = base + t;
-    bool bond = false;
-    if (k < count) {
-      const unsigned long long key = keys[k];
-      edge_dst[e0 + k] = (int)(key >> 31);
-      edge_img[(e0 + k) * 3 + 0] = (int)((key >> 21) & 1023) - kImgBias;
-      edge_img[(e0 + k) * 3 + 1] = (int)((key >> 11) & 1023) - kImgBias;
-      edge_img[(e0 + k) * 3 + 2] = (int)((key >> 1) & 1023) - kImgBias;
-      bond = (key & 1ull) != 0;
-    }
-    const unsigned long long m = __ballot(bond);
-    if (lane == 0) sh.wsum[w] = __popcll(m);
+    const unsigned long long key = k < count ? keys[k] : 0ull;
+    const unsigned long long m = __ballot(k < count && (key & 1ull));
+    if (lane == 0) wsum[wave] = __popcll(m);
     __syncthreads();
     int before = nb;
-    for (int q = 0; q < w; ++q) before += sh.wsum[q];
-    if (bond) bond_edge[b0 + before + __popcll(m & ((1ull << lane) - 1ull))] = e0 + k;
-    for (int q = 0; q < kSearchThreads / 64; ++q) nb += sh.wsum[q];
+    for (int q = 0; q < wave; ++q) before += wsum[q];
+    if (k < count) write_edge(key, k, before + __popcll(m & below), e0, b0, edge_dst, edge_img, bond_edge);
+    for (int q = 0; q < kSearchThreads / 64; ++q) nb += wsum[q];
     __syncthreads();
   }
 }
@@ -520,25 +795,54 @@ __global__ void __launch_bounds__(kSearchThreads) k_fill(SearchArgs A, int sort_
 // search always succeeds: D2 is the same number in both directions (see
 // pair_d2), and the cell list of j holds i at -n whenever that of i holds j
 // at n (both cover every pair closer than r + kMargin, while D2 < r^2 implies
-// a separation within fp32 rounding of r). The fallback value is never used.
+// a separation within fp32 rounding of r). Only the canonical direction of a
+// pair searches and writes both entries; a probe loads the image only where
+// the destination already equals i (few of a list's entries do).
 __device__ __forceinline__ void rev_atoms(int blk, int N, const int* __restrict__ edge_ptr, const int* __restrict__ edge_dst,
                                           const int* __restrict__ edge_img, int* __restrict__ edge_rev) {
   const int i = blk * 4 + (threadIdx.x >> 6);
   if (i >= N) return;
   const int lane = threadIdx.x & 63;
-  for (int e = edge_ptr[i] + lane; e < edge_ptr[i + 1]; e += 64) {
-    const int j = edge_dst[e];
-    const int t0 = -edge_img[e * 3 + 0], t1 = -edge_img[e * 3 + 1], t2 = -edge_img[e * 3 + 2];
-    int lo = edge_ptr[j], hi = edge_ptr[j + 1] - 1, found = -1;
-    while (lo <= hi) {
-      const int mid = (lo + hi) >> 1;
-      const int k0 = edge_dst[mid], k1 = edge_img[mid * 3 + 0], k2 = edge_img[mid * 3 + 1], k3 = edge_img[mid * 3 + 2];
-      int cmp = k0 != i ? (k0 < i ? -1 : 1)
-                        : (k1 != t0 ? (k1 < t0 ? -1 : 1) : (k2 != t1 ? (k2 < t1 ? -1 : 1) : (k3 != t2 ? (k3 < t2 ? -1 : 1) : 0)));
-      if (cmp == 0) { found = mid; break; }
-      if (cmp < 0) lo = mid + 1; else hi = mid - 1;
+  const int e1 = edge_ptr[i + 1];
+  // two edges a lane at once: their chains of probes overlap
+  for (int ea = edge_ptr[i] + lane; ea < e1; ea += 128) {
+    int t[2][3], lo[2], hi[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = min(ea + 64 * u, e1 - 1);
+      const int j = edge_dst[e];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) t[u][k] = -edge_img[e * 3 + k];
+      // n lexicographically negative on an atom's own image: not canonical
+      const bool neg = t[u][0] > 0 || (t[u][0] == 0 && (t[u][1] > 0 || (t[u][1] == 0 && t[u][2] > 0)));
+      const bool go = ea + 64 * u < e1 && (j > i || (j == i && !neg));
+      lo[u] = edge_ptr[j];
+      hi[u] = go ? edge_ptr[j + 1] - 1 : -1;
     }
-    edge_rev[e] = found < 0 ? e : found;
+    while (lo[0] < hi[0] || lo[1] < hi[1]) {  // first entry not below (i, -n)
+      int mid[2], k0[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        mid[u] = lo[u] < hi[u] ? (lo[u] + hi[u]) >> 1 : 0;
+        k0[u] = edge_dst[mid[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (lo[u] >= hi[u]) continue;
+        bool less = k0[u] < i;
+        if (k0[u] == i) {
+          const int k1 = edge_img[mid[u] * 3 + 0], k2 = edge_img[mid[u] * 3 + 1], k3 = edge_img[mid[u] * 3 + 2];
+          less = k1 != t[u][0] ? k1 < t[u][0] : (k2 != t[u][1] ? k2 < t[u][1] : k3 < t[u][2]);
+        }
+        if (less) lo[u] = mid[u] + 1; else hi[u] = mid[u];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (hi[u] >= 0) {
+        edge_rev[ea + 64 * u] = lo[u];
+        edge_rev[lo[u]] = ea + 64 * u;
+      }
   }
 }
 
@@ -589,8 +893,10 @@ struct GraphScratch {
   StructInfo* info;
   GraphInfo* ginfo;
   int* total_bins;
-  int *atom_struct, *atom_bin, *atom_cell, *atom_wrap;
-  int *bin_count, *bin_start, *bin_cursor, *bin_atoms;
+  AtomMeta* meta;
+  float4* bin_xyzj;
+  int* bin_wrap;
+  int *bin_count, *bin_start, *bin_cursor;
   int *edge_count, *bond_count;
   long long* angle_base;
 };
@@ -600,18 +906,32 @@ void carve(Arena& ar, int64_t N, int64_t S, GraphScratch& g) {
   g.info = ar.take<StructInfo>(S);
   g.ginfo = ar.take<GraphInfo>(1);
   g.total_bins = ar.take<int>(1);
-  g.atom_struct = ar.take<int>(N);
-  g.atom_bin = ar.take<int>(N);
-  g.atom_cell = ar.take<int>(3 * N);
-  g.atom_wrap = ar.take<int>(3 * N);
+  g.meta = ar.take<AtomMeta>(N);
+  g.bin_xyzj = ar.take<float4>(N);
+  g.bin_wrap = ar.take<int>(N);
   g.bin_count = ar.take<int>(nbins + 1);
   g.bin_start = ar.take<int>(nbins + 1);
   g.bin_cursor = ar.take<int>(nbins + 1);
-  g.bin_atoms = ar.take<int>(N);
   g.edge_count = ar.take<int>(N);
   g.bond_count = ar.take<int>(N);
   g.angle_base = ar.take<long long>(N + 1);
 }
+
+// The calling thread's pinned record for the sizes (allocated on its first
+// use): the scan kernel writes it directly, with no copy after it.
+int pinned_info(GraphInfo*& out) {
+  thread_local GraphInfo* pinned = nullptr;
+  if (!pinned) CHG_HIP(hipHostMalloc(reinterpret_cast<void**>(&pinned), sizeof(GraphInfo), hipHostMallocDefault));
+  out = pinned;
+  return CHGNET_OK;
+}
+
+// From this many atoms on, one wavefront an atom gives every SIMD of the chip
+// (1,024) one in the search kernels, and sizing the runs once an atom is
+// cheaper than four times; below it four share an atom, each taking every
+// fourth group of candidates (one 8-atom cell, 1,000 candidates an atom:
+// counting 9.0 -> 6.4 us, against one block of 256 threads in lock step).
+constexpr int kSearchWideAtoms = 1024;
 
 }  // namespace
 
@@ -645,16 +965,19 @@ int build_graph_impl(const chgnet_hparams* hp, const chgnet_batch* batch, chgnet
   if (!ws || !ar.ok()) return fail(CHGNET_EWORKSPACE, "workspace too small for the graph build");
   const int64_t nbins_cap = (int64_t)N + S + 1;
 
-  {
+  if (N <= 1024 * kBinAtomsPer && (int64_t)N + S <= kBinMax) {
+    KLAUNCH(st, "k_bin", k_bin<<<1, 1024, 0, st>>>(N, S, batch->atom_ptr, batch->pos, batch->Z, batch->lattice, hp->r_atom,
+                                                   g.info, g.meta, g.bin_start, g.bin_xyzj, g.bin_wrap, g.ginfo));
+  } else {
     const int n = (int)(nbins_cap + 1);
     KLAUNCH(st, "k_zero_scratch", k_zero_scratch<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(g.ginfo, g.bin_count, g.bin_cursor, n));
+    KLAUNCH(st, "k_struct_setup", k_struct_setup<<<1, 1024, 0, st>>>(N, S, batch->atom_ptr, batch->lattice, hp->r_atom, g.info, g.total_bins, g.ginfo));
+    KLAUNCH(st, "k_atom_bin", k_atom_bin<<<cdiv(N, 256), 256, 0, st>>>(N, S, batch->atom_ptr, batch->pos, batch->Z, g.info, g.meta,
+                                             g.bin_count, g.ginfo));
+    // total bins <= N + S (each crystal has at most max(1, n_s) bins)
+    KLAUNCH(st, "k_scan_single", k_scan_single<<<1, 1024, 0, st>>>((int)nbins_cap, g.bin_count, g.bin_start));
+    KLAUNCH(st, "k_bin_fill", k_bin_fill<<<cdiv(N, 256), 256, 0, st>>>(N, g.meta, g.bin_start, g.bin_cursor, batch->pos, g.bin_xyzj, g.bin_wrap));
   }
-  KLAUNCH(st, "k_struct_setup", k_struct_setup<<<1, 1024, 0, st>>>(S, batch->atom_ptr, batch->lattice, hp->r_atom, g.info, g.total_bins, g.ginfo));
-  KLAUNCH(st, "k_atom_bin", k_atom_bin<<<cdiv(N, 256), 256, 0, st>>>(N, S, batch->atom_ptr, batch->pos, batch->Z, g.info, g.atom_struct, g.atom_bin,
-                                           g.atom_cell, g.atom_wrap, g.bin_count, g.ginfo));
-  // total bins <= N + S (each crystal has at most max(1, n_s) bins)
-  KLAUNCH(st, "k_scan_single", k_scan_single<<<1, 1024, 0, st>>>((int)nbins_cap, g.bin_count, g.bin_start));
-  KLAUNCH(st, "k_bin_fill", k_bin_fill<<<cdiv(N, 256), 256, 0, st>>>(N, g.atom_bin, g.bin_start, g.bin_cursor, g.bin_atoms));
 
   SearchArgs A;
   A.N = N;
@@ -662,22 +985,19 @@ int build_graph_impl(const chgnet_hparams* hp, const chgnet_batch* batch, chgnet
   A.rc2_bond = candidates ? -1.0f : hp->r_bond * hp->r_bond;  // a candidate list has no bonds
   A.pos = batch->pos;
   A.info = g.info;
-  A.atom_struct = g.atom_struct;
-  A.atom_cell = g.atom_cell;
-  A.atom_wrap = g.atom_wrap;
+  A.meta = g.meta;
   A.bin_start = g.bin_start;
-  A.bin_atoms = g.bin_atoms;
-  KLAUNCH(st, "k_count", k_count<<<N, kSearchThreads, 0, st>>>(A, g.edge_count, g.bond_count));
+  A.bin_xyzj = g.bin_xyzj;
+  A.bin_wrap = g.bin_wrap;
+  const bool wide = N >= kSearchWideAtoms;
+  if (wide) KLAUNCH(st, "k_count", k_count<1><<<(unsigned)cdiv(N, 4), kSearchThreads, 0, st>>>(A, g.edge_count, g.bond_count));
+  else KLAUNCH(st, "k_count", k_count<4><<<N, kSearchThreads, 0, st>>>(A, g.edge_count, g.bond_count));
+  GraphInfo* pinned = nullptr;
+  if (pinned_readback) CHG_TRY(pinned_info(pinned));
   KLAUNCH(st, "k_scan_counts", k_scan_counts<<<1, 1024, 0, st>>>(N, g.edge_count, g.bond_count, graph->edge_ptr, graph->bond_ptr, g.angle_base,
-                                    g.ginfo));
-
-  // the sizes come back through a small pinned buffer (one per host thread,
-  // allocated on first use): a direct DMA instead of a staged pageable copy
+                                    nullptr, g.ginfo, pinned));
   GraphInfo hinfo;
-  if (pinned_readback) {
-    thread_local GraphInfo* pinned = nullptr;
-    if (!pinned) CHG_HIP(hipHostMalloc(reinterpret_cast<void**>(&pinned), sizeof(GraphInfo), hipHostMallocDefault));
-    CHG_HIP(hipMemcpyAsync(pinned, g.ginfo, sizeof(GraphInfo), hipMemcpyDeviceToHost, st));
+  if (pinned) {
     CHG_HIP(hipStreamSynchronize(st));
     hinfo = *pinned;
   } else {
@@ -702,24 +1022,29 @@ int build_graph_impl(const chgnet_hparams* hp, const chgnet_batch* batch, chgnet
     return fail(CHGNET_EINVAL, "build_graph: graph larger than 2^31 entries");
   if (hinfo.n_edges > graph->cap_edges || hinfo.n_bonds > graph->cap_bonds || hinfo.n_angles > graph->cap_angles)
     return fail(CHGNET_ECAPACITY, "build_graph: capacity too small (required sizes written to the graph)");
+  auto fill_edges = [&]() -> int {
+    if (wide && hinfo.max_count <= kWaveKeys) {
+      KLAUNCH(st, "k_fill", k_fill<1><<<(unsigned)cdiv(N, 4), kSearchThreads, sizeof(unsigned long long) * 4 * kWaveKeys, st>>>(
+                                A, 0, graph->edge_ptr, graph->bond_ptr, graph->edge_dst, graph->edge_img, graph->bond_edge));
+    } else {
+      int sort_size = 64;
+      while (sort_size < hinfo.max_count) sort_size <<= 1;
+      KLAUNCH(st, "k_fill", k_fill<4><<<N, kSearchThreads, sizeof(unsigned long long) * sort_size, st>>>(
+                                A, sort_size, graph->edge_ptr, graph->bond_ptr, graph->edge_dst, graph->edge_img, graph->bond_edge));
+    }
+    return CHGNET_OK;
+  };
   if (candidates) {
     if (hinfo.n_edges > 0 && (!graph->edge_dst || !graph->edge_img))
       return fail(CHGNET_EINVAL, "md: candidate arrays are required");
-    int sort_size = 64;
-    while (sort_size < hinfo.max_count) sort_size <<= 1;
-    KLAUNCH(st, "k_fill", k_fill<<<N, kSearchThreads, sizeof(unsigned long long) * sort_size, st>>>(
-                              A, sort_size, graph->edge_ptr, graph->bond_ptr, graph->edge_dst, graph->edge_img, nullptr));
-    return CHGNET_OK;
+    return fill_edges();
   }
   if (hinfo.n_edges > 0 && (!graph->edge_dst || !graph->edge_img || !graph->edge_rev))
     return fail(CHGNET_EINVAL, "graph: edge arrays are required");
   if (!graph->angle_ptr || (hinfo.n_bonds > 0 && !graph->bond_edge))
     return fail(CHGNET_EINVAL, "graph: bond_edge and angle_ptr are required");
 
-  int sort_size = 64;
-  while (sort_size < hinfo.max_count) sort_size <<= 1;
-  KLAUNCH(st, "k_fill", k_fill<<<N, kSearchThreads, sizeof(unsigned long long) * sort_size, st>>>(A, sort_size, graph->edge_ptr, graph->bond_ptr,
-                                                                graph->edge_dst, graph->edge_img, graph->bond_edge));
+  CHG_TRY(fill_edges());
   KLAUNCH(st, "k_rev_angles", k_rev_angles<<<2 * cdiv(N, 4), 256, 0, st>>>(N, graph->edge_ptr, graph->edge_dst, graph->edge_img,
                                                                        graph->edge_rev, graph->bond_ptr, g.angle_base,
                                                                        graph->angle_ptr, graph->angle_b2));
@@ -734,24 +1059,6 @@ int build_graph_impl(const chgnet_hparams* hp, const chgnet_batch* batch, chgnet
 // filtering it with the exact cutoff test at the current positions gives the
 // same graph, in the same order, as a full search.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_md_disp(int n, const float* __restrict__ pos, const float* __restrict__ ref,
-                                                 GraphInfo* ginfo) {
-  __shared__ float red[4];
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  float d2 = 0.f;
-  if (i < n) {
-    const float dx = pos[3 * i] - ref[3 * i], dy = pos[3 * i + 1] - ref[3 * i + 1], dz = pos[3 * i + 2] - ref[3 * i + 2];
-    d2 = dx * dx + dy * dy + dz * dz;
-  }
-  for (int off = 32; off > 0; off >>= 1) d2 = fmaxf(d2, __shfl_xor(d2, off, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = d2;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const float m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    atomicMax(&ginfo->max_disp2, __float_as_uint(m));  // non-negative floats order as their bits
-  }
-}
-
 struct CandArgs {
   int N, S;
   float rc2_atom, rc2_bond;
@@ -761,6 +1068,7 @@ struct CandArgs {
   const int* cand_ptr;
   const int* cand_dst;
   const int* cand_img;
+  const float* ref;  // positions at the list's build
 };
 
 // Cutoff test of candidate c of atom i at the current positions.
@@ -771,8 +1079,10 @@ __device__ __forceinline__ float cand_d2(const CandArgs& A, int i, const float* 
   return pair_d2(i, j, ri, rj, A.cand_img[3 * c], A.cand_img[3 * c + 1], A.cand_img[3 * c + 2], L);
 }
 
-// Edges and bonds of each atom among its candidates; one wavefront per atom.
-__global__ void __launch_bounds__(256) k_cand_count(CandArgs A, int* __restrict__ edge_count, int* __restrict__ bond_count) {
+// Edges and bonds of each atom among its candidates, and its squared
+// displacement since the list was built; one wavefront per atom.
+__global__ void __launch_bounds__(256) k_cand_count(CandArgs A, int* __restrict__ edge_count, int* __restrict__ bond_count,
+                                                    float* __restrict__ disp2) {
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (i >= A.N) return;
   const int s = find_struct(A.atom_ptr, A.S, i);
@@ -793,6 +1103,8 @@ __global__ void __launch_bounds__(256) k_cand_count(CandArgs A, int* __restrict_
   if (lane == 0) {
     edge_count[i] = ne;
     bond_count[i] = nb;
+    const float dx = ri[0] - A.ref[3 * i], dy = ri[1] - A.ref[3 * i + 1], dz = ri[2] - A.ref[3 * i + 2];
+    disp2[i] = dx * dx + dy * dy + dz * dz;
   }
 }
 
@@ -912,16 +1224,14 @@ int md_filter_graph(const chgnet_hparams* hp, const chgnet_batch* batch, const c
   GraphScratch g;
   carve(ar, N, S, g);
   if (!ws || !ar.ok()) return fail(CHGNET_EWORKSPACE, "workspace too small for the graph build");
-  KLAUNCH(st, "k_zero_scratch", k_zero_scratch<<<1, 256, 0, st>>>(g.ginfo, g.bin_count, g.bin_cursor, 1));
-  KLAUNCH(st, "k_md_disp", k_md_disp<<<(unsigned)cdiv(N, 256), 256, 0, st>>>(N, batch->pos, s->ref_pos, g.ginfo));
   CandArgs A{N, S, hp->r_atom * hp->r_atom, hp->r_bond * hp->r_bond, batch->atom_ptr, batch->pos, batch->lattice,
-             s->cand_ptr, s->cand_dst, s->cand_img};
-  KLAUNCH(st, "k_cand_count", k_cand_count<<<(unsigned)cdiv(N, 4), 256, 0, st>>>(A, g.edge_count, g.bond_count));
+             s->cand_ptr, s->cand_dst, s->cand_img, s->ref_pos};
+  float* disp2 = reinterpret_cast<float*>(g.bin_count);  // N of its N + S + 2 entries; the bins are not used here
+  KLAUNCH(st, "k_cand_count", k_cand_count<<<(unsigned)cdiv(N, 4), 256, 0, st>>>(A, g.edge_count, g.bond_count, disp2));
+  GraphInfo* pinned = nullptr;
+  CHG_TRY(pinned_info(pinned));
   KLAUNCH(st, "k_scan_counts", k_scan_counts<<<1, 1024, 0, st>>>(N, g.edge_count, g.bond_count, graph->edge_ptr,
-                                                                   graph->bond_ptr, g.angle_base, g.ginfo));
-  thread_local GraphInfo* pinned = nullptr;
-  if (!pinned) CHG_HIP(hipHostMalloc(reinterpret_cast<void**>(&pinned), sizeof(GraphInfo), hipHostMallocDefault));
-  CHG_HIP(hipMemcpyAsync(pinned, g.ginfo, sizeof(GraphInfo), hipMemcpyDeviceToHost, st));
+                                                                   graph->bond_ptr, g.angle_base, disp2, g.ginfo, pinned));
   CHG_HIP(hipStreamSynchronize(st));
   const GraphInfo hinfo = *pinned;
   // the list covers every pair within r of the current positions while twice
