@@ -44,17 +44,6 @@ __device__ __forceinline__ float wsum(float v) {
   return v;
 }
 
-template <class T>
-__device__ __forceinline__ int upper_bound_idx(const T* ptr, int n, T x) {
-  // largest s in [0, n) with ptr[s] <= x (ptr non-decreasing, ptr[0] <= x)
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (ptr[mid] <= x) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 __global__ void k_fill(float* __restrict__ p, int64_t n, float v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -99,8 +88,9 @@ __device__ __forceinline__ float envelope(float x, int p) {
   for (int k = 0; k < p; ++k) xp *= x;
   return 1.0f + xp * (a + x * (b + x * c));
 }
-__device__ __forceinline__ float srbf(float f, float d, float inv_c, int p) {
-  return sqrtf(2.0f * inv_c) * sinf(f * d * inv_c) / d * envelope(d * inv_c, p);
+// the factor of sin(f_n d / c) common to a row's functions
+__device__ __forceinline__ float srbf_pre(float d, float inv_c, int p) {
+  return sqrtf(2.0f * inv_c) / d * envelope(d * inv_c, p);
 }
 
 // Cartesian vector from atom i to the image n of atom j (fp64).
@@ -111,121 +101,162 @@ __device__ __forceinline__ void edge_vector(int i, int j, const int* __restrict_
     r[c] = (double)pos[3 * j + c] + (n0 * (double)L[c] + n1 * (double)L[3 + c] + n2 * (double)L[6 + c]) - (double)pos[3 * i + c];
 }
 
-// Geometry, bases and the atom embedding of a batch in one launch, by block
-// range: atoms (structure index, v0 = W_Z[Z - 1]); edges, 256 a block
-// (source atom, length, unit vector, then the block's sRBF rows at the atom
-// cutoff); angles (first and second bond, centre atom; cos/sin of theta from
-// (dot, |cross|) in fp64 and the Fourier basis by the complex-power
-// recurrence (cos m t + i sin m t) = (cos t + i sin t)^m).
+// Geometry, bases and the atom embedding of a batch in one launch, one block
+// per atom: its structure index and v0 = W_Z[Z - 1]; its edges (source atom,
+// length, unit vector, sRBF row at the atom cutoff); its bonds (source atom,
+// sRBF row at the bond cutoff); its angles (first and second bond, centre
+// atom; cos/sin of theta from (dot, |cross|) in fp64 and the Fourier basis by
+// the complex-power recurrence (cos m t + i sin m t) = (cos t + i sin t)^m).
+// An atom's edges, bonds and angles are contiguous, so no thread searches for
+// its atom or bond (blocks of 256 edges or angles did, 10 to 30 dependent
+// loads a thread, and the bonds took a launch of their own that read the
+// lengths back). Bound by latency on few atoms, by the sines on many; under
+// the profiler 23 -> 13 us on one 8-atom cell, 37 -> 17 us on 40 crystals of
+// 1,076 atoms, 78 -> 49 us on 128 of 5,541 (both launches against one).
 struct GeomArgs {
-  int N, S, E, B, A, D, R, K, p, nb_atoms, nb_edges;
-  float inv_ca;
+  int S, D, R, K, p;
+  float inv_ca, inv_cb;
   const int *atom_ptr, *Z, *edge_ptr, *edge_dst, *edge_img, *bond_ptr, *bond_edge, *angle_ptr;
-  const float *pos, *lattice, *WZ, *freq_a;
-  int *atom_struct, *edge_src, *ang_b1, *ang_b2, *ang_ctr;
-  float *v0, *edge_len, *edge_xhat, *rbf_a, *ft;
+  const float *pos, *lattice, *WZ, *freq_a, *freq_b;
+  int *atom_struct, *edge_src, *bond_src, *ang_b1, *ang_b2, *ang_ctr;
+  float *v0, *edge_len, *edge_xhat, *rbf_a, *rbf_b, *ft;
 };
+constexpr int kGeomBonds = 256;  // bonds whose vectors are kept in LDS (more are formed again per angle)
+
+// Fourier rows longer than 32 (K > 32) go straight out; others through LDS
+constexpr int kGeomAngles = 128;
 
 __global__ void __launch_bounds__(256) k_geom(GeomArgs g) {
-  __shared__ float dl[256];
-  int blk = blockIdx.x;
-  const int tid = threadIdx.x;
-  if (blk < g.nb_atoms) {
-    const int64_t t = (int64_t)blk * 256 + tid;
-    if (t >= (int64_t)g.N * g.D) return;
-    const int i = (int)(t / g.D), c = (int)(t % g.D);
-    g.v0[t] = g.WZ[(int64_t)(g.Z[i] - 1) * g.D + c];
-    if (c == 0) g.atom_struct[i] = upper_bound_idx(g.atom_ptr, g.S + 1, i);
-    return;
+  __shared__ float dl[256], pl[256];
+  __shared__ double rb[kGeomBonds][3];
+  __shared__ float fts[kGeomAngles * 32];
+  const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int e0 = g.edge_ptr[i], e1 = g.edge_ptr[i + 1], b0 = g.bond_ptr[i], k = g.bond_ptr[i + 1] - b0;
+  const int z = g.Z[i];
+  // the structure: last s with atom_ptr[s] <= i, 64 offsets a step (the
+  // crystals with atoms are found; empty ones before them share the offset)
+  int lo = 0, hi = g.S;  // atom_ptr[lo] <= i < atom_ptr[hi]
+  while (hi - lo > 1) {
+    const int stride = (hi - lo + 63) / 64, c = lo + lane * stride;
+    const unsigned long long m = __ballot(c < hi && g.atom_ptr[min(c, g.S)] <= i);
+    const int last = 63 - __clzll((long long)m);  // lane 0 always votes
+    const int nlo = lo + last * stride;
+    hi = min(hi, nlo + stride);
+    lo = nlo;
   }
-  blk -= g.nb_atoms;
-  if (blk < g.nb_edges) {
-    const int e0 = blk * 256, e = e0 + tid;
-    float d = 1.0f;
-    if (e < g.E) {
-      const int i = upper_bound_idx(g.edge_ptr, g.N + 1, e);
-      const int j = g.edge_dst[e];
+  const int s = lo;
+  if (tid < g.D) g.v0[(int64_t)i * g.D + tid] = g.WZ[(int64_t)(z - 1) * g.D + tid];
+  if (tid == 0) g.atom_struct[i] = s;
+  const float* L = g.lattice + 9 * s;
+  // bonds: their vectors first, so that the angles wait for nothing else
+  for (int q = tid; q < k; q += 256) {
+    const int e = g.bond_edge[b0 + q];
+    double r[3];
+    edge_vector(i, g.edge_dst[e], g.edge_img + 3 * e, L, g.pos, r);
+    if (q < kGeomBonds)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) rb[q][c] = r[c];
+    g.bond_src[b0 + q] = i;
+  }
+  // edges
+  for (int base = e0; base < e1; base += 256) {
+    const int e = base + tid;
+    if (e < e1) {
       double r[3];
-      edge_vector(i, j, g.edge_img + 3 * e, g.lattice + 9 * upper_bound_idx(g.atom_ptr, g.S + 1, i), g.pos, r);
+      edge_vector(i, g.edge_dst[e], g.edge_img + 3 * e, L, g.pos, r);
       const double dd = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+      const float d = (float)dd;
       g.edge_src[e] = i;
-      d = (float)dd;
       g.edge_len[e] = d;
       for (int c = 0; c < 3; ++c) g.edge_xhat[3 * e + c] = (float)(r[c] / dd);
+      dl[tid] = d * g.inv_ca;
+      pl[tid] = srbf_pre(d, g.inv_ca, g.p);
     }
-    dl[tid] = d;
     __syncthreads();
-    const int ne = min(256, g.E - e0);
-    float* out = g.rbf_a + (int64_t)e0 * g.R;
-    for (int t = tid; t < ne * g.R; t += 256) out[t] = srbf(g.freq_a[t % g.R], dl[t / g.R], g.inv_ca, g.p);
-    return;
-  }
-  blk -= g.nb_edges;
-  const int a0 = blk * 256, al = a0 + tid;
-  const int na = min(256, g.A - a0);
-  // the block's Fourier rows go through LDS, so that they are written as
-  // one contiguous run
-  __shared__ float fts[256 * 32];
-  if (al < g.A) {
-    const int b1 = upper_bound_idx(g.angle_ptr, g.B + 1, al);
-    const int i = upper_bound_idx(g.bond_ptr, g.N + 1, b1);
-    const int k0 = g.bond_ptr[i];
-    const int p = b1 - k0;
-    const int q0 = al - g.angle_ptr[b1];
-    const int b2 = k0 + (q0 < p ? q0 : q0 + 1);
-    g.ang_b1[al] = b1;
-    g.ang_b2[al] = b2;
-    g.ang_ctr[al] = i;
-    const float* L = g.lattice + 9 * upper_bound_idx(g.atom_ptr, g.S + 1, i);
-    double r[2][3];
-    const int es[2] = {g.bond_edge[b1], g.bond_edge[b2]};
-    for (int s = 0; s < 2; ++s) edge_vector(i, g.edge_dst[es[s]], g.edge_img + 3 * es[s], L, g.pos, r[s]);
-    const double dot = r[0][0] * r[1][0] + r[0][1] * r[1][1] + r[0][2] * r[1][2];
-    const double cx = r[0][1] * r[1][2] - r[0][2] * r[1][1];
-    const double cy = r[0][2] * r[1][0] - r[0][0] * r[1][2];
-    const double cz = r[0][0] * r[1][1] - r[0][1] * r[1][0];
-    const double cr = sqrt(cx * cx + cy * cy + cz * cz);
-    const double h = sqrt(dot * dot + cr * cr);
-    const double c1 = dot / h, s1 = cr / h;
-    const int M = (g.K - 1) / 2;
-    // n_fourier up to 32 is staged (the default 31); longer rows go straight out
-    float* o = g.K <= 32 ? fts + tid * g.K : g.ft + (int64_t)al * g.K;
-    const double inv_sqrt_pi = 0.56418958354775628695;
-    o[0] = (float)(inv_sqrt_pi * 0.70710678118654752440);
-    double cm = 1.0, sm = 0.0;
-    for (int m = 1; m <= M; ++m) {
-      const double cn = cm * c1 - sm * s1, sn = sm * c1 + cm * s1;
-      cm = cn;
-      sm = sn;
-      o[m] = (float)(cm * inv_sqrt_pi);
-      o[M + m] = (float)(sm * inv_sqrt_pi);
+    const int ne = min(256, e1 - base);
+    float* out = g.rbf_a + (int64_t)base * g.R;
+    for (int t = tid; t < ne * g.R; t += 256) {
+      const int row = t / g.R;
+      out[t] = pl[row] * sinf(g.freq_a[t - row * g.R] * dl[row]);
     }
+    __syncthreads();
   }
-  if (g.K > 32) return;  // uniform over the block
-  __syncthreads();
-  float* out = g.ft + (int64_t)a0 * g.K;
-  for (int t = tid; t < na * g.K; t += 256) out[t] = fts[t];
-}
-
-// Per bond (256 a block): source atom and the block's sRBF rows at the bond
-// cutoff (from the edge lengths).
-__global__ void __launch_bounds__(256) k_bond_geom(int B, int R, int p, float inv_c, const int* __restrict__ bond_edge,
-                                                   const int* __restrict__ edge_src, const float* __restrict__ edge_len,
-                                                   const float* __restrict__ freq, int* __restrict__ bond_src,
-                                                   float* __restrict__ rbf_b) {
-  __shared__ float dl[256];
-  const int b0 = blockIdx.x * 256, b = b0 + threadIdx.x;
-  float d = 1.0f;
-  if (b < B) {
-    const int e = bond_edge[b];
-    bond_src[b] = edge_src[e];
-    d = edge_len[e];
+  // bond basis rows
+  for (int base = 0; base < k; base += 256) {
+    const int q = base + tid;
+    if (q < k) {
+      double r[3];
+      if (q < kGeomBonds) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) r[c] = rb[q][c];
+      } else {
+        const int e = g.bond_edge[b0 + q];
+        edge_vector(i, g.edge_dst[e], g.edge_img + 3 * e, L, g.pos, r);
+      }
+      const float d = (float)sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+      dl[tid] = d * g.inv_cb;
+      pl[tid] = srbf_pre(d, g.inv_cb, g.p);
+    }
+    __syncthreads();
+    const int nk = min(256, k - base);
+    float* out = g.rbf_b + (int64_t)(b0 + base) * g.R;
+    for (int t = tid; t < nk * g.R; t += 256) {
+      const int row = t / g.R;
+      out[t] = pl[row] * sinf(g.freq_b[t - row * g.R] * dl[row]);
+    }
+    __syncthreads();
   }
-  dl[threadIdx.x] = d;
-  __syncthreads();
-  const int nbk = min(256, B - b0);
-  float* out = rbf_b + (int64_t)b0 * R;
-  for (int t = threadIdx.x; t < nbk * R; t += 256) out[t] = srbf(freq[t % R], dl[t / R], inv_c, p);
+  if (k < 2) return;  // uniform over the block
+  const int na = k * (k - 1);
+  const int64_t a0 = g.angle_ptr[b0];
+  const int M = (g.K - 1) / 2;
+  const bool staged = g.K <= 32;
+  for (int base = 0; base < na; base += kGeomAngles) {
+    const int x = base + tid;
+    if (tid < kGeomAngles && x < na) {
+      const int p = x / (k - 1), q0 = x - p * (k - 1), q = q0 < p ? q0 : q0 + 1;
+      const int64_t al = a0 + x;
+      g.ang_b1[al] = b0 + p;
+      g.ang_b2[al] = b0 + q;
+      g.ang_ctr[al] = i;
+      double r[2][3];
+      const int qs[2] = {p, q};
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (qs[u] < kGeomBonds) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) r[u][c] = rb[qs[u]][c];
+        } else {
+          const int e = g.bond_edge[b0 + qs[u]];
+          edge_vector(i, g.edge_dst[e], g.edge_img + 3 * e, L, g.pos, r[u]);
+        }
+      }
+      const double dot = r[0][0] * r[1][0] + r[0][1] * r[1][1] + r[0][2] * r[1][2];
+      const double cx = r[0][1] * r[1][2] - r[0][2] * r[1][1];
+      const double cy = r[0][2] * r[1][0] - r[0][0] * r[1][2];
+      const double cz = r[0][0] * r[1][1] - r[0][1] * r[1][0];
+      const double cr = sqrt(cx * cx + cy * cy + cz * cz);
+      const double h = sqrt(dot * dot + cr * cr);
+      const double c1 = dot / h, s1 = cr / h;
+      float* o = staged ? fts + tid * g.K : g.ft + al * g.K;
+      const double inv_sqrt_pi = 0.56418958354775628695;
+      o[0] = (float)(inv_sqrt_pi * 0.70710678118654752440);
+      double cm = 1.0, sm = 0.0;
+      for (int m = 1; m <= M; ++m) {
+        const double cn = cm * c1 - sm * s1, sn = sm * c1 + cm * s1;
+        cm = cn;
+        sm = sn;
+        o[m] = (float)(cm * inv_sqrt_pi);
+        o[M + m] = (float)(sm * inv_sqrt_pi);
+      }
+    }
+    if (!staged) continue;  // uniform over the block
+    __syncthreads();
+    float* out = g.ft + (a0 + base) * g.K;
+    const int n = min(kGeomAngles, na - base) * g.K;
+    for (int t = tid; t < n; t += 256) out[t] = fts[t];
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2836,23 +2867,18 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
   // geometry, bases and v0 (Eq. 2)
   {
     GeomArgs ga{};
-    ga.N = (int)N; ga.S = (int)S; ga.E = (int)E; ga.B = (int)B; ga.A = (int)A; ga.D = D; ga.R = m.R; ga.K = m.K;
+    ga.S = (int)S; ga.D = D; ga.R = m.R; ga.K = m.K;
     ga.p = c.hp->envelope_p;
     ga.inv_ca = 1.0f / c.hp->r_atom;
-    ga.nb_atoms = (int)cdiv(N * D, 256);
-    ga.nb_edges = (int)cdiv(E, 256);
+    ga.inv_cb = 1.0f / c.hp->r_bond;
     ga.atom_ptr = bt.atom_ptr; ga.Z = bt.Z; ga.edge_ptr = g.edge_ptr; ga.edge_dst = g.edge_dst; ga.edge_img = g.edge_img;
     ga.bond_ptr = g.bond_ptr; ga.bond_edge = g.bond_edge; ga.angle_ptr = g.angle_ptr;
-    ga.pos = bt.pos; ga.lattice = bt.lattice; ga.WZ = P + L.W_Z; ga.freq_a = P + L.f_a;
-    ga.atom_struct = a.atom_struct; ga.edge_src = a.edge_src; ga.ang_b1 = a.ang_b1; ga.ang_b2 = a.ang_b2; ga.ang_ctr = a.ang_ctr;
-    ga.v0 = a.v[0]; ga.edge_len = a.edge_len; ga.edge_xhat = a.edge_xhat; ga.rbf_a = a.rbf_a; ga.ft = a.ft;
-    const int64_t blocks = ga.nb_atoms + ga.nb_edges + cdiv(A, 256);
-    KLAUNCH(st, "k_geom", k_geom<<<(unsigned)blocks, 256, 0, st>>>(ga));
+    ga.pos = bt.pos; ga.lattice = bt.lattice; ga.WZ = P + L.W_Z; ga.freq_a = P + L.f_a; ga.freq_b = P + L.f_b;
+    ga.atom_struct = a.atom_struct; ga.edge_src = a.edge_src; ga.bond_src = a.bond_src;
+    ga.ang_b1 = a.ang_b1; ga.ang_b2 = a.ang_b2; ga.ang_ctr = a.ang_ctr;
+    ga.v0 = a.v[0]; ga.edge_len = a.edge_len; ga.edge_xhat = a.edge_xhat; ga.rbf_a = a.rbf_a; ga.rbf_b = a.rbf_b; ga.ft = a.ft;
+    KLAUNCH(st, "k_geom", k_geom<<<(unsigned)N, 256, 0, st>>>(ga));
   }
-  if (B > 0)
-    KLAUNCH(st, "k_bond_geom", k_bond_geom<<<(unsigned)cdiv(B, 256), 256, 0, st>>>((int)B, m.R, c.hp->envelope_p,
-                                                                              1.0f / c.hp->r_bond, g.bond_edge, a.edge_src,
-                                                                              a.edge_len, P + L.f_b, a.bond_src, a.rbf_b));
   {
     std::vector<GemmProblem> ps;
     GemmProblem p = gp(E, D, a.e[0], D);
