@@ -412,7 +412,7 @@ enum GateFwdMode { FWD_ATOM = 0, FWD_BOND = 1, FWD_ANGLE = 2 };
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 struct GateMmJob {
-  int mode, rows, tile0;
+  int mode, rows, ntiles;
   const float* x;  // [rows, d]
   const float* W;  // [d, 2d] core | gate columns, row stride ldw
   int ldw;
@@ -427,11 +427,62 @@ struct GateMmJob {
   float* xcopy;  // optional [rows, d]: a copy of x (the residual part of e^{t+1})
 };
 struct GateMmJobs {
-  int n, ntiles;
+  int n;
   GateMmJob j[3];
 };
 
 constexpr int kMmCpl = 8;
+
+// Deal of the tiles of up to three jobs to the blocks of a launch. Blocks are
+// dealt to the 8 XCDs in turn; XCD x takes the x-th eighth of every job's
+// tiles in order, its blocks taking them in turn, so that neighbouring tiles
+// (angles of one centre, edges of one atom: the same gathered table rows) run
+// on one XCD at about the same time and share its L2.
+struct XcdTiles {
+  int start[3], count[3], total;  // this XCD's tiles of each job
+  __device__ __forceinline__ void set(int k, int ntiles) {
+    const int x = (int)blockIdx.x & 7;
+    start[k] = (int)((int64_t)ntiles * x / 8);
+    count[k] = (int)((int64_t)ntiles * (x + 1) / 8) - start[k];
+  }
+  // the block's i-th tile: its job and the tile within the job
+  __device__ __forceinline__ int tile(int i, int& k) const {
+    int l = ((int)blockIdx.x >> 3) + i * ((int)gridDim.x >> 3);
+    k = 0;
+    if (l >= count[0]) {
+      l -= count[0];
+      k = 1;
+      if (l >= count[1]) {
+        l -= count[1];
+        k = 2;
+      }
+    }
+    return (k == 0 ? start[0] : k == 1 ? start[1] : start[2]) + l;
+  }
+  __device__ __forceinline__ int tiles_of_block() const {
+    const int s = (int)blockIdx.x >> 3, g = (int)gridDim.x >> 3;
+    return s < total ? (total - 1 - s) / g + 1 : 0;
+  }
+};
+template <class Jobs>
+__device__ __forceinline__ XcdTiles xcd_tiles(const Jobs& J) {
+  XcdTiles t;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) t.set(k, k < J.n ? J.j[k].ntiles : 0);
+  t.total = t.count[0] + t.count[1] + t.count[2];
+  return t;
+}
+// blocks of such a launch: 8 times the largest XCD's tile count, at most one
+// a compute unit
+inline int xcd_grid(const int* ntiles, int n) {
+  int most = 0;
+  for (int x = 0; x < 8; ++x) {
+    int c = 0;
+    for (int k = 0; k < n; ++k) c += (int)((int64_t)ntiles[k] * (x + 1) / 8) - (int)((int64_t)ntiles[k] * x / 8);
+    most = std::max(most, c);
+  }
+  return std::min(8 * most, 256);
+}
 
 // Wave priority of the consumer wavefronts in the fused gate kernels. The
 // consumers' chains of dependent loads set the pace of a tile; ahead of the
@@ -461,11 +512,19 @@ constexpr int kMmRows = MmCfg<64>::Rows;
 constexpr int kMmProducers = MmCfg<64>::Prod, kMmConsumers = MmCfg<64>::Cons;
 constexpr int kMmThreads = MmCfg<64>::Threads;
 
+// the wavefront's LDS writes are visible to all its lanes
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Gathered operands of one gate row (the atom/bond terms of the split first
 // layer and the multiplier row), loaded one tile ahead of their use; the
 // row indices are loaded one tile ahead of that.
 struct GateRowIn {
   float ac[kMaxAdds][kMmCpl], ag[kMaxAdds][kMmCpl], mv[kMmCpl];
+  int seg;  // the row's segment (the source atom, the first bond)
 };
 
 __device__ __forceinline__ void gate_mm_index(const GateMmJob& J, int row, int (&ix)[kMaxAdds + 1]) {
@@ -479,6 +538,7 @@ template <int D>
 __device__ __forceinline__ void gate_mm_gather(const GateMmJob& J, const int (&ix)[kMaxAdds + 1], GateRowIn& in) {
   constexpr int CPL = kMmCpl;
   const int j = (threadIdx.x & 63) % Lanes<D, CPL>::LPR;
+  in.seg = ix[0];
 #pragma unroll
   for (int q = 0; q < kMaxAdds; ++q) {
     if (q >= J.ad.n) break;
@@ -494,13 +554,30 @@ struct GateLnRegs {
   float gc[kMmCpl], bc[kMmCpl], gg[kMmCpl], bg[kMmCpl];
 };
 
+// The messages (FWD_ATOM, FWD_BOND) are summed over a segment's rows next, so
+// a wavefront first adds up the rows of each run of one segment among its RPW
+// consecutive rows: the row that ends the run (the last of a group of RPW
+// rows, or the segment's last) gets the run's sum, the others are not
+// written, and the segmented sum reads those rows only (SegJob::group). The
+// rows go through the wavefront's own rows of the z tile, a lane then holding
+// D / 64 columns of every row; rows are added in order. An atom's 76 rows of
+// messages become about 10 at d = 64 (20 at d = 128), a bond's 8 about 2 (3):
+// on 4,096 atoms (d = 64) 157 MB of messages were written and read back a
+// layer, and the segmented sum goes from 93 to 68 us a launch; on wide128 from
+// 112 to 91 us on average, with the gate 3 % faster.
 template <int D, int MODE>
-__device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr, const float* Zs, const GateRowIn& in,
+__device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr, float* Zs, const GateRowIn& in,
                                             const GateLnRegs& ln) {
   constexpr int CPL = kMmCpl;
   using L = Lanes<D, CPL>;
-  const int j = (threadIdx.x & 63) % L::LPR;
-  if (row >= J.rows) return;
+  const int lane = threadIdx.x & 63, j = lane % L::LPR;
+  unsigned long long ends = 0;  // lane 0 of each row that ends a run
+  if (MODE != FWD_ANGLE) {
+    const int next = __shfl_down(in.seg, L::LPR);
+    ends = __ballot(j == 0 && row < J.rows && (lane >= 64 - L::LPR || row + 1 >= J.rows || next != in.seg));
+  } else if (row >= J.rows) {
+    return;
+  }
   float zc[CPL], zg[CPL], rc, rg;
   {
     // odd rows of the z tile hold the two 32-column halves of each 64-column
@@ -526,7 +603,7 @@ __device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr,
       zg[k] += in.ag[q][k];
     }
   }
-  if (J.zsave) {
+  if (J.zsave && row < J.rows) {
     store_cols_nt<D, CPL>(J.zsave + (int64_t)row * J.ldzs, j, zc);
     store_cols_nt<D, CPL>(J.zsave + (int64_t)row * J.ldzs + D, j, zg);
   }
@@ -539,7 +616,38 @@ __device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr,
     const float phi = yc * sigm(yc) * sigm(yg);
     o[k] = MODE == FWD_ANGLE ? in.mv[k] + phi : in.mv[k] * phi;
   }
-  store_cols<D, CPL>(J.out + (int64_t)row * D, j, o);
+  if (MODE == FWD_ANGLE) {
+    store_cols<D, CPL>(J.out + (int64_t)row * D, j, o);
+    return;
+  }
+  {
+    float* zr = Zs + lr * MmCfg<D>::Zld;
+    const int sw = (lr & 1) * 32;
+#pragma unroll
+    for (int q = 0; q < CPL / 4; ++q)
+      *reinterpret_cast<float4*>(zr + ((q * L::STRIDE + 4 * j) ^ sw)) =
+          make_float4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
+  }
+  wave_lds_sync();
+  constexpr int CW = D / 64;  // columns a lane
+  const int lr0 = __builtin_amdgcn_readfirstlane(lr), row0 = __builtin_amdgcn_readfirstlane(row);
+  float acc[CW];
+#pragma unroll
+  for (int c = 0; c < CW; ++c) acc[c] = 0.f;
+#pragma unroll
+  for (int r = 0; r < L::RPW; ++r) {
+    const float* zr = Zs + (lr0 + r) * MmCfg<D>::Zld;
+#pragma unroll
+    for (int c = 0; c < CW; ++c) acc[c] += zr[(64 * c + lane) ^ (((lr0 + r) & 1) * 32)];
+    if ((ends >> (r * L::LPR)) & 1) {  // uniform over the wavefront
+      float* out = J.out + (int64_t)(row0 + r) * D + lane;
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        out[64 * c] = acc[c];
+        acc[c] = 0.f;
+      }
+    }
+  }
 }
 
 // Producer and consumer wavefronts: the producers form z of tile i (x tile
@@ -633,8 +741,7 @@ __device__ __forceinline__ void mm_tile(const float* X, float* Z, const float (&
       Z[(32 * s + 8 * (e >> 2) + 4 * h + (e & 3)) * C::Zld + ((32 * wave + l32) ^ ((e & 1) * 32))] = acc[s][e] + bias;
 }
 
-// One block per compute unit, walking tiles blockIdx.x, blockIdx.x +
-// gridDim.x, ... of the concatenated jobs.
+// One block per compute unit, walking its share of the jobs' tiles (XcdTiles).
 template <int D>
 __global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs J) {
   using C = MmCfg<D>;
@@ -651,42 +758,40 @@ __global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs
       LnS[jb][q][c] = (q == 0 ? ln.gc : q == 1 ? ln.bc : q == 2 ? ln.gg : ln.bg)[c];
     }
   }
-  auto job_of = [&](int tile) {
-    int k = 0;
-    while (k + 1 < J.n && tile >= J.j[k + 1].tile0) ++k;
-    return k;
-  };
-  const int nt = (int)blockIdx.x < J.ntiles ? (J.ntiles - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
+  const XcdTiles T = xcd_tiles(J);
+  const int nt = T.tiles_of_block();
   if (nt == 0) return;
-  auto tile_of = [&](int i) { return (int)blockIdx.x + i * (int)gridDim.x; };
   if (wave < C::Prod) {
     float4 xv[C::F / 4];
-    auto fetch_x = [&](int tile) {
-      const GateMmJob& jb = J.j[job_of(tile)];
-      mm_fetch_x<D>(jb.x, jb.rows, (tile - jb.tile0) * C::Rows, xv);
+    auto fetch_x = [&](int i) {
+      int k;
+      const int tile = T.tile(i, k);
+      mm_fetch_x<D>(J.j[k].x, J.j[k].rows, tile * C::Rows, xv);
     };
-    auto copy_x = [&](int tile) {
-      const GateMmJob& jb = J.j[job_of(tile)];
-      if (jb.xcopy) mm_copy_x<D>(jb.xcopy, jb.rows, (tile - jb.tile0) * C::Rows, xv);
+    auto copy_x = [&](int i) {
+      int k;
+      const int tile = T.tile(i, k);
+      if (J.j[k].xcopy) mm_copy_x<D>(J.j[k].xcopy, J.j[k].rows, tile * C::Rows, xv);
     };
     int cur = -1;
     float bfr[C::KB][16], bias = 0.f;
-    fetch_x(tile_of(0));
+    fetch_x(0);
     mm_store_x<D>(Xs[0], xv);
-    copy_x(tile_of(0));
-    if (nt > 1) fetch_x(tile_of(1));
+    copy_x(0);
+    if (nt > 1) fetch_x(1);
     __syncthreads();
     for (int i = 0; i <= nt; ++i) {
       if (i < nt) {
-        const int k = job_of(tile_of(i));
+        int k;
+        T.tile(i, k);
         if (k != cur) {
           cur = k;
           mm_load_w<D>(J.j[k].W, J.j[k].ldw, J.j[k].bias, wave, bfr, bias);
         }
         if (i + 1 < nt) {
           mm_store_x<D>(Xs[(i + 1) & 1], xv);
-          copy_x(tile_of(i + 1));
-          if (i + 2 < nt) fetch_x(tile_of(i + 2));
+          copy_x(i + 1);
+          if (i + 2 < nt) fetch_x(i + 2);
         }
         mm_tile<D>(Xs[i & 1], Zs[i & 1], bfr, bias, wave);
       }
@@ -698,23 +803,28 @@ __global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs
     // indices of the one after
     using GL = Lanes<D, kMmCpl>;
     const int lr = (wave - C::Prod) * GL::RPW + lane / GL::LPR;
-    auto row_of = [&](int tile, const GateMmJob& jb) { return (tile - jb.tile0) * C::Rows + lr; };
     GateRowIn in;
     GateLnRegs lnr;
     int lnjob = -1;
     int ix[kMaxAdds + 1];
-    const GateMmJob& j0 = J.j[job_of(tile_of(0))];
-    gate_mm_index(j0, row_of(tile_of(0), j0), ix);
-    gate_mm_gather<D>(j0, ix, in);
-    if (nt > 1) {
-      const GateMmJob& j1 = J.j[job_of(tile_of(1))];
-      gate_mm_index(j1, row_of(tile_of(1), j1), ix);
-    }
+    auto index = [&](int i) {
+      int k;
+      const int tile = T.tile(i, k);
+      gate_mm_index(J.j[k], tile * C::Rows + lr, ix);
+    };
+    auto gather = [&](int i) {
+      int k;
+      T.tile(i, k);
+      gate_mm_gather<D>(J.j[k], ix, in);
+    };
+    index(0);
+    gather(0);
+    if (nt > 1) index(1);
     __syncthreads();
     for (int i = 0; i <= nt; ++i) {
       if (i > 0) {
-        const int tile = tile_of(i - 1);
-        const int k = job_of(tile);
+        int k;
+        const int tile = T.tile(i - 1, k);
         const GateMmJob& jb = J.j[k];
         if (k != lnjob) {
           lnjob = k;
@@ -724,18 +834,17 @@ __global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs
           load_cols<D, kMmCpl>(LnS[k][2], jl, lnr.gg);
           load_cols<D, kMmCpl>(LnS[k][3], jl, lnr.bg);
         }
-        const int row = row_of(tile, jb);
-        const float* Z = Zs[(i - 1) & 1];
+        const int row = tile * C::Rows + lr;
+        float* Z = Zs[(i - 1) & 1];
         if (jb.mode == FWD_ATOM) gate_mm_row<D, FWD_ATOM>(jb, row, lr, Z, in, lnr);
         else if (jb.mode == FWD_BOND) gate_mm_row<D, FWD_BOND>(jb, row, lr, Z, in, lnr);
         else gate_mm_row<D, FWD_ANGLE>(jb, row, lr, Z, in, lnr);
+        // (issued before the rows are computed, into a second set of
+        // registers, the gathers made the launch 12 % slower at d = 64 and
+        // spill at d = 128)
         if (i < nt) {
-          const GateMmJob& jn = J.j[job_of(tile_of(i))];
-          gate_mm_gather<D>(jn, ix, in);
-          if (i + 1 < nt) {
-            const GateMmJob& jm = J.j[job_of(tile_of(i + 1))];
-            gate_mm_index(jm, row_of(tile_of(i + 1), jm), ix);
-          }
+          gather(i);
+          if (i + 1 < nt) index(i + 1);
         }
       }
       __syncthreads();
@@ -1511,13 +1620,6 @@ __device__ __forceinline__ void hd_epilogue(const v16f (&acc)[2], const float* _
   }
 }
 
-// the wavefront's LDS writes are visible to all its lanes
-__device__ __forceinline__ void hd_wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __global__ void __launch_bounds__(256, 2) k_head_mlp(HeadJobs J) {
   __shared__ __attribute__((aligned(16))) float T[4][kHdRows * kHdLd];
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
@@ -1545,7 +1647,7 @@ __global__ void __launch_bounds__(256, 2) k_head_mlp(HeadJobs J) {
     v16f acc[2];
     hd_layer(af, bf, acc);
     hd_epilogue(acc, jb.b1, jb.rows, row0, jb.h1, jb.a1, Tw, lane);
-    hd_wave_sync();
+    wave_lds_sync();
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -1554,10 +1656,10 @@ __global__ void __launch_bounds__(256, 2) k_head_mlp(HeadJobs J) {
         af[kb][4 * q] = v.x; af[kb][4 * q + 1] = v.y; af[kb][4 * q + 2] = v.z; af[kb][4 * q + 3] = v.w;
       }
     hd_bfrag(jb.W2, lane, bf);
-    hd_wave_sync();
+    wave_lds_sync();
     hd_layer(af, bf, acc);
     hd_epilogue(acc, jb.b2, jb.rows, row0, jb.h2, jb.a2, Tw, lane);
-    hd_wave_sync();
+    wave_lds_sync();
     // output layer: lane (row l32, half h) sums k in [32 h, 32 h + 32)
     for (int c = 0; c < jb.out; ++c) {
       float s = 0.f;
@@ -1566,7 +1668,7 @@ __global__ void __launch_bounds__(256, 2) k_head_mlp(HeadJobs J) {
       s += __shfl_xor(s, 32);
       if (h == 0 && valid) jb.o[(int64_t)row * jb.out + c] = s + jb.b3[c];
     }
-    hd_wave_sync();
+    wave_lds_sync();
   }
 }
 
@@ -1578,6 +1680,9 @@ __global__ void __launch_bounds__(256, 2) k_head_mlp(HeadJobs J) {
 struct SegJob {
   int nseg, ncb, width, ld_in, ld_out, ld_mul, ld_out2, accumulate, block0;
   int wps;  // wavefronts per (segment, column block): 4 for long segments, 1 for short
+  // > 1: the rows hold sums of runs (see gate_mm_row): of a segment's rows
+  // only the last of each group of `group` rows, and the last, are summed
+  int group;
   int lpr;  // set by the launch: 0, one column a lane; else lanes per row, four columns a lane
   // set by the launch on the first job of a pair: the pair's block count (a
   // multiple of 8); the two jobs' blocks are interleaved (see k_segsum)
@@ -1611,18 +1716,23 @@ __device__ __forceinline__ void segsum_block(const SegJob& S, float (*red)[64], 
   const bool ok = s < S.nseg && c < S.width;
   float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
   if (ok) {
-    const int lo = S.ptr[s], hi = S.ptr[s + 1];
+    int lo = S.ptr[s], hi = S.ptr[s + 1];
+    const int last = hi - 1, G = S.group;
+    if (G > 1 && hi > lo) {
+      lo /= G;
+      hi = last / G + 1;
+    }
+    auto at = [&](int r) -> int64_t { return S.idx ? S.idx[r] : G > 1 ? min(r * G + G - 1, last) : r; };
     int r = lo + 4 * w;
     for (; r + 3 < hi; r += 4 * WPS) {
-      const int64_t i0 = S.idx ? S.idx[r] : r, i1 = S.idx ? S.idx[r + 1] : r + 1, i2 = S.idx ? S.idx[r + 2] : r + 2,
-                    i3 = S.idx ? S.idx[r + 3] : r + 3;
+      const int64_t i0 = at(r), i1 = at(r + 1), i2 = at(r + 2), i3 = at(r + 3);
       a0 += S.vals[i0 * S.ld_in + c];
       a1 += S.vals[i1 * S.ld_in + c];
       a2 += S.vals[i2 * S.ld_in + c];
       a3 += S.vals[i3 * S.ld_in + c];
     }
     // r is now the start of one of this wave's groups: its partial tail
-    for (; r < hi; ++r) a0 += S.vals[(int64_t)(S.idx ? S.idx[r] : r) * S.ld_in + c];
+    for (; r < hi; ++r) a0 += S.vals[at(r) * S.ld_in + c];
   }
   float acc = (a0 + a1) + (a2 + a3);
   if (WPS > 1) {
@@ -1674,14 +1784,19 @@ __device__ __forceinline__ void segsum_block4(const SegJob& S, float4 (*red4)[64
 #pragma unroll
   for (int u = 0; u < U; ++u) a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
   if (ok) {
-    const int lo = S.ptr[s], hi = S.ptr[s + 1];
+    int lo = S.ptr[s], hi = S.ptr[s + 1];
+    const int last = hi - 1, gr = S.group;
+    if (!IDX && gr > 1 && hi > lo) {
+      lo /= gr;
+      hi = last / gr + 1;
+    }
     const float* __restrict__ vals = S.vals + c;
     int ix[U];
     auto rows_of = [&](int g) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int r = min(g + u * RPI + sub, hi - 1);
-        ix[u] = IDX ? S.idx[r] : r;
+        ix[u] = IDX ? S.idx[r] : gr > 1 ? min(r * gr + gr - 1, last) : r;
       }
     };
     int g = lo + G * w;
@@ -2656,17 +2771,15 @@ int pack_params(const ParamLayout& L, const ParamLayout& La, const float* P, flo
 int gate_fwd_mm_launch(int D, GateMmJobs J, hipStream_t st) {
   const int rows_per_tile = D == 64 ? MmCfg<64>::Rows : MmCfg<128>::Rows;
   GateMmJobs K{};
-  int tiles = 0;
+  int nt[3];
   for (int i = 0; i < J.n; ++i) {
     if (J.j[i].rows <= 0) continue;
     K.j[K.n] = J.j[i];
-    K.j[K.n].tile0 = tiles;
-    tiles += (int)cdiv(J.j[i].rows, rows_per_tile);
+    nt[K.n] = K.j[K.n].ntiles = (int)cdiv(J.j[i].rows, rows_per_tile);
     K.n++;
   }
-  K.ntiles = tiles;
-  if (tiles == 0) return CHGNET_OK;
-  const int grid = std::min(tiles, 256);
+  const int grid = xcd_grid(nt, K.n);
+  if (grid == 0) return CHGNET_OK;
   if (D == 64) KLAUNCH(st, "k_gate_fwd", k_gate_fwd_mm<64><<<grid, MmCfg<64>::Threads, 0, st>>>(K));
   else KLAUNCH(st, "k_gate_fwd", k_gate_fwd_mm<128><<<grid, MmCfg<128>::Threads, 0, st>>>(K));
   return CHGNET_OK;
@@ -2971,12 +3084,15 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     // at d = 64 the same launch applies the output linears of the updates
     // (v' = v + m Wo + bo; e'_b = e_b + mu Wo + bo): a wavefront holds a row
     const bool fuse_upd = D == 64;
+    // rows of a consumer wavefront of the gates, whose runs it has summed
+    const int run_rows = D == 64 ? Lanes<64, kMmCpl>::RPW : Lanes<128, kMmCpl>::RPW;
     auto messages = [&](int which) -> int {
       SegJobs J{};
       if (which & 1) {
         SegJob& q = J.j[J.n++];
         q = seg_job(N, g.edge_ptr, nullptr, a.msg, D, D, a.m[t], D);
         q.wps = 4;
+        q.group = run_rows;
         if (fuse_upd) {
           q.Wo = P + lo.av_Wo;
           q.bo = P + lo.av_bo;
@@ -2988,6 +3104,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
         SegJob& q = J.j[J.n++];
         q = seg_job(B, g.angle_ptr, nullptr, a.msgb, D, D, a.ssum[t], D, a.eb, D, a.mu[t], D);
         q.wps = 1;
+        q.group = run_rows;
         if (fuse_upd) {
           q.Wo = P + lo.be_Wo;
           q.bo = P + lo.be_bo;
