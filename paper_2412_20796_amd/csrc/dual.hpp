@@ -849,7 +849,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
     p = gp(A, D, d.a_t[0], D);
     seg(p, d.ft_t, K, 0, K, P + L.W_th, D, 0);
     ps.push_back(p);
-    CHG_TRY(run_gemms(ps, st, "kd_gemm"));
+    CHG_TRY(run_gemms(c, ps, st, "kd_gemm"));
   }
   CHG_TRY(fill(d.v_t[0], N * D, 0.f, st));
 
@@ -923,7 +923,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
         ps.push_back(p);
         ps.push_back(tangent_of(p, {d.a_t[t]}, d.zan[t][1], nullptr));
       }
-      return run_gemms(ps, st, "kd_gemm");
+      return run_gemms(c, ps, st, "kd_gemm");
     };
     auto gates_fwd = [&](int which) -> int {
       DnGates J{};
@@ -999,7 +999,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
         p.c_rows = g.bond_edge;
         ps.push_back(p);
       }
-      return run_gemms(ps, st, "kd_gemm");
+      return run_gemms(c, ps, st, "kd_gemm");
     };
     if (!seq) {
       CHG_TRY(project(ang ? 7 : 3, a.v[t], d.v_t[t], a.e[t], d.e_t[t]));
@@ -1032,7 +1032,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
     GemmProblem p = gp(M, Nc, C, ldc);
     seg(p, Ain, lda, 0, Kd, W, ldw, trans);
     ps.push_back(p);
-    return run_gemms(ps, st, "kd_gemm");
+    return run_gemms(c, ps, st, "kd_gemm");
   };
   CHG_TRY(gemm1(N, D, d.h1_t, D, d.v_t[m.T], D, D, P + hE.W1, D, 0));
   KLAUNCH(st, "kd_head", kd_act<<<dn_blocks(ND), 256, 0, st>>>(ND, a.hE1, d.h1_t, d.a1_t));
@@ -1068,7 +1068,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
     seg(p, Ain[0], lda, 0, Kd, W, ldw, trans);
     ps.push_back(p);
     ps.push_back(tangent_of(p, {Ain[1]}, C[1], nullptr));
-    return run_gemms(ps, st, "kd_gemm");
+    return run_gemms(c, ps, st, "kd_gemm");
   };
 
   KLAUNCH(st, "kd_head", kd_head_seed<<<dn_blocks(ND), 256, 0, st>>>(ND, D, a.atom_struct, dE, P + hE.W3, a.hE2, d.h2_t,
@@ -1219,7 +1219,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
         ps.push_back(which == 4 ? tangent_of(p, {d.dzan[1]}, d.da[1], nullptr)
                                 : tangent_of(p, {d.dzbe[1], d.dzan[1]}, d.da[1], nullptr));
       }
-      CHG_TRY(run_gemms(ps, st, "kd_gemm"));
+      CHG_TRY(run_gemms(c, ps, st, "kd_gemm"));
       if (which & 6) {
         ps.clear();
         p = gp(B, D, d.de[0], D);
@@ -1235,7 +1235,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
         }
         ps.push_back(p);
         ps.push_back(tangent_of(p, {d.T[1], d.T[1], d.T[1], d.T[1]}, d.de[1], nullptr));
-        CHG_TRY(run_gemms(ps, st, "kd_gemm"));
+        CHG_TRY(run_gemms(c, ps, st, "kd_gemm"));
       }
       return CHGNET_OK;
     };
@@ -1324,7 +1324,7 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
       ps.push_back(p);
       ps.push_back(tangent_of(p, {d.deb[1]}, d.drbfb[1], nullptr));
     }
-    CHG_TRY(run_gemms(ps, st, "kd_gemm"));
+    CHG_TRY(run_gemms(c, ps, st, "kd_gemm"));
     KLAUNCH(st, "kd_embed", kd_freq<<<dn_blocks(E * R), 256, 0, st>>>(E * R, R, pe, inv_ca, nullptr, a.edge_len, d.ddot,
                                                                        P + L.f_a, d.drbfa[0], d.drbfa[1], d.fpa));
     colsum(E, R, d.fpa, R, nullptr, Lg.f_a);

@@ -1,10 +1,9 @@
-// fp32 MFMA GEMMs for the per-atom, per-edge and per-angle linear layers.
+// Matrix products of the per-atom, per-edge and per-angle linear layers.
 //
-// k_gemm: a 256-thread workgroup owns a 128 x 64 tile of C, each wavefront
-// 32 rows x 64 columns as two 32x32 fp32 MFMA (32x32x2) accumulators, with
-// the K dimension streamed through LDS in chunks of 32. k_gemm_w: direct-load
-// 32 x 64 wave tiles with k split over wavefronts, for few rows or a long k.
-// k_tn: split-K weight-gradient products X^T Y. Operand rows may be gathered
+// k_gemm_p: products with a weight block, at most 128 deep, over many rows;
+// k_gemm_k: the same over few rows or deeper, k split over wavefronts. Both
+// multiply split operands on the bf16 matrix cores (see gemm.hpp). k_tn:
+// split-K weight-gradient products X^T Y. Operand rows may be gathered
 // through an index array (edge -> source atom, bond -> edge, angle -> bond),
 // so the concatenated GatedMLP inputs of Eq. (4)-(6) never exist in memory:
 // the products of their blocks are summed in the epilogue.
@@ -16,6 +15,7 @@
 
 #include "common.hpp"
 #include "gemm.hpp"
+#include "split.hpp"
 
 namespace chg {
 
@@ -26,68 +26,6 @@ namespace {
 __device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
 typedef float v16f __attribute__((ext_vector_type(16)));
-
-// Load 4 consecutive floats p[k..k+3] of a row of length K (zero past K).
-__device__ __forceinline__ float4 load4(const float* __restrict__ p, int k, int K, bool vec) {
-  if (vec && k + 3 < K) return *reinterpret_cast<const float4*>(p + k);
-  float4 v;
-  v.x = k < K ? p[k] : 0.f;
-  v.y = k + 1 < K ? p[k + 1] : 0.f;
-  v.z = k + 2 < K ? p[k + 2] : 0.f;
-  v.w = k + 3 < K ? p[k + 3] : 0.f;
-  return v;
-}
-
-// NN product, 128 x BN tile per 256-thread block; wave w owns rows
-// [32w, 32w + 32) and all BN columns as BN/32 tiles of 32x32 (fp32 MFMA
-// 32x32x2). K is streamed through LDS in chunks of 32; the global loads of
-// chunk c+1 are issued into registers before the MFMAs of chunk c.
-// NADD gathered addends are summed in the epilogue; their row indices are
-// staged in LDS once per block.
-template <int BN>
-struct GemmStage {
-  float4 a[4];
-  float4 b[BN / 32];
-};
-
-template <int BN>
-__device__ __forceinline__ void gemm_fetch(const GemmProblem& P, const GemmSeg& S, int k0, int c0, int tid,
-                                           const int64_t (&arow)[4], const bool (&aval)[4], GemmStage<BN>& g) {
-  constexpr int KC = 32;
-  const bool avec = ((S.lda | S.a_col) & 3) == 0 && ((uintptr_t)S.A & 15) == 0;
-  const bool bvec = (S.ldb & 3) == 0 && ((uintptr_t)S.B & 15) == 0;
-  (void)bvec;
-  const int ak = (tid & 7) * 4;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    g.a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (aval[q]) g.a[q] = load4(S.A + arow[q] * S.lda + S.a_col + k0, ak, S.K - k0, avec);
-  }
-  if (!S.trans) {
-    // column strips: thread takes column n = tid % BN and 4 consecutive k
-    constexpr int G = 256 / BN;  // k-groups per pass
-    const int n = tid % BN, kg = tid / BN;
-    const bool nv = c0 + n < P.N;
-#pragma unroll
-    for (int q = 0; q < BN / 32; ++q) {
-      const int kb = k0 + 4 * (kg + G * q);
-      const float* col = S.B + c0 + n;
-      float4 v;
-      v.x = (nv && kb + 0 < S.K) ? col[(int64_t)(kb + 0) * S.ldb] : 0.f;
-      v.y = (nv && kb + 1 < S.K) ? col[(int64_t)(kb + 1) * S.ldb] : 0.f;
-      v.z = (nv && kb + 2 < S.K) ? col[(int64_t)(kb + 2) * S.ldb] : 0.f;
-      v.w = (nv && kb + 3 < S.K) ? col[(int64_t)(kb + 3) * S.ldb] : 0.f;
-      g.b[q] = v;
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < BN / 32; ++q) {
-      const int idx = tid + 256 * q, n = idx / (KC / 4), kk = (idx % (KC / 4)) * 4;
-      g.b[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (c0 + n < P.N) g.b[q] = load4(S.B + (int64_t)(c0 + n) * S.ldb + k0, kk, S.K - k0, bvec);
-    }
-  }
-}
 
 // Epilogue of one row and 4 consecutive columns: activation, bias,
 // residual, optional accumulation, 16-byte stores when aligned.
@@ -149,160 +87,303 @@ __device__ __forceinline__ void gemm_store4(const GemmProblem& P, int row, int c
   }
 }
 
-// ROLE only names the instantiation (0 other, 2 input gradients) so that
-// profilers can tell the launches apart. OCC: wavefronts per SIMD the
-// registers are sized for; at 4 the fragments of a chunk are read in two
-// halves of 8 k-steps (126 VGPRs), for launches with a plain epilogue.
-template <int BN, int ROLE, int OCC>
-__global__ void __launch_bounds__(256, OCC == 4 ? 4 : 1) k_gemm(GemmBatch batch) {
-  constexpr int BM = 128, KC = 32, NT = BN / 32, KP = KC + 4, SP = 64 + 4;
-  const GemmProblem& P = batch.p[blockIdx.z];
-  // Workgroups are dealt to the 8 XCDs round-robin by linear id (gridDim.x
-  // is a multiple of 8). Renumber so that the column tiles of one row worker
-  // share an XCD, and its A rows are fetched into one L2.
-  int bx, by;
-  {
-    const int p = blockIdx.x + gridDim.x * blockIdx.y, j = p >> 3;
-    by = j % gridDim.y;
-    bx = 8 * (j / gridDim.y) + (p & 7);
-  }
-  const int c0 = by * BN;
-  const int ntiles = (P.M + BM - 1) / BM;
-  if (bx >= ntiles || c0 >= P.N) return;
-  // Operand tiles are stored k-contiguous: As[row][k], Bs[col][k]. In MFMA
-  // k-step i, lane half h = lane / 32 supplies k = 16 h + i, so each lane
-  // reads its 16 A and B values of a chunk with four 16-byte LDS reads.
-  // After the K loop the same LDS holds the output tile, 64 columns at a
-  // time, so the epilogue writes whole rows with 16-byte stores. A block
-  // walks row tiles bx, bx + gridDim.x, ...; the first chunk
-  // of its next tile is fetched before the current tile's epilogue.
-  constexpr int kOperand = BM * KP + BN * KP, kStage = 4 * 32 * SP;
-  __shared__ __attribute__((aligned(16))) float smem[kOperand > kStage ? kOperand : kStage];
-  float (*As)[KP] = reinterpret_cast<float (*)[KP]>(smem);
-  float (*Bs)[KP] = reinterpret_cast<float (*)[KP]>(smem + BM * KP);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
-  const int ar = tid >> 3, ak = (tid & 7) * 4;
-  const bool cvec = gemm_cvec(P);
-  int64_t arow[4];
-  bool aval[4];
-  auto set_rows = [&](int r0) {
+// segment of a 16-deep step (uniform over the wavefront)
+__device__ __forceinline__ int seg_of(const GemmProblem& P, int ks) {
+  int s = 0;
+  while (s + 1 < P.nseg && ks >= P.seg[s + 1].ks0) ++s;
+  return s;
+}
+
+// The sign that odd rows are multiplied with (see gemm.hpp): `flip_odd` for a
+// lane that holds row lane % 32 of A, `unflip` for value j of a 32 x 32
+// accumulator, which belongs to row 8 (j / 4) + 4 (lane / 32) + j % 4.
+__device__ __forceinline__ void flip_odd(float (&v)[8], int lane) {
+  const unsigned s = (unsigned)lane << 31;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = r0 + ar + 32 * q;
-      aval[q] = r < P.M;
-      arow[q] = aval[q] ? (P.a_rows ? P.a_rows[r] : r) : 0;
-    }
-  };
-  GemmStage<BN> g;
-  int tile = bx;
-  set_rows(tile * BM);
-  if (P.nseg > 0) gemm_fetch<BN>(P, P.seg[0], 0, c0, tid, arow, aval, g);
-  while (tile < ntiles) {
-    const int r0 = tile * BM;
-    const int next = tile + gridDim.x;
-    v16f acc[NT];
+  for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(__float_as_uint(v[e]) ^ s);
+}
+__device__ __forceinline__ float unflip(float x, int j) { return (j & 1) ? -x : x; }
+
+// this lane's eight A values of a step (its row, k = 16 step + 8 (lane / 32) ..)
+__device__ __forceinline__ void load_a(const GemmProblem& P, int ks, int64_t arow, int h, float (&v)[8]) {
+  const GemmSeg& S = P.seg[seg_of(P, ks)];
+  const int k0 = (ks - S.ks0) * 16, k = k0 + 8 * h;
+  const float* p = S.A + arow * S.lda + S.a_col + k;
+  if (k0 + 16 <= S.K) {  // uniform
+    const f4u a = *reinterpret_cast<const f4u*>(p), b = *reinterpret_cast<const f4u*>(p + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) acc[t][j] = 0.f;
-    int s = 0, k0 = 0;
-    while (s < P.nseg) {
-      const bool trans = P.seg[s].trans;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) *reinterpret_cast<float4*>(&As[ar + 32 * q][ak]) = g.a[q];
-      if (!trans) {
-        constexpr int G = 256 / BN;
-#pragma unroll
-        for (int q = 0; q < BN / 32; ++q)
-          *reinterpret_cast<float4*>(&Bs[tid % BN][4 * (tid / BN + G * q)]) = g.b[q];
-      } else {
-#pragma unroll
-        for (int q = 0; q < BN / 32; ++q) {
-          const int idx = tid + 256 * q, n = idx / (KC / 4), kk = (idx % (KC / 4)) * 4;
-          *reinterpret_cast<float4*>(&Bs[n][kk]) = g.b[q];
-        }
-      }
-      __syncthreads();
-      k0 += KC;
-      if (k0 >= P.seg[s].K) {
-        k0 = 0;
-        ++s;
-      }
-      if (s < P.nseg) {
-        gemm_fetch<BN>(P, P.seg[s], k0, c0, tid, arow, aval, g);
-      } else if (next < ntiles) {
-        set_rows(next * BM);
-        gemm_fetch<BN>(P, P.seg[0], 0, c0, tid, arow, aval, g);
-      }
-      constexpr int HS = OCC >= 4 ? 2 : 1, KH = 16 / HS;  // fragment reads per chunk, k-steps each
-#pragma unroll
-      for (int hh = 0; hh < HS; ++hh) {
-        float af[KH], bf[NT][KH];
-        const float* ap = &As[32 * wave + (lane & 31)][16 * h + KH * hh];
-#pragma unroll
-        for (int q = 0; q < KH / 4; ++q) {
-          const float4 v = *reinterpret_cast<const float4*>(ap + 4 * q);
-          af[4 * q] = v.x; af[4 * q + 1] = v.y; af[4 * q + 2] = v.z; af[4 * q + 3] = v.w;
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const float* bp = &Bs[32 * t + (lane & 31)][16 * h + KH * hh];
-#pragma unroll
-          for (int q = 0; q < KH / 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4*>(bp + 4 * q);
-            bf[t][4 * q] = v.x; bf[t][4 * q + 1] = v.y; bf[t][4 * q + 2] = v.z; bf[t][4 * q + 3] = v.w;
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < KH; ++i)
-#pragma unroll
-          for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[t][i], acc[t], 0, 0, 0);
-      }
-      __syncthreads();
-    }
-    // ---- epilogue, 64 columns (two 32x32 tiles) at a time through LDS
-    float* stg = smem + wave * 32 * SP;
-#pragma unroll
-    for (int half = 0; half < (NT + 1) / 2; ++half) {
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-        if (2 * half + tt >= NT) break;
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-          stg[(8 * (j >> 2) + 4 * h + (j & 3)) * SP + 32 * tt + (lane & 31)] = acc[2 * half + tt][j];
-      }
-      __syncthreads();
-      const int cl = 4 * (lane & 15);
-      const int col = c0 + 64 * half + cl;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int lr = (lane >> 4) + 4 * i;
-        const float4 sv = *reinterpret_cast<const float4*>(stg + lr * SP + cl);
-        gemm_store4(P, r0 + 32 * wave + lr, col, sv, cvec);
-      }
-      __syncthreads();
-    }
-    tile = next;
+    for (int e = 0; e < 8; ++e) v[e] = k + e < S.K ? p[e] : 0.f;
   }
 }
 
-// Direct-load GEMM for short or few row tiles: each wavefront owns a 32 x 64
-// tile of C and streams its fragments straight from global memory (no LDS
-// staging), k in groups of 8: in MFMA k-step i of a group, lane half h
-// supplies k = 4h + i; lane c = lane % 32 holds output columns 2c + u of the
-// tile (u < 2: two 32x32 tiles with interleaved columns), so B fragments are
-// 8-byte row pieces (or 16-byte k runs when B is stored transposed). The
-// WK wavefronts of a tile split its k groups into contiguous runs and their
-// partial tiles are added in wave order in LDS before the shared epilogue.
-// Rows, columns and k beyond the matrices are clamped into them and
-// cancelled through a 0/1 mask on the B fragment (a clamped A entry is a
-// finite operand entry times zero).
+// the value that lane lr + 4 h holds, for both halves h of a wavefront
+__device__ __forceinline__ int row_lane(int v, int lr, int h) {
+  const int a = __builtin_amdgcn_readlane(v, lr), b = __builtin_amdgcn_readlane(v, lr + 4);
+  return h ? b : a;
+}
+
+// The 32 x 32 accumulator tiles of a wavefront (32 rows at r0, NT tiles at
+// column c0) to C: lane (c, h) holds column c of rows 8 (j / 4) + 4 h + j % 4,
+// so a store instruction writes whole 128-byte pieces of two rows (with the
+// operands swapped, a lane has 16 bytes of one row: 32-byte pieces of 32
+// rows, 88 -> 116 us for the embeddings of 4,096 atoms).
+// A tile's 16 values a lane of the residual, the factor and the old C are all
+// loaded before the first of its stores, which they could not pass otherwise.
+template <int NT>
+__device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, const v16f (&acc)[NT],
+                                         const float (&bias)[2], int lane) {
+  const int c = lane & 31, h = lane >> 5;
+  const bool full = r0 + 32 <= P.M && c0 + 32 * NT <= P.N;  // uniform
+  const bool plain = full && !P.res_rows && !P.c_rows;
+  const int mine = min(r0 + c, P.M - 1);
+  const int rr = P.res_rows ? P.res_rows[mine] : mine, cr = P.c_rows ? P.c_rows[mine] : mine;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int col = c0 + 32 * t + c;
+    float x[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = unflip(acc[t][j], j);
+    if (plain) {
+      // rows at a fixed distance: one offset a lane, the rest uniform
+      if (P.act == ACT_DSILU_MUL) {
+        const float* q = P.mul + (int64_t)r0 * P.mul_ld + (4 * h * P.mul_ld + col);
+        float m[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) m[j] = q[(8 * (j >> 2) + (j & 3)) * P.mul_ld];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const float sg = sigm(m[j]);
+          x[j] *= sg * (1.0f + m[j] * (1.0f - sg));
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] += bias[t];
+      if (P.res) {
+        const float* q = P.res + (int64_t)r0 * P.res_ld + (4 * h * P.res_ld + col);
+        float m[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) m[j] = q[(8 * (j >> 2) + (j & 3)) * P.res_ld];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] += m[j];
+      }
+      float* d = P.C + (int64_t)r0 * P.ldc + (4 * h * P.ldc + col);
+      if (P.accumulate) {
+        float m[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) m[j] = d[(8 * (j >> 2) + (j & 3)) * P.ldc];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] += m[j];
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) d[(8 * (j >> 2) + (j & 3)) * P.ldc] = x[j];
+      if (P.act == ACT_SILU_OUT) {
+        float* d2 = P.C2 + (int64_t)r0 * P.ldc2 + (4 * h * P.ldc2 + col);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) d2[(8 * (j >> 2) + (j & 3)) * P.ldc2] = x[j] * sigm(x[j]);
+      }
+      continue;
+    }
+    // gathered or scattered rows, and the edges of C: rows past the end are
+    // clamped, columns past it do nothing
+    if (col >= P.N) continue;
+    if (P.act == ACT_DSILU_MUL) {
+      float m[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        m[j] = P.mul[(int64_t)min(r0 + 8 * (j >> 2) + 4 * h + (j & 3), P.M - 1) * P.mul_ld + col];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const float sg = sigm(m[j]);
+        x[j] *= sg * (1.0f + m[j] * (1.0f - sg));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] += bias[t];
+    if (P.res) {
+      float m[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) m[j] = P.res[(int64_t)row_lane(rr, 8 * (j >> 2) + (j & 3), h) * P.res_ld + col];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] += m[j];
+    }
+    if (P.accumulate) {
+      float m[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) m[j] = P.C[(int64_t)row_lane(cr, 8 * (j >> 2) + (j & 3), h) * P.ldc + col];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] += m[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int row = r0 + 8 * (j >> 2) + 4 * h + (j & 3);
+      if (row >= P.M) continue;
+      P.C[(int64_t)row_lane(cr, 8 * (j >> 2) + (j & 3), h) * P.ldc + col] = x[j];
+      if (P.act == ACT_SILU_OUT) P.C2[(int64_t)row * P.ldc2 + col] = x[j] * sigm(x[j]);
+    }
+  }
+}
+
+// Products over many rows. A block takes 64 columns and keeps their packed
+// weights, KS steps of 16 k, in LDS; its four wavefronts walk 32-row tiles: a
+// step's eight A values a lane are split and multiplied, and the same
+// registers take the values of that step of the next tile (DEEP: of the next
+// KS steps), so they are in flight meanwhile. Problems at most 16 KS deep load
+// the weights once and run without a further barrier; deeper ones (DEEP) take
+// them KS steps at a time through two LDS buffers, the next steps loaded
+// straight into LDS while these are multiplied, one barrier a chunk.
+// At k = 64 bound by the bytes of C, at k = 128 and more by the matrix cores
+// and the latency of a chunk. Against the fp32 matrix cores with both operands
+// staged through LDS, kernel time: a layer's bond projections of 4,096 atoms
+// (36,300 x 512 x 64) 51 -> 37 us, its embeddings 115 -> 82 us; wide128's
+// launches of k = 128 92-170 -> 84 us; the Eq. 10 block's input gradients (k
+// = 256) 151 -> 136 us. Blocks: three a compute unit (four for KS = 2); with
+// registers for four at KS = 4 the epilogue spilled (37 -> 66 us).
+struct GemmPArgs {
+  GemmBatch b;
+  int block0[kMaxGemmProblems + 1];  // first block of each problem (multiples of 8)
+};
+template <int KS, bool DEEP>
+__global__ void __launch_bounds__(256, KS <= 2 ? 4 : 3) k_gemm_p(GemmPArgs args) {
+  int pi = 0;
+  while (pi + 1 < args.b.n && (int)blockIdx.x >= args.block0[pi + 1]) ++pi;
+  const GemmProblem& P = args.b.p[pi];
+  // Workgroups are dealt to the 8 XCDs in turn: the column groups of one row
+  // worker sit 8 apart, on one XCD, and its A rows are fetched into one L2.
+  const int ncol = (P.N + 63) / 64, nb = args.block0[pi + 1] - args.block0[pi], workers = nb / ncol;
+  int bx, by;
+  {
+    const int p = (int)blockIdx.x - args.block0[pi], j = p >> 3;
+    by = j % ncol;
+    bx = 8 * (j / ncol) + (p & 7);
+  }
+  const int c0 = by * 64, ntiles = (P.M + 31) / 32;
+  if (bx * 4 >= ntiles) return;  // uniform over the block
+  constexpr int kPanel = 2 * KS * kPackTile;
+  __shared__ uint4 Bs[(DEEP ? 2 : 1) * kPanel];
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nks = P.nks;
+  const bool two = c0 + 32 < P.N;  // uniform
+  auto load_b = [&](int k0) {
+    const int n = min(KS, nks - k0);
+    for (int u = tid; u < (two ? 2 : 1) * n * kPackTile; u += 256) {
+      const int t = u / (n * kPackTile), ks = (u / kPackTile) % n, o = u % kPackTile;
+      const GemmSeg& S = P.seg[seg_of(P, k0 + ks)];
+      Bs[(t * KS + ks) * kPackTile + o] = S.Bp[((int64_t)(c0 / 32 + t) * S.bnt + k0 + ks - S.ks0) * kPackTile + o];
+    }
+  };
+  const int step = workers * 4;
+  int tile = bx * 4 + wave;
+  auto row_of = [&](int t) -> int64_t {
+    const int r = min(t * 32 + (lane & 31), P.M - 1);
+    return P.a_rows ? P.a_rows[r] : r;
+  };
+  float a[KS][8];
+  int64_t ar = row_of(tile);
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    if (ks < nks) load_a(P, ks, ar, h, a[ks]);
+  int buf = 0;
+  load_b(0);
+  __syncthreads();
+  if (!DEEP && tile >= ntiles) return;
+  float bias[2] = {0.f, 0.f};
+  if (P.bias)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) bias[t] = P.bias[min(c0 + 32 * t + (lane & 31), P.N - 1)];
+  auto put = [&](const v16f (&acc)[2]) {
+    if (two) {
+      gemm_put<2>(P, tile * 32, c0, acc, bias, lane);
+    } else {
+      const v16f one[1] = {acc[0]};
+      gemm_put<1>(P, tile * 32, c0, one, bias, lane);
+    }
+  };
+  // DEEP: the panel of steps k0 .. k0 + KS - 1 straight into LDS, a kilobyte
+  // (a plane of a tile) a wavefront at a time; steps and columns past the end
+  // are clamped and not used
+  auto fetch_b = [&](int k0, int to) {
+#pragma unroll
+    for (int q = 0; q < 2 * KS * 3 / 4; ++q) {
+      const int pc = wave + 4 * q, t = two ? pc / (KS * 3) : 0;
+      const int ks = min(k0 + (pc / 3) % KS, nks - 1);
+      const GemmSeg& S = P.seg[seg_of(P, ks)];
+      const uint4* src = S.Bp + ((int64_t)(c0 / 32 + t) * S.bnt + ks - S.ks0) * kPackTile + 64 * (pc % 3) + lane;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned*)src,
+                                       (__attribute__((address_space(3))) unsigned*)(Bs + to * kPanel + 64 * pc), 16, 0, 0);
+    }
+  };
+  auto mul = [&](const uint4* B, int ks, const Split8& x, v16f (&acc)[2]) {
+    const uint4* b0 = B + ks * kPackTile + lane;
+    mfma_split(x, packed8(b0), acc[0]);
+    if (two) mfma_split(x, packed8(b0 + KS * kPackTile), acc[1]);
+  };
+  // (DEEP: every wavefront runs the block's rounds; a tile past the end is
+  // clamped rows, not stored)
+  for (int base = bx * 4; base < ntiles; base += step, tile += step) {
+    if (!DEEP && tile >= ntiles) break;
+    const bool more = (DEEP ? base : tile) + step < ntiles;
+    v16f acc[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[t][j] = 0.f;
+    if constexpr (!DEEP) {
+      const int64_t arn = more ? row_of(tile + step) : ar;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks >= nks) break;
+        flip_odd(a[ks], lane);
+        const Split8 x = split8(a[ks]);
+        load_a(P, ks, arn, h, a[ks]);
+        mul(Bs, ks, x, acc);
+      }
+      put(acc);
+    } else {
+      for (int k0 = 0; k0 < nks; k0 += KS) {
+        const bool last = k0 + KS >= nks;
+        const uint4* B = Bs + buf * kPanel;
+        if (!last || more) fetch_b(last ? 0 : k0 + KS, buf ^ 1);
+        const int64_t arn = last && more ? row_of(tile + step) : ar;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          if (k0 + ks >= nks) break;
+          flip_odd(a[ks], lane);
+          const Split8 x = split8(a[ks]);
+          const int nx = last ? ks : k0 + KS + ks;
+          if (nx < nks) load_a(P, nx, arn, h, a[ks]);
+          mul(B, ks, x, acc);
+        }
+        // steps of the next tile whose registers this short chunk did not use
+        if (last && more)
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks)
+            if (k0 + ks >= nks && ks < nks) load_a(P, ks, arn, h, a[ks]);
+        if (last) ar = arn;
+        // (the other buffer was last read before the barrier before this one)
+        buf ^= 1;
+        __builtin_amdgcn_s_waitcnt(0);  // the panel is in LDS
+        __syncthreads();
+      }
+      if (tile < ntiles) put(acc);
+    }
+  }
+}
+
+// Products over few rows: each wavefront owns a 32 x 64 tile of C and streams
+// both operands from global memory (the packed weights
+// as contiguous kilobytes), one step in flight ahead of the matrix cores. The
+// WK wavefronts of a tile take contiguous runs of its steps and their partial
+// tiles are added in wave order in LDS before the epilogue.
 constexpr int kGwWaves = 8;
 constexpr int kGwLd = 64 + 4;
 
 template <int WK>
-__global__ void __launch_bounds__(512, 2) k_gemm_w(GemmBatch batch) {
-  __shared__ __attribute__((aligned(16))) float slot[kGwWaves * 32 * kGwLd];
+__global__ void __launch_bounds__(512, 2) k_gemm_k(GemmBatch batch) {
+  __shared__ __attribute__((aligned(16))) float slot[WK > 1 ? kGwWaves * 32 * kGwLd : 4];
   const GemmProblem& P = batch.p[blockIdx.z];
   constexpr int TPB = kGwWaves / WK;  // row tiles per block
   const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, h = lane >> 5;
@@ -310,102 +391,63 @@ __global__ void __launch_bounds__(512, 2) k_gemm_w(GemmBatch batch) {
   const int tl = wave / WK, kp = wave % WK;
   const int r0 = (blockIdx.x * TPB + tl) * 32, n0 = blockIdx.y * 64;
   if ((int)blockIdx.x * TPB * 32 >= P.M || n0 >= P.N) return;  // uniform over the block
-  int groups = 0;
-  for (int s = 0; s < P.nseg; ++s) groups += (P.seg[s].K + 7) / 8;
-  const int g_lo = kp * groups / WK, g_hi = (kp + 1) * groups / WK;
-  // this lane's A row (clamped) and B columns (clamped)
+  const int lo = kp * P.nks / WK, hi = (kp + 1) * P.nks / WK;
   const int arow_i = min(r0 + c, P.M - 1);
   const int64_t arow = P.a_rows ? P.a_rows[arow_i] : arow_i;
-  const int ncol0 = n0 + 2 * c;
-  const int nc0 = min(ncol0, P.N - 1), nc1 = min(ncol0 + 1, P.N - 1);
-  const float nm0 = ncol0 < P.N ? 1.f : 0.f, nm1 = ncol0 + 1 < P.N ? 1.f : 0.f;
+  const bool two = n0 + 32 < P.N;  // uniform
   v16f acc[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[u][j] = 0.f;
-  constexpr int NB = 4;  // register buffers: NB - 1 groups in flight ahead of the MFMAs
-  float af[NB][4], bf[NB][4][2];
-  // group g -> (segment, k0)
-  auto locate = [&](int g, int& s, int& k0) {
-    s = 0;
-    int left = g;
-    while (s + 1 < P.nseg && left >= (P.seg[s].K + 7) / 8) {
-      left -= (P.seg[s].K + 7) / 8;
-      ++s;
-    }
-    k0 = 8 * left;
-  };
-  auto fetch = [&](int g, int b) {
-    int s, k0;
-    locate(g, s, k0);
-    const GemmSeg& S = P.seg[s];
-    const int kb = k0 + 4 * h;
-    const float* ap = S.A + arow * S.lda + S.a_col;
-    // vector paths only where every lane's piece is inside (uniform tests)
-    if (((S.lda | S.a_col | S.K) & 3) == 0 && ((uintptr_t)S.A & 15) == 0 && (S.K & 7) == 0) {
-      const float4 t = *reinterpret_cast<const float4*>(ap + kb);
-      af[b][0] = t.x; af[b][1] = t.y; af[b][2] = t.z; af[b][3] = t.w;
-    } else {
+  float a[2][8];
+  uint4 b[2][2][3];
+  auto fetch = [&](int ks, int q) {
+    load_a(P, ks, arow, h, a[q]);
+    const GemmSeg& S = P.seg[seg_of(P, ks)];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) af[b][i] = ap[min(kb + i, S.K - 1)];
-    }
-    float km[4];
+    for (int t = 0; t < 2; ++t) {
+      if (t == 1 && !two) break;
+      const uint4* src = S.Bp + ((int64_t)(n0 / 32 + t) * S.bnt + ks - S.ks0) * kPackTile + lane;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) km[i] = kb + i < S.K ? 1.f : 0.f;
-    if (!S.trans) {
-      const bool bvec = (S.ldb & 1) == 0 && ((uintptr_t)S.B & 7) == 0 && n0 + 64 <= P.N;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float* bp = S.B + (int64_t)min(kb + i, S.K - 1) * S.ldb;
-        if (bvec) {
-          const float2 t = *reinterpret_cast<const float2*>(bp + ncol0);
-          bf[b][i][0] = t.x * km[i];
-          bf[b][i][1] = t.y * km[i];
-        } else {
-          bf[b][i][0] = bp[nc0] * (km[i] * nm0);
-          bf[b][i][1] = bp[nc1] * (km[i] * nm1);
-        }
-      }
-    } else {
-      const bool bvec = (S.ldb & 3) == 0 && ((uintptr_t)S.B & 15) == 0 && (S.K & 7) == 0;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float* bp = S.B + (int64_t)(u ? nc1 : nc0) * S.ldb;
-        const float m = u ? nm1 : nm0;
-        if (bvec) {
-          const float4 t = *reinterpret_cast<const float4*>(bp + kb);
-          bf[b][0][u] = t.x * m; bf[b][1][u] = t.y * m; bf[b][2][u] = t.z * m; bf[b][3][u] = t.w * m;
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) bf[b][i][u] = bp[min(kb + i, S.K - 1)] * (km[i] * m);
-        }
-      }
+      for (int pl = 0; pl < 3; ++pl) b[q][t][pl] = src[64 * pl];
     }
   };
-  auto compute = [&](int b) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[b][i], bf[b][i][u], acc[u], 0, 0, 0);
+  auto compute = [&](int q) {
+    flip_odd(a[q], lane);
+    const Split8 x = split8(a[q]);
+    mfma_split(x, as_split8(b[q][0]), acc[0]);
+    if (two) mfma_split(x, as_split8(b[q][1]), acc[1]);
   };
-  const int n = g_hi - g_lo;
-#pragma unroll
-  for (int j = 0; j < NB - 1; ++j)
-    if (j < n) fetch(g_lo + j, j);
-  for (int it = 0; it < n; it += NB) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (it + j + NB - 1 < n) fetch(g_lo + it + j + NB - 1, (j + NB - 1) % NB);
-      if (it + j < n) compute(j);
+  if (r0 < P.M) {
+    if (lo < hi) fetch(lo, 0);
+    for (int ks = lo; ks < hi; ks += 2) {
+      if (ks + 1 < hi) fetch(ks + 1, 1);
+      compute(0);
+      if (ks + 2 < hi) fetch(ks + 2, 0);
+      if (ks + 1 < hi) compute(1);
     }
   }
-  // partial tiles -> LDS, rows 8(j/4) + 4h + j%4, columns 2c + u
+  if constexpr (WK == 1) {
+    if (r0 >= P.M) return;
+    float bias[2] = {0.f, 0.f};
+    if (P.bias)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) bias[t] = P.bias[min(n0 + 32 * t + c, P.N - 1)];
+    if (two) {
+      gemm_put<2>(P, r0, n0, acc, bias, lane);
+    } else {
+      const v16f one[1] = {acc[0]};
+      gemm_put<1>(P, r0, n0, one, bias, lane);
+    }
+    return;
+  }
+  // partial tiles -> LDS
   float* my = slot + wave * 32 * kGwLd;
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) my[(8 * (j >> 2) + 4 * h + (j & 3)) * kGwLd + 2 * c + u] = acc[u][j];
+    for (int j = 0; j < 16; ++j) my[(8 * (j >> 2) + 4 * h + (j & 3)) * kGwLd + 32 * u + c] = unflip(acc[u][j], j);
   __syncthreads();
   // wave-ordered sum of each tile's WK partials, epilogue with row-contiguous
   // 4-column pieces: 32 rows x 16 pieces per tile
@@ -421,6 +463,41 @@ __global__ void __launch_bounds__(512, 2) k_gemm_w(GemmBatch batch) {
     }
     gemm_store4(P, (blockIdx.x * TPB + t) * 32 + rr, n0 + cl, sum, cvec);
   }
+}
+
+// Packing of the weights: a wavefront a tile.
+constexpr int kPackMats = 96;
+struct PackArgs {
+  int n;
+  int64_t tiles;
+  struct { int src, rows, cols, tile0; } m[kPackMats];  // tile0: within the launch, ascending
+};
+template <bool T>
+__global__ void __launch_bounds__(256) k_pack_split(PackArgs A, const float* __restrict__ src, uint4* __restrict__ out) {
+  const int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (tile >= A.tiles) return;
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = A.n;  // matrix with tile0 <= tile
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) / 2;
+    if (A.m[mid].tile0 <= tile) lo = mid;
+    else hi = mid;
+  }
+  const auto& M = A.m[lo];
+  const int K = T ? M.cols : M.rows, N = T ? M.rows : M.cols;
+  const int nks = (K + 15) / 16, l = (int)(tile - M.tile0);
+  const int n = (l / nks) * 32 + (lane & 31), k0 = (l % nks) * 16 + 8 * (lane >> 5);
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int k = k0 + e;
+    v[e] = n < N && k < K ? src[M.src + (T ? (int64_t)n * M.cols + k : (int64_t)k * M.cols + n)] : 0.f;
+  }
+  const Split8 x = split8(v);
+  uint4* o = out + tile * kPackTile + lane;
+  o[0] = __builtin_bit_cast(uint4, x.h);
+  o[64] = __builtin_bit_cast(uint4, x.m);
+  o[128] = __builtin_bit_cast(uint4, x.l);
 }
 
 struct TnPlan {
@@ -847,207 +924,108 @@ __global__ void __launch_bounds__(256) k_reduce_rows2(ReduceJobs J, int groups_m
 }
 
 
-// Linear + SiLU layers of the d = 128 readout MLPs (C = A W + b, C2 =
-// silu(C), k = N = 128, more than 32768 rows): each wavefront of a 4-wave
-// block owns 32 output columns and holds its B fragments (64 floats a lane)
-// in registers for the whole launch (reloaded when the problem changes);
-// blocks walk the 32-row tiles of the batch's problems. The A tile of tile
-// i + 1 goes from registers to the other LDS buffer and the A loads of tile
-// i + 2 are issued before the MFMAs of tile i; one block barrier per tile.
-// The epilogue works from the accumulators: lane (h, c) holds column c of
-// rows 8 (j / 4) + 4 h + j % 4, so each store writes two 128-byte row
-// pieces. Measured on wide128: 0.27 -> 0.22 ms per head launch against the
-// LDS-tiled GEMM (which re-reads the weights for every tile); with gathered
-// residuals, scattered outputs or SiLU' factors it was slower and is not
-// used for them.
-struct SiluTiles {
-  int tile0[kMaxGemmProblems + 1];
-};
-constexpr int kSiluRows = 32, kSiluK = 128, kSiluWaves = 4;
-
-__global__ void __launch_bounds__(64 * kSiluWaves, 4) k_gemm_silu(GemmBatch batch, SiluTiles T) {
-  constexpr int R = kSiluRows, K = kSiluK, NW = kSiluWaves, LD = K + 4, F = R * K / (64 * NW), TPR = K / F,
-                KB = K / 32;
-  static_assert(F % 4 == 0 && R * TPR == 64 * NW, "A tile split");
-  __shared__ __attribute__((aligned(16))) float As[2][R * LD];
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ntiles = T.tile0[batch.n];
-  const int nt = (int)blockIdx.x < ntiles ? (ntiles - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
-  if (nt == 0) return;
-  auto prob_of = [&](int tile) {
-    int k = 0;
-    while (k + 1 < batch.n && tile >= T.tile0[k + 1]) ++k;
-    return k;
-  };
-  auto tile_of = [&](int i) { return (int)blockIdx.x + i * (int)gridDim.x; };
-  // A tile: thread -> row tid / TPR, F columns at F (tid % TPR); rows past M read as zero
-  float4 av[F / 4];
-  auto fetch = [&](int tile) {
-    const int k = prob_of(tile);
-    const GemmProblem& P = batch.p[k];
-    const GemmSeg& S = P.seg[0];
-    const int row = (tile - T.tile0[k]) * R + tid / TPR, ac = F * (tid % TPR);
-#pragma unroll
-    for (int q = 0; q < F / 4; ++q) av[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (row < P.M) {
-      const int64_t ar = P.a_rows ? P.a_rows[row] : row;
-      const float* src = S.A + ar * S.lda + S.a_col + ac;
-#pragma unroll
-      for (int q = 0; q < F / 4; ++q) av[q] = *reinterpret_cast<const float4*>(src + 4 * q);
-    }
-  };
-  auto store = [&](float* X) {
-    const int xr = tid / TPR, ac = F * (tid % TPR);
-#pragma unroll
-    for (int q = 0; q < F / 4; ++q) *reinterpret_cast<float4*>(&X[xr * LD + ac + 4 * q]) = av[q];
-  };
-  // B fragments: MFMA k-step e of k block kb takes k = 32 kb + 16 h + e
-  float bfr[KB][16];
-  int cur = -1;
-  fetch(tile_of(0));
-  store(As[0]);
-  if (nt > 1) fetch(tile_of(1));
-  __syncthreads();
-  for (int i = 0; i < nt; ++i) {
-    const int tile = tile_of(i);
-    const int k = prob_of(tile);
-    const GemmProblem& P = batch.p[k];
-    const int col = 32 * wave + l32;
-    if (k != cur) {
-      cur = k;
-      const GemmSeg& S = P.seg[0];
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int kk = 32 * kb + 16 * h + e;
-          bfr[kb][e] = S.trans ? S.B[(int64_t)col * S.ldb + kk] : S.B[(int64_t)kk * S.ldb + col];
-        }
-    }
-    if (i + 1 < nt) {
-      store(As[(i + 1) & 1]);
-      if (i + 2 < nt) fetch(tile_of(i + 2));
-    }
-    const float* X = As[i & 1];
-    v16f acc;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) acc[j] = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      float af[16];
-      const float* ap = &X[l32 * LD + 32 * kb + 16 * h];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 v = *reinterpret_cast<const float4*>(ap + 4 * q);
-        af[4 * q] = v.x; af[4 * q + 1] = v.y; af[4 * q + 2] = v.z; af[4 * q + 3] = v.w;
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bfr[kb][e], acc, 0, 0, 0);
-    }
-    const int r0 = (tile - T.tile0[k]) * R;
-    const float bias = P.bias ? P.bias[col] : 0.f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int row = r0 + 8 * (j >> 2) + 4 * h + (j & 3);
-      if (row < P.M) {
-        const float x = acc[j] + bias;
-        P.C[(int64_t)row * P.ldc + col] = x;
-        P.C2[(int64_t)row * P.ldc2 + col] = x * sigm(x);
-      }
-    }
-    __syncthreads();
-  }
-}
-
 }  // namespace
 
+void PackTable::add(int64_t off, int64_t src, int rows, int cols) {
+  PackMat q{off, src, rows, cols, n_tiles, t_tiles};
+  n_tiles += cdiv(cols, 32) * cdiv(rows, 16);
+  t_tiles += cdiv(rows, 32) * cdiv(cols, 16);
+  m.push_back(q);
+}
+void PackTable::finish() {
+  std::sort(m.begin(), m.end(), [](const PackMat& a, const PackMat& b) { return a.off < b.off; });
+}
+
+int pack_weights(const PackTable& t, const float* src, uint4* out, bool with_t, hipStream_t st) {
+  if ((int)t.m.size() > kPackMats) return fail(CHGNET_EINVAL, "pack: too many weight matrices");
+  for (int tr = 0; tr <= (with_t ? 1 : 0); ++tr) {
+    PackArgs A{};
+    A.tiles = tr ? t.t_tiles : t.n_tiles;
+    std::vector<const PackMat*> by(t.m.size());
+    for (size_t i = 0; i < t.m.size(); ++i) by[i] = &t.m[i];
+    std::sort(by.begin(), by.end(), [&](const PackMat* a, const PackMat* b) { return tr ? a->t0 < b->t0 : a->n0 < b->n0; });
+    for (const PackMat* q : by) A.m[A.n++] = {(int)q->src, q->rows, q->cols, (int)(tr ? q->t0 : q->n0)};
+    const unsigned blocks = (unsigned)cdiv(A.tiles, 4);
+    if (tr) KLAUNCH(st, "k_pack_params", k_pack_split<true><<<blocks, 256, 0, st>>>(A, src, out + t.n_tiles * kPackTile));
+    else KLAUNCH(st, "k_pack_params", k_pack_split<false><<<blocks, 256, 0, st>>>(A, src, out));
+  }
+  return CHGNET_OK;
+}
+
+int gemm_resolve(GemmProblem& p, const PackTable& t, const float* P, const uint4* packed) {
+  p.nks = 0;
+  for (int s = 0; s < p.nseg; ++s) {
+    GemmSeg& S = p.seg[s];
+    const int64_t off = S.B - P;
+    auto it = std::upper_bound(t.m.begin(), t.m.end(), off, [](int64_t o, const PackMat& q) { return o < q.off; });
+    if (it == t.m.begin()) return fail(CHGNET_EINVAL, "gemm: weights not packed");
+    const PackMat& q = *--it;
+    const int64_t at = off - q.off, r = at / q.cols, c = at % q.cols;
+    // the block's first k and first column in the packed orientation
+    const int64_t k0 = S.trans ? c : r, n0 = S.trans ? r : c;
+    const int64_t ks = cdiv(S.trans ? q.cols : q.rows, 16);
+    const int64_t kmax = S.trans ? q.cols : q.rows, nmax = S.trans ? q.rows : q.cols;
+    if (S.ldb != q.cols || at >= (int64_t)q.rows * q.cols || k0 % 16 || n0 % 32 || k0 + S.K > kmax || n0 + p.N > nmax ||
+        (S.K % 16 && k0 + S.K != kmax))
+      return fail(CHGNET_EINVAL, "gemm: weight block not aligned to the packed tiles");
+    S.bnt = (int)ks;
+    S.Bp = packed + ((S.trans ? t.n_tiles + q.t0 : q.n0) + (n0 / 32) * ks + k0 / 16) * kPackTile;
+    S.ks0 = p.nks;
+    p.nks += (int)cdiv(S.K, 16);
+  }
+  return CHGNET_OK;
+}
+
 int gemm_launch(const GemmBatch& b, hipStream_t st, const char* tag) {
-  if (b.n == 0) return CHGNET_OK;
-  {
-    // the Linear + SiLU layers of the d = 128 heads (see k_gemm_silu)
-    bool silu = true;
-    int maxM = 0;
-    SiluTiles T{};
-    for (int i = 0; i < b.n && silu; ++i) {
-      const GemmProblem& P = b.p[i];
-      const GemmSeg& S = P.seg[0];
-      silu = P.nseg == 1 && S.K == kSiluK && P.N == 32 * kSiluWaves && P.act == ACT_SILU_OUT && !P.res &&
-             !P.c_rows && !P.accumulate && ((S.lda | S.a_col) & 3) == 0 && ((uintptr_t)S.A & 15) == 0;
-      maxM = std::max(maxM, P.M);
-      T.tile0[i + 1] = T.tile0[i] + (int)cdiv(std::max(P.M, 0), kSiluRows);
-    }
-    if (silu && maxM > 32768) {
-      const unsigned grid = (unsigned)std::min(T.tile0[b.n], 4 * 256);
-      KLAUNCH(st, tag, k_gemm_silu<<<grid, 64 * kSiluWaves, 0, st>>>(b, T));
-      return CHGNET_OK;
-    }
-  }
-  // 64-column tiles: a 128-column variant needs ~170 VGPRs (2 waves per
-  // SIMD) and measured slower on every shape used here
-  const int BN = 64;
-  int gx = 0, gy = 0;
+  // Launches with enough 32 x 64 tiles for two wavefronts on every SIMD keep
+  // their weights in LDS (k_gemm_p); those with fewer stream them (k_gemm_k),
+  // k split over up to eight wavefronts so that the launch has about 2,048 of
+  // them. (A product of 14 x 512 x 64 takes 5.4 us so, against 8.7 us with fp32
+  // matrix cores and weights read across their rows; ten thousand rows 512
+  // deep 14.8 against 28 us.)
+  GemmBatch q{};
+  int64_t tiles = 0, maxM = 0, maxN = 0;
+  int maxks = 0;
   for (int i = 0; i < b.n; ++i) {
-    gx = std::max<int>(gx, (int)cdiv(b.p[i].M, 128));
-    gy = std::max<int>(gy, (int)cdiv(b.p[i].N, BN));
+    const GemmProblem& p = b.p[i];
+    if (p.M <= 0 || p.N <= 0) continue;
+    q.p[q.n++] = p;
+    tiles += cdiv(p.M, 32) * cdiv(p.N, 64);
+    maxM = std::max<int64_t>(maxM, p.M);
+    maxN = std::max<int64_t>(maxN, p.N);
+    maxks = std::max(maxks, p.nks);
   }
-  if (gx == 0 || gy == 0) return CHGNET_OK;
-  int maxM = 0, maxN = 0, maxK = 0;
-  for (int i = 0; i < b.n; ++i) {
-    maxM = std::max(maxM, b.p[i].M);
-    maxN = std::max(maxN, b.p[i].N);
-    int k = 0;
-    for (int s = 0; s < b.p[i].nseg; ++s) k += b.p[i].seg[s].K;
-    maxK = std::max(maxK, k);
-  }
-  if (maxM <= 32768 && (maxK >= 128 || maxM <= 4096)) {
-    // few row tiles and a long k, or very few rows: direct-load wave tiles,
-    // k split over 1-8 wavefronts so that the launch has about 2048 of them
-    // (with k = 64 and ~10^4 rows the LDS-staged tiles below measured faster)
-    int64_t tiles = 0;
-    int maxg = 0;
-    for (int i = 0; i < b.n; ++i) {
-      tiles += cdiv(b.p[i].M, 32) * cdiv(b.p[i].N, 64);
-      int g = 0;
-      for (int s = 0; s < b.p[i].nseg; ++s) g += (int)cdiv(b.p[i].seg[s].K, 8);
-      maxg = std::max(maxg, g);
+  if (q.n == 0) return CHGNET_OK;
+  const unsigned gy = (unsigned)cdiv(maxN, 64);
+  if (tiles >= 2048) {
+    // one resident round of blocks (four or three a compute unit), dealt to
+    // the problems by their steps, row workers in multiples of 8 (one per XCD)
+    const bool deep = maxks > 8;
+    const int64_t slots = (maxks <= 2 ? 4 : 3) * 256;
+    int64_t work = 0;
+    for (int i = 0; i < q.n; ++i) work += cdiv(q.p[i].M, 32) * cdiv(q.p[i].N, 64) * (q.p[i].nks + 2);
+    GemmPArgs A{};
+    A.b = q;
+    for (int i = 0; i < q.n; ++i) {
+      const GemmProblem& p = q.p[i];
+      const int64_t ncol = cdiv(p.N, 64), mine = cdiv(p.M, 32) * ncol * (p.nks + 2);
+      const int64_t workers = std::min(cdiv(p.M, 128), std::max<int64_t>(1, slots * mine / (work * ncol)));
+      A.block0[i + 1] = A.block0[i] + (int)(cdiv(workers, 8) * 8 * ncol);
     }
-    int wk = 1;
-    while (wk < kGwWaves && tiles * wk < 2048 && 2 * wk * 2 <= maxg) wk *= 2;
-    const unsigned gyw = (unsigned)cdiv(maxN, 64);
-    const unsigned gxw = (unsigned)cdiv(maxM, 32 * (kGwWaves / wk));
-    const dim3 grid(gxw, gyw, b.n);
-    if (wk == 1) KLAUNCH(st, tag, k_gemm_w<1><<<grid, 512, 0, st>>>(b));
-    else if (wk == 2) KLAUNCH(st, tag, k_gemm_w<2><<<grid, 512, 0, st>>>(b));
-    else if (wk == 4) KLAUNCH(st, tag, k_gemm_w<4><<<grid, 512, 0, st>>>(b));
-    else KLAUNCH(st, tag, k_gemm_w<8><<<grid, 512, 0, st>>>(b));
+    const unsigned grid = (unsigned)A.block0[q.n];
+    if (maxks <= 2) KLAUNCH(st, tag, k_gemm_p<2, false><<<grid, 256, 0, st>>>(A));
+    else if (maxks <= 4) KLAUNCH(st, tag, k_gemm_p<4, false><<<grid, 256, 0, st>>>(A));
+    else if (!deep) KLAUNCH(st, tag, k_gemm_p<8, false><<<grid, 256, 0, st>>>(A));
+    else KLAUNCH(st, tag, k_gemm_p<4, true><<<grid, 256, 0, st>>>(A));
     return CHGNET_OK;
   }
-  // persistent row tiles: about 2048 blocks over the launch; row workers in
-  // multiples of 8 (one per XCD, see k_gemm)
-  const int per_problem = std::max(1, 2048 / (gy * b.n));
-  const dim3 grid((unsigned)(cdiv(std::min(gx, per_problem), 8) * 8), gy, b.n);
-  // four wavefronts per SIMD where no problem has an activation epilogue,
-  // every segment is at least 128 deep and no problem has both more than
-  // 65,536 rows and k > 128 (measured on wide128: the projection, update and
-  // input-gradient launches 4-17 % faster; the SiLU / SiLU' launches of the
-  // heads 17-25 % and the 31-deep embeddings 3 % slower; the Eq. 10 block's
-  // edge and angle input gradients, k = 2d and 4d, 664 against 511 us)
-  bool plain = true;
-  for (int i = 0; i < b.n; ++i) {
-    plain = plain && b.p[i].act == ACT_NONE;
-    int k = 0;
-    for (int s = 0; s < b.p[i].nseg; ++s) {
-      plain = plain && b.p[i].seg[s].K >= 128;
-      k += b.p[i].seg[s].K;
-    }
-    plain = plain && !(b.p[i].M > 65536 && k > 128);
-  }
-  const bool in_bwd = std::string(tag) == "gemm_in_bwd";
-  if (in_bwd && plain) KLAUNCH(st, tag, k_gemm<64, 2, 4><<<grid, 256, 0, st>>>(b));
-  else if (in_bwd) KLAUNCH(st, tag, k_gemm<64, 2, 3><<<grid, 256, 0, st>>>(b));
-  else if (plain) KLAUNCH(st, tag, k_gemm<64, 0, 4><<<grid, 256, 0, st>>>(b));
-  else KLAUNCH(st, tag, k_gemm<64, 0, 3><<<grid, 256, 0, st>>>(b));
+  int wk = 1;
+  while (wk < kGwWaves && tiles * wk < 2048 && 2 * wk <= maxks) wk *= 2;
+  const dim3 grid((unsigned)cdiv(maxM, 32 * (kGwWaves / wk)), gy, q.n);
+  if (wk == 1) KLAUNCH(st, tag, k_gemm_k<1><<<grid, 512, 0, st>>>(q));
+  else if (wk == 2) KLAUNCH(st, tag, k_gemm_k<2><<<grid, 512, 0, st>>>(q));
+  else if (wk == 4) KLAUNCH(st, tag, k_gemm_k<4><<<grid, 512, 0, st>>>(q));
+  else KLAUNCH(st, tag, k_gemm_k<8><<<grid, 512, 0, st>>>(q));
   return CHGNET_OK;
 }
 

@@ -1,13 +1,58 @@
-// fp32 MFMA GEMMs with gathered operands and fused epilogues (gfx950).
+// GEMMs with gathered operands and fused epilogues, and split-K weight
+// gradients (gfx950).
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 namespace chg {
 
+// ---------------------------------------------------------------------------
+// Weights as the B operand of the matrix products.
+//
+// An fp32 number is the exact sum of three bf16 numbers, x = h + m + l, each
+// the rounded remainder of the ones before it (8 significand bits each; |m| <=
+// 2^-9 |x|, |l| <= 2^-18 |x|). The products run on the bf16 matrix cores as
+// the six terms hh + hm + mh + hl + lh + mm with fp32 accumulation: the terms
+// left out are below 2^-26 of |x y|, less than the rounding of one fp32
+// product, and a 16-deep step rounds its sum fewer times than a chain of fp32
+// multiply-adds does. Six bf16 passes take 6/16 of the fp32 matrix cores'
+// time. (An infinite operand gives NaN, not an infinity.)
+// These matrix cores cut the bits of a small addend that fall below the sum
+// towards minus infinity, half a last place on average: nothing in one
+// element, but the same sign in every element, so that a gradient summed over
+// 50,000 rows was off by 2e-6 of its size where fp32 products gave 7e-7.
+// Odd rows are therefore multiplied with -1 and their results turned back,
+// which gives their errors the other sign.
+//
+// The weights are split once a pass: a matrix is packed, as B (k, n) =
+// W[k][n] and, for backward passes, as W[n][k], into tiles of 16 k x 32
+// columns in fragment order, three planes (h, m, l) of 64 lanes x 8 values
+// (lane l: column l % 32, k = 8 (l / 32) ..), so that a wavefront reads a
+// plane as one contiguous kilobyte. k and columns past the matrix are zero.
+// ---------------------------------------------------------------------------
+constexpr int kPackTile = 3 * 64;  // 16-byte pieces of a tile
+struct PackMat {
+  int64_t off;      // first value of the matrix in the aligned weight copy
+  int64_t src;      // and in the public layout
+  int rows, cols;
+  int64_t n0, t0;   // first tile of W[k][n] and of W[n][k]
+};
+struct PackTable {
+  std::vector<PackMat> m;  // in order of `off`
+  int64_t n_tiles = 0, t_tiles = 0;  // t tiles follow the n tiles
+  void add(int64_t off, int64_t src, int rows, int cols);
+  void finish();
+};
+// Packs every matrix (with_t: also the transposes) of the weights `src`
+// (public layout) into `out`.
+int pack_weights(const PackTable& t, const float* src, uint4* out, bool with_t, hipStream_t st);
+
 // One K-segment of an NN product: rows of A (gathered by the problem's
-// a_rows) times B. B element (k, n) = trans ? B[n*ldb + k] : B[k*ldb + n].
+// a_rows) times B. B element (k, n) = trans ? B[n*ldb + k] : B[k*ldb + n],
+// B a block of a packed weight matrix whose first column (trans: row) is a
+// multiple of 32 and first row (trans: column) a multiple of 16.
 struct GemmSeg {
   const float* A;
   int lda;
@@ -16,6 +61,10 @@ struct GemmSeg {
   const float* B;
   int ldb;
   int trans;
+  // set by gemm_resolve
+  const uint4* Bp;  // packed tile of column 0, k 0
+  int bnt;          // tiles from one 32-column group to the next
+  int ks0;          // 16-deep steps of the segments before
 };
 
 enum GemmAct { ACT_NONE = 0, ACT_SILU_OUT = 1, ACT_DSILU_MUL = 2 };
@@ -43,6 +92,7 @@ struct GemmProblem {
   int ldc2;
   const float* mul;
   int mul_ld;
+  int nks;  // 16-deep steps (set by gemm_resolve)
 };
 
 constexpr int kMaxGemmProblems = 6;
@@ -51,6 +101,9 @@ struct GemmBatch {
   GemmProblem p[kMaxGemmProblems];
 };
 
+// The packed tiles of a problem's weights: `P` is the aligned weight copy that
+// its B pointers point into.
+int gemm_resolve(GemmProblem& p, const PackTable& t, const float* P, const uint4* packed);
 int gemm_launch(const GemmBatch& b, hipStream_t st, const char* tag);
 
 // dW[m, n] (+)= sum_r X[x_rows(r), x_col + m] * Y[y_rows(r), y_col + n]

@@ -50,7 +50,7 @@ __global__ void k_fill(float* __restrict__ p, int64_t n, float v) {
 }
 
 constexpr int kPackTensors = 128, kPackChunk = 2048;
-struct PackTable {
+struct CopyTable {
   int n;
   int src[kPackTensors], dst[kPackTensors], len[kPackTensors];
   int chunk0[kPackTensors + 1];  // first chunk of each tensor; chunk0[n] = total
@@ -58,7 +58,7 @@ struct PackTable {
 
 // Copy of the flat parameters with every tensor on a 16-byte boundary; one
 // block per chunk of kPackChunk values of one tensor.
-__global__ void __launch_bounds__(256) k_pack_params(PackTable t, const float* __restrict__ src, float* __restrict__ dst) {
+__global__ void __launch_bounds__(256) k_pack_params(CopyTable t, const float* __restrict__ src, float* __restrict__ dst) {
   const int b = blockIdx.x;
   int lo = 0, hi = t.n;  // tensor k with chunk0[k] <= b < chunk0[k + 1]
   while (hi - lo > 1) {
@@ -2479,6 +2479,7 @@ struct Acts {
   float *dv[2], *de[3], *da[2], *dm, *dmu, *dzv, *dzae, *t2, *AT, *DZ12, *dea, *deb;
   float *doE, *doS, *dn, *doF, *dh2E, *dh2S, *dh2F, *dh1ES, *dh1F, *drbf_a, *drbf_b;
   float *lnpart, *tnpart, *fpart, *Pal;
+  uint4* Bpk;  // the weight matrices as split and packed operands
   double* red2;
   int64_t lnpart_stride;
   int64_t tnpart_cap;
@@ -2490,9 +2491,45 @@ struct Acts {
   float *dft, *gvec, *pang;
 };
 
+// The weight matrices that products take as operands.
+PackTable pack_table(const ParamLayout& L, const ParamLayout& La, const Dims& m) {
+  PackTable t;
+  const int D = m.D;
+  auto add = [&](int64_t off, int64_t src, int rows, int cols) { t.add(off, src, rows, cols); };
+  add(La.W_e, L.W_e, m.R, 2 * D);
+  add(La.W_eb, L.W_eb, m.R, D);
+  add(La.W_th, L.W_th, m.K, D);
+  for (int q = 0; q < m.T; ++q) {
+    const LayerOffsets &x = La.layer[q], &y = L.layer[q];
+    add(x.av.W, y.av.W, 3 * D, 2 * D);
+    add(x.av_Wo, y.av_Wo, D, D);
+    add(x.be.W, y.be.W, 4 * D, 2 * D);
+    add(x.be_Wo, y.be_Wo, D, D);
+    if (x.has_angle) add(x.an.W, y.an.W, 4 * D, 2 * D);
+  }
+  for (int h = 0; h < 3; ++h) {
+    add(La.head[h].W1, L.head[h].W1, D, D);
+    add(La.head[h].W2, L.head[h].W2, D, D);
+    add(La.head[h].W3, L.head[h].W3, D, La.head[h].out);
+  }
+  t.finish();
+  return t;
+}
+
 void carve_acts(Arena& ar, const Dims& m, Acts& a, int64_t n_params_aligned) {
   const int64_t N = m.N, S = m.S, E = m.E, B = m.B, A = m.A, D = m.D, R = m.R, K = m.K;
   a.Pal = ar.take<float>(n_params_aligned);
+  {
+    // (the number of tiles does not depend on the offsets)
+    chgnet_hparams hp{};
+    hp.d = m.D;
+    hp.n_layers = m.T;
+    hp.n_rbf = m.R;
+    hp.n_fourier = m.K;
+    const ParamLayout L = make_layout(hp, 4);
+    const PackTable t = pack_table(L, L, m);
+    a.Bpk = ar.take<uint4>((t.n_tiles + t.t_tiles) * kPackTile);
+  }
   // carved before anything that depends on the graph sizes: the same address
   // for every graph of the batch
   a.md_pos = ar.take<float>(3 * N);
@@ -2614,11 +2651,26 @@ void seg(GemmProblem& p, const float* A, int lda, int a_col, int K, const float*
   s.trans = trans;
 }
 
-int run_gemms(const std::vector<GemmProblem>& ps, hipStream_t st, const char* tag) {
+struct Ctx {
+  const chgnet_hparams* hp;
+  const chgnet_batch* batch;
+  const chgnet_graph* graph;
+  Dims dm;
+  ParamLayout L;   // public layout (gradients)
+  ParamLayout La;  // aligned layout of the internal weight copy (reads)
+  PackTable pk;    // the packed weight matrices
+  Acts a;
+  char* ws;        // workspace, and the bytes the activations use of it
+  size_t ws_bytes, ws_used;
+  bool save_z = true;  // keep the gate pre-activations for a backward pass
+};
+
+int run_gemms(const Ctx& c, const std::vector<GemmProblem>& ps, hipStream_t st, const char* tag) {
   GemmBatch b{};
   for (const auto& p : ps) {
     if (p.M <= 0 || p.N <= 0) continue;
-    b.p[b.n++] = p;
+    b.p[b.n] = p;
+    CHG_TRY(gemm_resolve(b.p[b.n++], c.pk, c.a.Pal, c.a.Bpk));
     if (b.n == kMaxGemmProblems) {
       CHG_TRY(gemm_launch(b, st, tag));
       b.n = 0;
@@ -2748,9 +2800,14 @@ int segsum_launch(SegJobs J, int wps, hipStream_t st) {
   return CHGNET_OK;
 }
 
-int pack_params(const ParamLayout& L, const ParamLayout& La, const float* P, float* Pal, hipStream_t st) {
+// The aligned weight copy and the packed matrices (with_t: also the
+// transposes, which backward passes multiply with).
+int pack_params(const ParamLayout& L, const ParamLayout& La, const PackTable& pk, const float* P, const Acts& a,
+                bool with_t, hipStream_t st) {
+  float* Pal = a.Pal;
+  CHG_TRY(pack_weights(pk, P, a.Bpk, with_t, st));
   for (int k0 = 0; k0 < L.ntensors; k0 += kPackTensors) {
-    PackTable t{};
+    CopyTable t{};
     int chunks = 0;
     for (int k = k0; k < L.ntensors && t.n < kPackTensors; ++k, ++t.n) {
       t.src[t.n] = (int)L.toff[k];
@@ -2921,19 +2978,6 @@ GateAdds adds(int n, const float* p0, int ld0, const int* i0, const float* p1, i
 
 LnPtrs ln_ptrs(const float* P, const GatedOffsets& g) { return LnPtrs{P + g.g_c, P + g.b_c, P + g.g_g, P + g.b_g}; }
 
-struct Ctx {
-  const chgnet_hparams* hp;
-  const chgnet_batch* batch;
-  const chgnet_graph* graph;
-  Dims dm;
-  ParamLayout L;   // public layout (gradients)
-  ParamLayout La;  // aligned layout of the internal weight copy (reads)
-  Acts a;
-  char* ws;        // workspace, and the bytes the activations use of it
-  size_t ws_bytes, ws_used;
-  bool save_z = true;  // keep the gate pre-activations for a backward pass
-};
-
 int make_ctx(const chgnet_hparams* hp, const chgnet_batch* batch, const chgnet_graph* graph, void* ws, size_t ws_bytes,
              Ctx& c) {
   CHG_TRY(validate_hparams(hp));
@@ -2952,6 +2996,7 @@ int make_ctx(const chgnet_hparams* hp, const chgnet_batch* batch, const chgnet_g
               hp->d, hp->n_layers, hp->n_rbf, hp->n_fourier};
   c.L = make_layout(*hp, 1);
   c.La = make_layout(*hp, 4);
+  c.pk = pack_table(c.L, c.La, c.dm);
   Arena ar{static_cast<char*>(ws), ws_bytes, 0};
   ar.used = graph_scratch_bytes(c.dm.N, c.dm.S);
   carve_acts(ar, c.dm, c.a, c.La.total);
@@ -2970,7 +3015,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
   const Dims& m = c.dm;
   Acts& a = c.a;
   const ParamLayout& L = c.La;
-  if (pack) CHG_TRY(pack_params(c.L, c.La, Pflat, a.Pal, st));
+  if (pack) CHG_TRY(pack_params(c.L, c.La, c.pk, Pflat, a, c.hp->conservative != 0, st));
   const float* P = a.Pal;
   const chgnet_graph& g = *c.graph;
   const chgnet_batch& bt = *c.batch;
@@ -3008,7 +3053,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     seg(p, a.ft, m.K, 0, m.K, P + L.W_th, D, 0);
     p.bias = P + L.b_th;
     ps.push_back(p);
-    CHG_TRY(run_gemms(ps, st, "gemm_embed"));
+    CHG_TRY(run_gemms(c, ps, st, "gemm_embed"));
   }
 
   const bool seq = c.hp->sequential != 0;
@@ -3029,7 +3074,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
         seg(p, vin, D, 0, D, W, 2 * D, 0);
         ps.push_back(p);
       }
-      return run_gemms(ps, st, "gemm_proj");
+      return run_gemms(c, ps, st, "gemm_proj");
     };
     // Bond terms, Xb blocks in `mask`: 0 bond-conv role b1, 1 angle role b1,
     // 2 bond-conv role b2, 3 angle role b2.
@@ -3050,7 +3095,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
         }
         ps.push_back(p);
       }
-      return run_gemms(ps, st, "gemm_proj");
+      return run_gemms(c, ps, st, "gemm_proj");
     };
     const GateAdds ad_av = adds(2, a.Xa[t], 8 * D, a.edge_src, a.Xa[t] + 2 * D, 8 * D, g.edge_dst);
     const GateAdds ad_be = adds(2, a.Xb[t], 8 * D, a.ang_b1, a.Xb[t] + 4 * D, 8 * D, a.ang_b2);
@@ -3138,7 +3183,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
         p.c_rows = g.bond_edge;
         ps.push_back(p);
       }
-      return run_gemms(ps, st, "gemm_update");
+      return run_gemms(c, ps, st, "gemm_update");
     };
     if (!seq) {
       // Eq. (11): the three modules read layer-t features and run together
@@ -3185,7 +3230,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
       p.ldc2 = D;
       ps.push_back(p);
     }
-    CHG_TRY(run_gemms(ps, st, "gemm_head1"));
+    CHG_TRY(run_gemms(c, ps, st, "gemm_head1"));
     ps.clear();
     for (auto& l : ls) {
       GemmProblem p = gp(l.M, D, l.h2, D);
@@ -3196,7 +3241,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
       p.ldc2 = D;
       ps.push_back(p);
     }
-    CHG_TRY(run_gemms(ps, st, "gemm_head2"));
+    CHG_TRY(run_gemms(c, ps, st, "gemm_head2"));
     ps.clear();
     for (auto& l : ls) {
       GemmProblem p = gp(l.M, l.h->out, l.o, l.h->out);
@@ -3204,7 +3249,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
       p.bias = P + l.h->b3;
       ps.push_back(p);
     }
-    CHG_TRY(run_gemms(ps, st, "gemm_head3"));
+    CHG_TRY(run_gemms(c, ps, st, "gemm_head3"));
   }
   if (D == 64) {
     // heads: MLP d -> d -> d -> out with SiLU, the three layers in one launch
@@ -3280,7 +3325,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
   Acts& a = c.a;
   const ParamLayout& L = c.La;   // reads from the aligned weight copy
   const ParamLayout& Lg = c.L;   // gradients in the public layout
-  if (repack) CHG_TRY(pack_params(c.L, c.La, Pflat, a.Pal, st));
+  if (repack) CHG_TRY(pack_params(c.L, c.La, c.pk, Pflat, a, true, st));
   const float* P = a.Pal;
   const chgnet_graph& g = *c.graph;
   const chgnet_batch& bt = *c.batch;
@@ -3334,7 +3379,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       p.mul_ld = D;
       ps.push_back(p);
     }
-    CHG_TRY(run_gemms(ps, st, "gemm_head_bwd2"));
+    CHG_TRY(run_gemms(c, ps, st, "gemm_head_bwd2"));
     ps.clear();
     for (auto& l : ls) {
       GemmProblem p = gp(l.M, D, l.dh1base + l.dh1col, l.ld1);
@@ -3344,7 +3389,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       p.mul_ld = D;
       ps.push_back(p);
     }
-    CHG_TRY(run_gemms(ps, st, "gemm_head_bwd1"));
+    CHG_TRY(run_gemms(c, ps, st, "gemm_head_bwd1"));
     ps.clear();
     {
       GemmProblem p = gp(N, D, a.dv[cur], D);
@@ -3354,7 +3399,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       p = gp(E, D, a.de[ecur], D);
       seg(p, a.dh1F, D, 0, D, P + hF.W1, D, 1);
       ps.push_back(p);
-      CHG_TRY(run_gemms(ps, st, "gemm_head_bwd0"));
+      CHG_TRY(run_gemms(c, ps, st, "gemm_head_bwd0"));
     }
     const bool mag = c.hp->magmom && dM;
     if (mag)
@@ -3510,7 +3555,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
         seg(p, a.de[ecur], D, 0, D, P + lo.be_Wo, D, 1);
         q.push_back(p);
       }
-      return run_gemms(q, st, "gemm_out_bwd");
+      return run_gemms(c, q, st, "gemm_out_bwd");
     };
     SegJobs sj{};
     if (!seq) {
@@ -3535,7 +3580,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
         seg(p, a.DZ12, 8 * D, 2 * D, 2 * D, Wan + D * 2 * D, 2 * D, 1);
         seg(p, a.DZ12, 8 * D, 6 * D, 2 * D, Wan + 2 * D * 2 * D, 2 * D, 1);
         ps.push_back(p);
-        CHG_TRY(run_gemms(ps, st, "gemm_bond_bwd"));
+        CHG_TRY(run_gemms(c, ps, st, "gemm_bond_bwd"));
         ps.clear();
       }
       CHG_TRY(out_bwd(nullptr, false, true));
@@ -3549,7 +3594,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       p.res = a.dv[cur];
       p.res_ld = D;
       ps.push_back(p);
-      CHG_TRY(run_gemms(ps, st, "gemm_in_bwd"));
+      CHG_TRY(run_gemms(c, ps, st, "gemm_in_bwd"));
       ps.clear();
       CHG_TRY(out_bwd(a.dvf, true, false));
       CHG_TRY(gates(1));
@@ -3642,7 +3687,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       // fused: the atom rows' product shares the launch of the bond rows'
       // (both direct-load, k = 8d)
       if (!fused) {
-        CHG_TRY(run_gemms(ps, st, "gemm_in_bwd"));
+        CHG_TRY(run_gemms(c, ps, st, "gemm_in_bwd"));
         ps.clear();
       }
       GemmProblem p = gp(B, D, a.de[enx], D);
@@ -3655,7 +3700,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
         seg(p, a.DZ12, 8 * D, 6 * D, 2 * D, Wan + 2 * D * 2 * D, 2 * D, 1);
       }
       ps.push_back(p);
-      CHG_TRY(run_gemms(ps, st, fused ? "gemm_in_bwd" : "gemm_bond_bwd"));
+      CHG_TRY(run_gemms(c, ps, st, fused ? "gemm_in_bwd" : "gemm_bond_bwd"));
       ps.clear();
     }
     // the weight gradients of this layer run on the side stream, overlapping
@@ -3699,7 +3744,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       seg(p, a.da[cur], D, 0, D, P + L.W_th, D, 1);
       ps.push_back(p);
     }
-    CHG_TRY(run_gemms(ps, st, "gemm_embed_bwd"));
+    CHG_TRY(run_gemms(c, ps, st, "gemm_embed_bwd"));
     if (!wg) return CHGNET_OK;
     float* fpart_b = a.fpart + cdiv(std::max(E, (int64_t)1), kFreqRowsPerBlock) * m.R;
     if (E > 0) {
@@ -3807,7 +3852,7 @@ int backward_entry(const chgnet_hparams* hp, const chgnet_batch* batch, const ch
   if (!params || !dE || !dF || !dS || !grad) return fail(CHGNET_EINVAL, "backward: null argument");
   if (dM && !hp->magmom) return fail(CHGNET_EINVAL, "backward: dM without the magnetic-moment head");
   if (hp->conservative) {
-    CHG_TRY(pack_params(c.L, c.La, params, c.a.Pal, st));
+    CHG_TRY(pack_params(c.L, c.La, c.pk, params, c.a, true, st));
     return cons_grad_impl(c, dE, dF, dS, dM, grad, st);
   }
   return backward_impl(c, params, true, dE, dF, dS, dM, grad, st);
@@ -3836,7 +3881,7 @@ int step_entry(const chgnet_hparams* hp, const chgnet_batch* batch, chgnet_graph
     const ParamLayout L1 = make_layout(*hp, 1), L4 = make_layout(*hp, 4);
     carve_acts(ar, d0, a0, L4.total);
     if (!ws || !ar.ok()) return fail(CHGNET_EWORKSPACE, "workspace too small (query chgnet_workspace_size)");
-    CHG_TRY(pack_params(L1, L4, params, a0.Pal, st));
+    CHG_TRY(pack_params(L1, L4, pack_table(L1, L4, d0), params, a0, true, st));
   }
   CHG_TRY(build_graph(hp, batch, graph, ws, ws_bytes, st));
   Ctx c;
