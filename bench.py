@@ -397,8 +397,7 @@ def mandatory_cost(tag, z):
 # its 64 x 64 wave-tile plans separately)
 def tag_symbols(tag, d):
     return {
-        "gemm_in_bwd": ["k_gemm<64, 2, 4>"],
-        "tn_in": ["k_tn<1, true>", "k_tn<1, false>"],
+        "tn_in": ["k_tn<1>"],
         "k_gate_fwd": ["k_gate_fwd_mm<%d>" % d],
         "k_gate_bwd": ["k_gate_bwd_mm" if d == 64 else "k_gate_bwd_mm128"],
     }.get(tag)

@@ -29,11 +29,6 @@
  *    buffer per host thread for the size readback (allocated on first use).
  *  - Return value: CHGNET_OK (0) or a negative error code below; the text of
  *    the last error of the calling thread is chgnet_last_error_string().
- *  - Environment: CHGNET_TN_WIDE_MIN_UNITS (a non-negative integer, read on
- *    every weight-gradient launch) sets the launch size, in units of 64 rows
- *    times 64 x 64 output tiles, from which the weight-gradient products use
- *    64 x 128 wave tiles (default 24576). It changes only the kernel
- *    schedule, not what is computed; unset is the measured default.
  *
  * Hyperparameters (Sec. IV): feature width d (64; 128 supported), layers T,
  * 31 radial and 31 angular basis functions, envelope exponent p = 8, atom
@@ -284,9 +279,7 @@ const char* chgnet_last_error_string(void);
  * "<tag> <launches> <total milliseconds>\n". Tags are kernel names, or the
  * role of a GEMM launch (gemm_proj: per-atom and per-bond terms of the split
  * first layers; gemm_in_bwd: input gradients of the interaction block;
- * tn_in: weight gradients of the interaction block; ...); a call that
- * launches several kernels under one tag (the weight gradients' 64 x 128
- * and 64 x 64 wave-tile launches) is timed as one launch. Returns
+ * tn_in: weight gradients of the interaction block; ...). Returns
  * CHGNET_EINVAL if buf is too small and CHGNET_EWORKSPACE if more than
  * max_launches launches ran. */
 int chgnet_profile_start(int max_launches);

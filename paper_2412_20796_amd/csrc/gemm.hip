@@ -10,7 +10,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstdlib>
 #include <string>
 
 #include "common.hpp"
@@ -519,20 +518,28 @@ struct TnLaunch {
 };
 
 // Split-K X^T Y without LDS tiles: each wavefront streams its own row range
-// and loads its MFMA fragments straight from global memory. In MFMA k-step i
-// of a group of 2 KS rows, lane half h supplies row KS h + i; lane c = lane % 32
-// holds columns vx c + v (v < vx) of the X row and vy c + u of the Y row, so
-// wave tile v of X and u of Y are column-interleaved and the fragment loads
-// are 4-, 8- or 16-byte vectors (vy = 4: 64 x 128 wave tiles, in a launch of
-// their own at two blocks per compute unit). The next group's fragments are loaded while the
-// current group's MFMAs run. The four wavefronts of a block take consecutive
+// and loads its fragments straight from global memory, 16 rows a step: lane
+// half h supplies rows 8 h .. 8 h + 7; lane c = lane % 32 holds columns
+// vx c + v (v < vx) of the X rows and vy c + u of the Y rows, so wave tile v
+// of X and u of Y are column-interleaved and the loads are 4- or 8-byte
+// vectors. Both
+// operands are split into three bf16 parts and multiplied on the bf16 matrix
+// cores (see gemm.hpp; odd wavefronts multiply -X, so that the one-sided
+// rounding cancels in the block's sum). The next steps' rows are loaded while
+// a step is multiplied. The four wavefronts of a block take consecutive
 // quarters of the block's rows; their tiles are added in wave order in LDS.
 // A problem with a bias row also sums the Y columns (the bias gradient of a
 // layer whose weight gradient is X^T Y).
+// Bound by the vector instructions that split the operands (about 230 a step
+// against 24 matrix instructions of 32 cycles) and, beside the gate kernels,
+// by the compute units those leave. Against the fp32 matrix cores (64 x 128
+// wave tiles on large launches): wide128 step 21.9 -> 19.8 ms, 64 tail cells
+// with the Eq. 10 block 4.13 -> 3.87 ms, conservative training 6.87 -> 6.58.
 // ROLE only names the instantiation (1: interaction-block weight gradients).
 // reduction buffer: two wave tiles and four wavefronts' column sums
-template <bool WIDE>
-constexpr int tn_red_floats() { return WIDE ? 2 * 64 * 128 + 4 * 128 : 2 * 64 * 64 + 4 * 64; }
+constexpr int kTnRedFloats = 2 * 64 * 64 + 4 * 64;
+constexpr int kTnBuffers = 2;
+constexpr int kTnSlots = 2 * 256;  // resident blocks
 // Rows per split-K chunk at most: the eight output tiles of a chunk stream
 // the same rows on one XCD, and a chunk of 2048 rows of 384 floats (3 MB)
 // stays in that XCD's 4 MB L2 while they do (4480-row chunks measured 1.30
@@ -541,43 +548,24 @@ constexpr int kTnMaxChunkRows = 2048;
 // rows of one wavefront's range (a quarter of a chunk): the size of its
 // LDS row-index tables
 constexpr int kTnWaveRows = kTnMaxChunkRows / 4;
-// 64-row units of a launch (summed over its products and 64 x 64 wave tiles)
-// from which it takes 64 x 128 wave tiles where N allows (enough work that
-// 64 x 64 tiles would fill every block slot with kTnMaxChunkRows-row
-// chunks). Measured per training step:
-// wide128 -0.4 ms; triclinic40 (below the bound) 0.06 ms slower with them.
-constexpr int kTnWideUnits = 3 * 256 * (kTnMaxChunkRows / 64);
-// The bound in force: CHGNET_TN_WIDE_MIN_UNITS (a non-negative integer,
-// read on every launch) overrides kTnWideUnits, so that the wide tiles can
-// also be run, and checked, on small batches.
-int64_t tn_wide_min_units() {
-  const char* e = std::getenv("CHGNET_TN_WIDE_MIN_UNITS");
-  if (e != nullptr && *e != 0) {
-    char* end = nullptr;
-    const long long v = std::strtoll(e, &end, 10);
-    if (*end == 0 && v >= 0) return v;
-  }
-  return kTnWideUnits;
-}
-
 // RIDX: the problem gathers X or Y rows through an index array. The wave
 // first copies its range's row indices to LDS (ridx: [2][kTnWaveRows], in the
 // reduction buffer, which the block takes over once every wave is past its
 // rows), so the fragment loads depend on no other global load and the loads
-// of the groups ahead stay in flight.
+// of the steps ahead stay in flight.
 template <int VX, int VY, bool XFULL, bool YFULL, bool HASX, bool RIDX>
 __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int n0, bool colsum, float* red,
                                         int* ridx, float* __restrict__ part) {
-  // MFMA k-steps (row pairs) per register buffer: 2, or 1 where two-column
-  // fragments are loaded one element at a time (partial or unaligned tiles,
-  // not on the common shapes)
-  constexpr int KS = ((VX == 2 && HASX && !XFULL) || (VY >= 2 && !YFULL)) ? 1 : 2;
-  const TnProblem& P = Q.p;
+  // (the plan's fields by value: through a reference the whole argument block
+  // went to scratch memory)
+  const float *const PX = Q.p.X + (HASX ? Q.p.x_col : 0), *const PY = Q.p.Y + Q.p.y_col;
+  const int *const x_rows = Q.p.x_rows, *const y_rows = Q.p.y_rows;
+  const int ldx = Q.p.ldx, ldy = Q.p.ldy, PM = Q.p.M, PN = Q.p.N, PR = Q.p.R;
   const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar row range
   const int wr = Q.rpc / 4;
   const int rlo = chunk * Q.rpc + wave * wr;
-  const int rhi = min(P.R, rlo + wr);
+  const int rhi = min(PR, rlo + wr);
   const int xm = m0 + VX * c, yn = n0 + VY * c;
   v16f acc[VX][VY];
 #pragma unroll
@@ -589,100 +577,121 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
   float ysum[VY];
 #pragma unroll
   for (int u = 0; u < VY; ++u) ysum[u] = 0.f;
-  constexpr int NB = 4;  // register buffers: NB - 1 groups in flight ahead of the MFMAs
-  float xf[NB][KS][VX], yf[NB][KS][VY];
+  // register buffers: NB - 1 steps in flight ahead of the matrix cores
+  constexpr int NB = kTnBuffers;
+  float xf[NB][8][VX], yf[NB][8][VY];
   // Branch-free loads: rows and columns are clamped into the matrix. Columns
   // past M or N only reach outputs that are not stored; rows past the wave's
-  // range are cancelled by a 0/1 mask on the Y values, applied when the
-  // group is consumed, so that every load of a group is in flight at once.
-  float rmask[NB][KS];
+  // range are zeroed in the range's last step.
   if (RIDX) {
     for (int r = rlo + lane; r < rhi; r += 64) {
-      ridx[r - rlo] = P.x_rows ? P.x_rows[r] : r;
-      ridx[kTnWaveRows + r - rlo] = P.y_rows ? P.y_rows[r] : r;
+      ridx[r - rlo] = x_rows ? x_rows[r] : r;
+      ridx[kTnWaveRows + r - rlo] = y_rows ? y_rows[r] : r;
     }
   }
+  auto load_x = [&](const float* xp, int i, int b, int col) {
+    if (XFULL) {
+      const float2 t = *reinterpret_cast<const float2*>(xp + col);
+      xf[b][i][0] = t.x;
+      xf[b][i][VX - 1] = t.y;
+    } else {
+#pragma unroll
+      for (int v = 0; v < VX; ++v) xf[b][i][v] = xp[col - xm + min(xm + v, PM - 1)];
+    }
+  };
+  auto load_y = [&](const float* yp, int i, int b, int col) {
+    if (YFULL) {
+      const float2 t = *reinterpret_cast<const float2*>(yp + col);
+      yf[b][i][0] = t.x;
+      yf[b][i][VY - 1] = t.y;
+    } else {
+#pragma unroll
+      for (int u = 0; u < VY; ++u) yf[b][i][u] = yp[col - yn + min(yn + u, PN - 1)];
+    }
+  };
+  // a lane's offset from the first row of a step (rows in order): the row's
+  // own address is uniform, so a load needs no address arithmetic
+  const int xo = 8 * h * ldx + xm, yo = 8 * h * ldy + yn;
+  // the 16 rows from g, all inside the range (in order: g is uniform)
   auto fetch = [&](int g, int b) {
-    int xr[KS], yr[KS];
+    if constexpr (!RIDX) {
+      const float* xb = HASX ? PX + (int64_t)g * ldx : nullptr;
+      const float* yb = PY + (int64_t)g * ldy;
 #pragma unroll
-    for (int i = 0; i < KS; ++i) {
-      xr[i] = yr[i] = min(g + KS * h + i, rhi - 1);
-      rmask[b][i] = g + KS * h + i < rhi ? 1.f : 0.f;
-    }
-    if (RIDX)
-#pragma unroll
-      for (int i = 0; i < KS; ++i) {
-        xr[i] = ridx[xr[i] - rlo];
-        yr[i] = ridx[kTnWaveRows + yr[i] - rlo];
+      for (int i = 0; i < 8; ++i) {
+        if (HASX) load_x(xb + (int64_t)i * ldx, i, b, xo);
+        load_y(yb + (int64_t)i * ldy, i, b, yo);
       }
+    } else {
 #pragma unroll
-    for (int i = 0; i < KS; ++i) {
-      if (HASX) {
-        const float* xp = P.X + (int64_t)xr[i] * P.ldx + P.x_col;
-        if (XFULL) {
-          const float2 t = *reinterpret_cast<const float2*>(xp + xm);
-          xf[b][i][0] = t.x;
-          xf[b][i][VX - 1] = t.y;
-        } else {
-#pragma unroll
-          for (int v = 0; v < VX; ++v) xf[b][i][v] = xp[min(xm + v, P.M - 1)];
-        }
-      }
-      const float* yp = P.Y + (int64_t)yr[i] * P.ldy + P.y_col;
-      if (YFULL && VY == 4) {
-        const float4 t = *reinterpret_cast<const float4*>(yp + yn);
-        yf[b][i][0] = t.x;
-        yf[b][i][1 % VY] = t.y;
-        yf[b][i][2 % VY] = t.z;
-        yf[b][i][VY - 1] = t.w;
-      } else if (YFULL) {
-        const float2 t = *reinterpret_cast<const float2*>(yp + yn);
-        yf[b][i][0] = t.x;
-        yf[b][i][VY - 1] = t.y;
-      } else {
-#pragma unroll
-        for (int u = 0; u < VY; ++u) yf[b][i][u] = yp[min(yn + u, P.N - 1)];
+      for (int i = 0; i < 8; ++i) {
+        const int at = g - rlo + 8 * h + i;
+        if (HASX) load_x(PX + (int64_t)ridx[at] * ldx, i, b, xm);
+        load_y(PY + (int64_t)ridx[kTnWaveRows + at] * ldy, i, b, yn);
       }
     }
   };
+  const unsigned flip = (unsigned)(wave & 1) << 31;
   auto compute = [&](int b) {
+    if (colsum) {
 #pragma unroll
-    for (int i = 0; i < KS; ++i) {
-      float y[VY];
+      for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int u = 0; u < VY; ++u) y[u] = yf[b][i][u] * rmask[b][i];
-      if (HASX) {
+        for (int u = 0; u < VY; ++u) ysum[u] += yf[b][i][u];
+    }
+    if (HASX) {
+      Split8 xs[VX];
 #pragma unroll
-        for (int v = 0; v < VX; ++v)
+      for (int v = 0; v < VX; ++v) {
+        float t[8];
 #pragma unroll
-          for (int u = 0; u < VY; ++u)
-            acc[v][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf[b][i][v], y[u], acc[v][u], 0, 0, 0);
+        for (int i = 0; i < 8; ++i) t[i] = __uint_as_float(__float_as_uint(xf[b][i][v]) ^ flip);
+        xs[v] = split8(t);
       }
-      if (colsum) {
 #pragma unroll
-        for (int u = 0; u < VY; ++u) ysum[u] += y[u];
+      for (int u = 0; u < VY; ++u) {
+        float t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = yf[b][i][u];
+        const Split8 y = split8(t);
+#pragma unroll
+        for (int v = 0; v < VX; ++v) mfma_split(xs[v], y, acc[v][u]);
       }
     }
   };
-  // a ring of NB register buffers with constant indices (NB groups per
-  // iteration); a fixed trip count (rows past the range are masked) keeps
-  // the accumulators in place
-  constexpr int GRW = 2 * KS;  // rows per group (KS per lane half)
-  const int iters = rhi > rlo ? (rhi - rlo + NB * GRW - 1) / (NB * GRW) : 0;
-  if (iters > 0) {
+  // the whole steps of the range, through a ring of NB register buffers with
+  // constant indices (a step past the last loads the last one again)
+  const int nf = rhi > rlo ? (rhi - rlo) / 16 : 0;
+  if (nf > 0) {
+    auto step = [&](int s) { return rlo + 16 * min(s, nf - 1); };
 #pragma unroll
-    for (int b = 0; b < NB - 1; ++b) fetch(rlo + b * GRW, b);
-  }
-  for (int it = 0; it < iters; ++it) {
-    const int g = rlo + it * NB * GRW;
-    const bool more = it + 1 < iters;
-    fetch(g + (NB - 1) * GRW, NB - 1);
-    compute(0);
+    for (int b = 0; b < NB - 1; ++b) fetch(step(b), b);
+    for (int s = 0; s < nf; s += NB) {
 #pragma unroll
-    for (int b = 1; b < NB; ++b) {
-      if (more) fetch(g + (NB - 1 + b) * GRW, b - 1);
-      compute(b);
+      for (int b = 0; b < NB; ++b) {
+        fetch(step(s + b + NB - 1), (b + NB - 1) % NB);
+        if (s + b < nf) compute(b);
+      }
     }
+  }
+  // the rows left: clamped into the range, those past it zeroed (the clamped
+  // X row as well, so that a value that is not finite does not reach the sum)
+  const int g = rlo + 16 * nf;
+  if (g < rhi) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = min(g + 8 * h + i, rhi - 1), at = r - rlo;
+      const bool in = g + 8 * h + i < rhi;
+      if (HASX) {
+        load_x(PX + (int64_t)(RIDX ? ridx[at] : r) * ldx, i, 0, xm);
+#pragma unroll
+        for (int v = 0; v < VX; ++v) xf[0][i][v] = in ? xf[0][i][v] : 0.f;
+      }
+      load_y(PY + (int64_t)(RIDX ? ridx[kTnWaveRows + at] : r) * ldy, i, 0, yn);
+#pragma unroll
+      for (int u = 0; u < VY; ++u) yf[0][i][u] = in ? yf[0][i][u] : 0.f;
+    }
+    compute(0);
   }
   // the row-index tables share this LDS: every wavefront is past its rows
   if (RIDX) __syncthreads();
@@ -703,7 +712,8 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
 #pragma unroll
       for (int u = 0; u < VY; ++u)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) dst[((v * VY + u) * 16 + j) * 64 + lane] = acc[v][u][j];
+        for (int j = 0; j < 16; ++j)
+          dst[((v * VY + u) * 16 + j) * 64 + lane] = __uint_as_float(__float_as_uint(acc[v][u][j]) ^ flip);
   };
   auto add = [&](const float* src) {
 #pragma unroll
@@ -723,19 +733,19 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
   __syncthreads();
   if (wave != 0) return;
   add(red);
-  const int rows_out = P.M + Q.has_bias;
-  float* out = part + Q.off + (int64_t)chunk * rows_out * P.N;
+  const int rows_out = PM + Q.has_bias;
+  float* out = part + Q.off + (int64_t)chunk * rows_out * PN;
   if (HASX) {
 #pragma unroll
     for (int v = 0; v < VX; ++v)
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         const int m = m0 + VX * (8 * (j >> 2) + 4 * h + (j & 3)) + v;
-        if (m >= P.M) continue;
+        if (m >= PM) continue;
 #pragma unroll
         for (int u = 0; u < VY; ++u) {
           const int n = yn + u;
-          if (n < P.N) out[(int64_t)m * P.N + n] = acc[v][u][j];
+          if (n < PN) out[(int64_t)m * PN + n] = acc[v][u][j];
         }
       }
   }
@@ -746,7 +756,7 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
       const int k = u * 32 + c;
       const float s = (ys[k] + ys[CS + k]) + (ys[2 * CS + k] + ys[3 * CS + k]);
       const int n = yn + u;
-      if (n < P.N) out[(int64_t)P.M * P.N + n] = s;
+      if (n < PN) out[(int64_t)PM * PN + n] = s;
     }
   }
 }
@@ -775,13 +785,11 @@ __device__ __forceinline__ void tn_dispatch(const TnPlan& Q, int chunk, int m0, 
   }
 }
 
-// WIDE: the launch of the plans with 64 x 128 wave tiles (their blocks come
-// first); b0 is the launch's first block.
-template <int ROLE, bool WIDE>
-__global__ void __launch_bounds__(256, WIDE ? 2 : 3) k_tn(TnLaunch L, int b0, float* __restrict__ part) {
-  __shared__ float red[tn_red_floats<WIDE>()];
-  static_assert(4 * 2 * kTnWaveRows <= tn_red_floats<false>(), "row-index tables fit in the reduction buffer");
-  const int bid = b0 + (int)blockIdx.x;
+template <int ROLE>
+__global__ void __launch_bounds__(256, 2) k_tn(TnLaunch L, float* __restrict__ part) {
+  __shared__ float red[kTnRedFloats];
+  static_assert(4 * 2 * kTnWaveRows <= kTnRedFloats, "row-index tables fit in the reduction buffer");
+  const int bid = (int)blockIdx.x;
   int k = 0;
   while (k + 1 < L.n && bid >= L.q[k + 1].block0) ++k;
   const TnPlan& Q = L.q[k];
@@ -807,30 +815,10 @@ __global__ void __launch_bounds__(256, WIDE ? 2 : 3) k_tn(TnLaunch L, int b0, fl
   // the rows are 8-byte aligned
   const TnProblem& P = Q.p;
   const bool xf = Q.vx == 2 && P.X && ((P.ldx | P.x_col) & 1) == 0 && ((uintptr_t)P.X & 7) == 0 && m0 + 64 <= P.M;
+  const bool yf = Q.vy == 2 && ((P.ldy | P.y_col) & 1) == 0 && ((uintptr_t)P.Y & 7) == 0 && n0 + 64 <= P.N;
   int* ridx = reinterpret_cast<int*>(red) + (threadIdx.x >> 6) * 2 * kTnWaveRows;
-  if constexpr (WIDE) {
-    const bool yf = ((P.ldy | P.y_col) & 3) == 0 && ((uintptr_t)P.Y & 15) == 0 && n0 + 128 <= P.N;
-    if (Q.tiles_m == 0) {
-      // column sums only
-      if (P.x_rows || P.y_rows) {
-        if (yf) tn_wave<1, 4, false, true, false, true>(Q, chunk, m0, n0, colsum, red, ridx, part);
-        else tn_wave<1, 4, false, false, false, true>(Q, chunk, m0, n0, colsum, red, ridx, part);
-      } else {
-        if (yf) tn_wave<1, 4, false, true, false, false>(Q, chunk, m0, n0, colsum, red, ridx, part);
-        else tn_wave<1, 4, false, false, false, false>(Q, chunk, m0, n0, colsum, red, ridx, part);
-      }
-    } else if (P.x_rows || P.y_rows) {
-      if (xf && yf) tn_wave<2, 4, true, true, true, true>(Q, chunk, m0, n0, colsum, red, ridx, part);
-      else tn_wave<2, 4, false, false, true, true>(Q, chunk, m0, n0, colsum, red, ridx, part);
-    } else {
-      if (xf && yf) tn_wave<2, 4, true, true, true, false>(Q, chunk, m0, n0, colsum, red, ridx, part);
-      else tn_wave<2, 4, false, false, true, false>(Q, chunk, m0, n0, colsum, red, ridx, part);
-    }
-  } else {
-    const bool yf = Q.vy == 2 && ((P.ldy | P.y_col) & 1) == 0 && ((uintptr_t)P.Y & 7) == 0 && n0 + 64 <= P.N;
-    if (P.x_rows || P.y_rows) tn_dispatch<true>(Q, chunk, m0, n0, colsum, xf, yf, red, ridx, part);
-    else tn_dispatch<false>(Q, chunk, m0, n0, colsum, xf, yf, red, ridx, part);
-  }
+  if (P.x_rows || P.y_rows) tn_dispatch<true>(Q, chunk, m0, n0, colsum, xf, yf, red, ridx, part);
+  else tn_dispatch<false>(Q, chunk, m0, n0, colsum, xf, yf, red, ridx, part);
 }
 
 // Ordered column sums of chunk partials: 16 wavefronts per block, wave w
@@ -1074,28 +1062,11 @@ int tn_launch(const TnBatch& b, float* part, int64_t part_cap, hipStream_t st, c
     q.tiles_n = (int)cdiv(q.p.N, 32 * q.vy);
     units += cdiv(std::max(q.p.R, 0), 64) * std::max(q.tiles_m, 1) * q.tiles_n;
   }
-  // 64 x 128 wave tiles (half the Y fragment loads and row-index reads per
-  // MFMA; two 4-wave blocks per compute unit) for the large launches, and
-  // the column sums of bias-only problems with them (no launch of 64 x 64
-  // tiles is left for those)
-  if (units >= tn_wide_min_units()) {
-    units = 0;
-    for (int i = 0; i < L.n; ++i) {
-      TnPlan& q = L.q[i];
-      if (q.p.N % 128 == 0 && (!q.p.X || q.p.M > 32)) {
-        q.vy = 4;
-        q.tiles_n = q.p.N / 128;
-      }
-      units += cdiv(std::max(q.p.R, 0), 64) * std::max(q.tiles_m, 1) * q.tiles_n;
-    }
-  }
-  // about one block per resident slot (three 4-wave blocks per compute
+  // about one block per resident slot (two 4-wave blocks per compute
   // unit): fewer, longer blocks measured faster than several rounds
-  const int64_t per = std::max<int64_t>(1, cdiv(units, 3 * 256));
+  const int64_t per = std::max<int64_t>(1, cdiv(units, kTnSlots));
   const int rpc = (int)std::min<int64_t>(64 * per, kTnMaxChunkRows);
-  // the wide plans first: their blocks are the first launch's
-  std::stable_partition(L.q, L.q + L.n, [](const TnPlan& q) { return q.vy == 4; });
-  int64_t off = 0, blocks = 0, maxmn = 0, wide_blocks = 0;
+  int64_t off = 0, blocks = 0, maxmn = 0;
   for (int i = 0; i < L.n; ++i) {
     TnPlan& q = L.q[i];
     q.rpc = rpc;
@@ -1106,20 +1077,12 @@ int tn_launch(const TnBatch& b, float* part, int64_t part_cap, hipStream_t st, c
     off += (int64_t)q.nchunks * mn;
     blocks += (int64_t)q.nchunks * std::max(q.tiles_m, 1) * q.tiles_n;
     maxmn = std::max(maxmn, mn);
-    if (q.vy == 4) wide_blocks = blocks;
   }
   if (off > part_cap) return fail(CHGNET_EWORKSPACE, "split-K partial buffer too small");
   if (blocks > 0x7fffffff) return fail(CHGNET_EINVAL, "tn: too many blocks");
   if (blocks > 0) {
-    // the wide and the 64 x 64 plans' launches are timed as one under `tag`
-    const bool in = std::string(tag) == "tn_in";
-    const unsigned wb = (unsigned)wide_blocks, nb = (unsigned)(blocks - wide_blocks);
-    KLAUNCH(st, tag, {
-      if (wb > 0 && in) k_tn<1, true><<<wb, 256, 0, st>>>(L, 0, part);
-      if (wb > 0 && !in) k_tn<0, true><<<wb, 256, 0, st>>>(L, 0, part);
-      if (nb > 0 && in) k_tn<1, false><<<nb, 256, 0, st>>>(L, (int)wb, part);
-      if (nb > 0 && !in) k_tn<0, false><<<nb, 256, 0, st>>>(L, (int)wb, part);
-    });
+    if (std::string(tag) == "tn_in") KLAUNCH(st, tag, k_tn<1><<<(unsigned)blocks, 256, 0, st>>>(L, part));
+    else KLAUNCH(st, tag, k_tn<0><<<(unsigned)blocks, 256, 0, st>>>(L, part));
     KLAUNCH(st, "k_tn_reduce", k_tn_reduce<<<dim3((unsigned)cdiv(maxmn, 64), L.n), 1024, 0, st>>>(L, part));
   }
   return CHGNET_OK;
