@@ -62,7 +62,7 @@ __device__ __forceinline__ void gemm_store4(const GemmProblem& P, int row, int c
       const float4 o = *dst;
       v[0] += o.x; v[1] += o.y; v[2] += o.z; v[3] += o.w;
     }
-    *dst = make_float4(v[0], v[1], v[2], v[3]);
+    if (P.C) *dst = make_float4(v[0], v[1], v[2], v[3]);
     if (P.act == ACT_SILU_OUT)
       *reinterpret_cast<float4*>(P.C2 + (int64_t)row * P.ldc2 + col) =
           make_float4(v[0] * sigm(v[0]), v[1] * sigm(v[1]), v[2] * sigm(v[2]), v[3] * sigm(v[3]));
@@ -81,7 +81,8 @@ __device__ __forceinline__ void gemm_store4(const GemmProblem& P, int row, int c
     if (P.bias) x += P.bias[cc];
     if (P.res) x += P.res[rr + cc];
     float* dst = P.C + cr + cc;
-    *dst = P.accumulate ? *dst + x : x;
+    if (P.accumulate) x += *dst;
+    if (P.C) *dst = x;
     if (P.act == ACT_SILU_OUT) P.C2[(int64_t)row * P.ldc2 + cc] = x * sigm(x);
   }
 }
@@ -176,8 +177,9 @@ __device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, c
 #pragma unroll
         for (int j = 0; j < 16; ++j) x[j] += m[j];
       }
+      if (P.C)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) d[(8 * (j >> 2) + (j & 3)) * P.ldc] = x[j];
+        for (int j = 0; j < 16; ++j) d[(8 * (j >> 2) + (j & 3)) * P.ldc] = x[j];
       if (P.act == ACT_SILU_OUT) {
         float* d2 = P.C2 + (int64_t)r0 * P.ldc2 + (4 * h * P.ldc2 + col);
 #pragma unroll
@@ -219,7 +221,7 @@ __device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, c
     for (int j = 0; j < 16; ++j) {
       const int row = r0 + 8 * (j >> 2) + 4 * h + (j & 3);
       if (row >= P.M) continue;
-      P.C[(int64_t)row_lane(cr, 8 * (j >> 2) + (j & 3), h) * P.ldc + col] = x[j];
+      if (P.C) P.C[(int64_t)row_lane(cr, 8 * (j >> 2) + (j & 3), h) * P.ldc + col] = x[j];
       if (P.act == ACT_SILU_OUT) P.C2[(int64_t)row * P.ldc2 + col] = x[j] * sigm(x[j]);
     }
   }
@@ -635,9 +637,9 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
   auto compute = [&](int b) {
     if (colsum) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int u = 0; u < VY; ++u) ysum[u] += yf[b][i][u];
+      for (int u = 0; u < VY; ++u)
+        ysum[u] += ((yf[b][0][u] + yf[b][1][u]) + (yf[b][2][u] + yf[b][3][u])) +
+                   ((yf[b][4][u] + yf[b][5][u]) + (yf[b][6][u] + yf[b][7][u]));
     }
     if (HASX) {
       Split8 xs[VX];

@@ -71,7 +71,7 @@ enum GemmAct { ACT_NONE = 0, ACT_SILU_OUT = 1, ACT_DSILU_MUL = 2 };
 
 // C[c_rows(r), c] (+)= sum_seg A[a_rows(r), a_col + k] B(k, c) + bias[c]
 //                      + res[res_rows(r), c]
-// ACT_SILU_OUT: also C2[r, c] = silu(value).
+// ACT_SILU_OUT: also C2[r, c] = silu(value) (C may then be null: not stored).
 // ACT_DSILU_MUL: value *= silu'(mul[r, c]) before bias/adds (backward of an
 //                activation; use without bias/adds/res).
 struct GemmProblem {

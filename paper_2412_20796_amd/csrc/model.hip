@@ -1611,7 +1611,7 @@ __device__ __forceinline__ void hd_epilogue(const v16f (&acc)[2], const float* _
       const int r = 8 * (j >> 2) + 4 * h + (j & 3);
       const float hv = acc[ct][j] + bc;
       const float av = hv * sigm(hv);
-      if (row0 + r < rows) {
+      if (hout && row0 + r < rows) {  // (hout: uniform)
         hout[(int64_t)(row0 + r) * 64 + c] = hv;
         aout[(int64_t)(row0 + r) * 64 + c] = av;
       }
@@ -1995,7 +1995,8 @@ __global__ void __launch_bounds__(256) k_struct_heads(int S, const int* __restri
   for (int k = 0; k < 10; ++k) acc[k] = 0.0;
   for (int i = atom_ptr[s] + threadIdx.x; i < atom_ptr[s + 1]; i += 256) {
     acc[0] += oE[i];
-    for (int k = 0; k < 9; ++k) acc[1 + k] += oS[(int64_t)i * 9 + k];
+    if (oS)
+      for (int k = 0; k < 9; ++k) acc[1 + k] += oS[(int64_t)i * 9 + k];
   }
   for (int k = 0; k < 10; ++k) red[k][threadIdx.x] = acc[k];
   __syncthreads();
@@ -2006,6 +2007,7 @@ __global__ void __launch_bounds__(256) k_struct_heads(int S, const int* __restri
   }
   if (threadIdx.x == 0) {
     energy[s] = (float)red[0][0];
+    if (!oS) return;
     double U[9], vol;
     lattice_units(lattice + 9 * s, U, vol);
     for (int x = 0; x < 3; ++x)
@@ -2663,6 +2665,12 @@ struct Ctx {
   char* ws;        // workspace, and the bytes the activations use of it
   size_t ws_bytes, ws_used;
   bool save_z = true;  // keep the gate pre-activations for a backward pass
+  // Modules whose result reaches the outputs. With the conservative readout
+  // only the energy does, which reads v^T: the last layer's bond conv feeds
+  // e^T alone (the force head's input), and the angle update before it feeds
+  // that bond conv alone; neither is run, and their weights' gradients are 0.
+  bool has_bond_conv(int t) const { return !(hp->conservative && t == dm.T - 1); }
+  bool has_angle(int t) const { return La.layer[t].has_angle && !(hp->conservative && t >= dm.T - 2); }
 };
 
 int run_gemms(const Ctx& c, const std::vector<GemmProblem>& ps, hipStream_t st, const char* tag) {
@@ -3021,6 +3029,11 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
   const chgnet_batch& bt = *c.batch;
   const int D = m.D;
   const int64_t N = m.N, S = m.S, E = m.E, B = m.B, A = m.A;
+  const bool cons = c.hp->conservative != 0;
+  // without a backward pass one copy of the edge features is enough: every
+  // reader of e^t in a layer comes before the update of its bond rows
+  if (!c.save_z)
+    for (int t = 1; t <= m.T; ++t) a.e[t] = a.e[0];
 
   // geometry, bases and v0 (Eq. 2)
   {
@@ -3059,7 +3072,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
   const bool seq = c.hp->sequential != 0;
   for (int t = 0; t < m.T; ++t) {
     const LayerOffsets& lo = L.layer[t];
-    const bool ang = lo.has_angle;
+    const bool ang = c.has_angle(t), bond = c.has_bond_conv(t);
     const float* Wav = P + lo.av.W;
     const float* Wbe = P + lo.be.W;
     const float* Wan = P + lo.an.W;
@@ -3068,7 +3081,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     auto proj_atoms = [&](int k0, int k1, const float* vin) -> int {
       std::vector<GemmProblem> ps;
       for (int k = k0; k < k1; ++k) {
-        if (k == 3 && !ang) break;
+        if ((k == 2 && !bond) || (k == 3 && !ang)) break;
         const float* W = k == 0 ? Wav : k == 1 ? Wav + D * 2 * D : k == 2 ? Wbe : Wan;
         GemmProblem p = gp(N, 2 * D, a.Xa[t] + k * 2 * D, 8 * D);
         seg(p, vin, D, 0, D, W, 2 * D, 0);
@@ -3081,7 +3094,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     auto proj_bonds = [&](int mask, const float* ein) -> int {
       std::vector<GemmProblem> ps;
       for (int k = 0; k < 4; ++k) {
-        if (!((mask >> k) & 1) || ((k & 1) && !ang)) continue;
+        if (!((mask >> k) & 1) || !(k & 1 ? ang : bond)) continue;
         const float* W = (k & 1 ? Wan : Wbe) + (k < 2 ? 1 : 2) * D * 2 * D;
         GemmProblem p = gp(B, 2 * D, a.Xb[t] + k * 2 * D, 8 * D);
         p.a_rows = g.bond_edge;
@@ -3106,6 +3119,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     // GatedMLPs: bit 0 atom conv, bit 1 bond conv, bit 2 angle update
     auto gates = [&](int which) -> int {
       if (!ang) which &= 3;
+      if (!bond) which &= 5;
       // pre-activations formed inside the gate kernel; z kept for a backward
       // pass unless the caller asked for none
       GateMmJobs J{};
@@ -3114,7 +3128,8 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
       if (which & 1) {
         J.j[J.n] = mm_job(D, FWD_ATOM, E, a.e[t], Wx_av, P + lo.av.b, ad_av, ln_ptrs(P, lo.av), a.ea, nullptr, a.msg,
                           zv, 2 * D);
-        J.j[J.n++].xcopy = a.e[t + 1];  // e^{t+1} = e^t outside G^b (the bond rows are updated after)
+        // e^{t+1} = e^t outside G^b (the bond rows are updated after)
+        J.j[J.n++].xcopy = bond && a.e[t + 1] != a.e[t] ? a.e[t + 1] : nullptr;
       }
       if (which & 2)
         J.j[J.n++] = mm_job(D, FWD_BOND, A, a.a[t], Wx_be, P + lo.be.b, ad_be, ln_ptrs(P, lo.be), a.eb, a.ang_b2,
@@ -3132,6 +3147,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     // rows of a consumer wavefront of the gates, whose runs it has summed
     const int run_rows = D == 64 ? Lanes<64, kMmCpl>::RPW : Lanes<128, kMmCpl>::RPW;
     auto messages = [&](int which) -> int {
+      if (!bond) which &= 1;
       SegJobs J{};
       if (which & 1) {
         SegJob& q = J.j[J.n++];
@@ -3163,6 +3179,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     // updates: v' = v + m Wo + bo; e' = e (+ mu Wo + bo on bonds)
     auto updates = [&](int which) -> int {
       if (fuse_upd) return CHGNET_OK;  // done by the message launch (and the copy by the atom-conv gate)
+      if (!bond) which &= 1;
       std::vector<GemmProblem> ps;
       if (which & 1) {
         GemmProblem p = gp(N, D, a.v[t + 1], D);
@@ -3221,8 +3238,11 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     Lay ls[3] = {{vT, N, &hE, a.hE1, a.aE1, a.hE2, a.aE2, a.oE},
                  {vT, N, &hS, a.hS1, a.aS1, a.hS2, a.aS2, a.oS},
                  {eT, E, &hF, a.hF1, a.aF1, a.hF2, a.aF2, a.oF}};
-    for (auto& l : ls) {
-      GemmProblem p = gp(l.M, D, l.h1, D);
+    // (conservative: the energy head only; h is kept for a backward pass)
+    const int nl = cons ? 1 : 3;
+    for (int k = 0; k < nl; ++k) {
+      auto& l = ls[k];
+      GemmProblem p = gp(l.M, D, c.save_z ? l.h1 : nullptr, D);
       seg(p, l.in, D, 0, D, P + l.h->W1, D, 0);
       p.bias = P + l.h->b1;
       p.act = ACT_SILU_OUT;
@@ -3232,8 +3252,9 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     }
     CHG_TRY(run_gemms(c, ps, st, "gemm_head1"));
     ps.clear();
-    for (auto& l : ls) {
-      GemmProblem p = gp(l.M, D, l.h2, D);
+    for (int k = 0; k < nl; ++k) {
+      auto& l = ls[k];
+      GemmProblem p = gp(l.M, D, c.save_z ? l.h2 : nullptr, D);
       seg(p, l.a1, D, 0, D, P + l.h->W2, D, 0);
       p.bias = P + l.h->b2;
       p.act = ACT_SILU_OUT;
@@ -3243,7 +3264,8 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     }
     CHG_TRY(run_gemms(c, ps, st, "gemm_head2"));
     ps.clear();
-    for (auto& l : ls) {
+    for (int k = 0; k < nl; ++k) {
+      auto& l = ls[k];
       GemmProblem p = gp(l.M, l.h->out, l.o, l.h->out);
       seg(p, l.a2, D, 0, D, P + l.h->W3, l.h->out, 0);
       p.bias = P + l.h->b3;
@@ -3258,19 +3280,23 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     int tiles = 0;
     auto add = [&](const float* x, int64_t rows, const HeadOffsets& h, float* h1, float* a1, float* h2, float* a2, float* o) {
       if (rows <= 0) return;
+      if (!c.save_z) h1 = a1 = h2 = a2 = nullptr;  // kept for a backward pass only
       HeadJob& q = J.j[J.n++];
       q = HeadJob{(int)rows, tiles, h.out, x, P + h.W1, P + h.b1, P + h.W2, P + h.b2, P + h.W3, P + h.b3, h1, a1, h2, a2, o};
       tiles += (int)cdiv(rows, kHdRows);
     };
-    add(a.e[m.T], E, hF, a.hF1, a.aF1, a.hF2, a.aF2, a.oF);
+    if (!cons) add(a.e[m.T], E, hF, a.hF1, a.aF1, a.hF2, a.aF2, a.oF);
     add(a.v[m.T], N, hE, a.hE1, a.aE1, a.hE2, a.aE2, a.oE);
-    add(a.v[m.T], N, hS, a.hS1, a.aS1, a.hS2, a.aS2, a.oS);
+    if (!cons) add(a.v[m.T], N, hS, a.hS1, a.aS1, a.hS2, a.aS2, a.oS);
     J.ntiles = tiles;
     const int blocks = (int)std::min<int64_t>(cdiv(tiles, 4), 512);
     KLAUNCH(st, "k_head_mlp", k_head_mlp<<<blocks, 256, 0, st>>>(J));
   }
-  KLAUNCH(st, "k_struct_heads", k_struct_heads<<<(unsigned)S, 256, 0, st>>>((int)S, bt.atom_ptr, bt.lattice, a.oE, a.oS, energy, stress));
-  KLAUNCH(st, "k_forces", k_forces<<<(unsigned)cdiv(N, 4), 256, 0, st>>>((int)N, g.edge_ptr, g.edge_rev, a.oF, a.edge_xhat, forces));
+  // (conservative: forces and stress come from the energy's derivatives)
+  KLAUNCH(st, "k_struct_heads", k_struct_heads<<<(unsigned)S, 256, 0, st>>>((int)S, bt.atom_ptr, bt.lattice, a.oE,
+                                                                              cons ? nullptr : a.oS, energy, stress));
+  if (!cons)
+    KLAUNCH(st, "k_forces", k_forces<<<(unsigned)cdiv(N, 4), 256, 0, st>>>((int)N, g.edge_ptr, g.edge_rev, a.oF, a.edge_xhat, forces));
   if (c.hp->magmom)
     KLAUNCH(st, "k_magmom", k_magmom<<<(unsigned)cdiv(N, 4), 256, 0, st>>>((int)N, D, a.v[m.T], P + L.M_W, P + L.M_b,
                                                                             a.oM, magmom));
@@ -3317,8 +3343,9 @@ int side_fork(SideStream& ss, hipStream_t st, hipEvent_t e) {
   return CHGNET_OK;
 }
 
-// G == nullptr: input gradients only (no weight gradients); dft_out != nullptr:
-// also dE/d FT = da^0 W_th^T [A,K] for the conservative readout.
+// G == nullptr with dft_out: the conservative readout's pass, the input
+// gradients of the energy (no weight gradients; dE, dF, dS not read), and also
+// dE/d FT = da^0 W_th^T [A,K].
 int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, const float* dF, const float* dS,
                   const float* dM, float* G, hipStream_t st, float* dft_out = nullptr) {
   const Dims& m = c.dm;
@@ -3349,9 +3376,11 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
   }
   SideStream& ss = wg ? *ssp : no_side;
 
-  // heads
-  KLAUNCH(st, "k_seed_atoms", k_seed_atoms<<<(unsigned)cdiv(N, 256), 256, 0, st>>>((int)N, a.atom_struct, bt.lattice, dE, dS, a.doE, a.doS));
-  if (E > 0) {
+  // heads (conservative: dE/dv through the energy head alone, its upstream one)
+  const bool cons = dft_out != nullptr;
+  if (cons) CHG_TRY(fill(a.doE, N, 1.f, st));
+  if (!cons) KLAUNCH(st, "k_seed_atoms", k_seed_atoms<<<(unsigned)cdiv(N, 256), 256, 0, st>>>((int)N, a.atom_struct, bt.lattice, dE, dS, a.doE, a.doS));
+  if (!cons && E > 0) {
     KLAUNCH(st, "k_seed_edges", k_seed_edges<<<(unsigned)cdiv(E, 256), 256, 0, st>>>((int)E, a.edge_src, dF, a.edge_xhat, a.dn));
     KLAUNCH(st, "k_seed_edges2", k_seed_edges2<<<(unsigned)cdiv(E, 256), 256, 0, st>>>((int)E, g.edge_rev, a.dn, a.doF));
   }
@@ -3371,7 +3400,9 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
                  {a.v[m.T], N, &hS, &Lg.head[2], a.hS1, a.aS1, a.hS2, a.aS2, a.doS, a.dh2S, a.dh1ES, D, 2 * D},
                  {a.e[m.T], E, &hF, &Lg.head[1], a.hF1, a.aF1, a.hF2, a.aF2, a.doF, a.dh2F, a.dh1F, 0, D}};
     std::vector<GemmProblem> ps;
-    for (auto& l : ls) {
+    const int nl = cons ? 1 : 3;
+    for (int k = 0; k < nl; ++k) {
+      auto& l = ls[k];
       GemmProblem p = gp(l.M, D, l.dh2, D);
       seg(p, l.dout, l.h->out, 0, l.h->out, P + l.h->W3, l.h->out, 1);
       p.act = ACT_DSILU_MUL;
@@ -3381,7 +3412,8 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
     }
     CHG_TRY(run_gemms(c, ps, st, "gemm_head_bwd2"));
     ps.clear();
-    for (auto& l : ls) {
+    for (int k = 0; k < nl; ++k) {
+      auto& l = ls[k];
       GemmProblem p = gp(l.M, D, l.dh1base + l.dh1col, l.ld1);
       seg(p, l.dh2, D, 0, D, P + l.h->W2, D, 1);
       p.act = ACT_DSILU_MUL;
@@ -3394,11 +3426,13 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
     {
       GemmProblem p = gp(N, D, a.dv[cur], D);
       seg(p, a.dh1ES, 2 * D, 0, D, P + hE.W1, D, 1);
-      seg(p, a.dh1ES, 2 * D, D, D, P + hS.W1, D, 1);
+      if (!cons) seg(p, a.dh1ES, 2 * D, D, D, P + hS.W1, D, 1);
       ps.push_back(p);
-      p = gp(E, D, a.de[ecur], D);
-      seg(p, a.dh1F, D, 0, D, P + hF.W1, D, 1);
-      ps.push_back(p);
+      if (!cons) {
+        p = gp(E, D, a.de[ecur], D);
+        seg(p, a.dh1F, D, 0, D, P + hF.W1, D, 1);
+        ps.push_back(p);
+      }
       CHG_TRY(run_gemms(c, ps, st, "gemm_head_bwd0"));
     }
     const bool mag = c.hp->magmom && dM;
@@ -3438,7 +3472,11 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
   for (int t = m.T - 1; t >= 0; --t) {
     const LayerOffsets& lo = L.layer[t];
     const LayerOffsets& lg = Lg.layer[t];
-    const bool ang = lo.has_angle;
+    const bool ang = c.has_angle(t), bond = c.has_bond_conv(t);
+    // the first layers of the backward that have each: they start the sums
+    // d e^b and d e^a; no gradient reaches e^T of a conservative readout
+    const bool deb_acc = t < m.T - 1 && c.has_bond_conv(t + 1);
+    const float* de_res = cons && t == m.T - 1 ? nullptr : a.de[ecur];
     const int W4 = ang ? 4 * D : 2 * D;
     a.dzv = a.dzv_pp[t & 1];
     a.dzae = a.dzae_pp[t & 1];
@@ -3492,10 +3530,10 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
                          a.dzv, 2 * D);
         q.g[0].aux_acc = t < m.T - 1;  // the first layer of the backward starts d e^a
         q.W[0] = Wav + 2 * D * 2 * D;
-        q.res = a.de[ecur];
+        q.res = de_res;
         q.dx = a.de[enx];
       }
-      {
+      if (bond) {
         GateBwdMmJob& q = J.j[J.n++];
         q.rows = (int)A;
         q.ngates = ang ? 2 : 1;
@@ -3525,7 +3563,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       const int cpl = ncols / 64;
       const float* dz = a.dzae + col0;
       float* dz12 = a.DZ12 + col0;
-      const int acc = t < m.T - 1;
+      const int acc = deb_acc;
 #define BOND_REDUCE(CPL, TPL, DEB)                                                                                \
   KLAUNCH(st, "k_bond_bwd_reduce", k_bond_bwd_reduce<CPL, TPL, DEB><<<nb, 256, 0, st>>>((int)B, D, a.bond_src,      \
                                      g.bond_ptr, g.angle_ptr, dz, a.t2, a.dmu, a.ssum[t], dz12, a.deb, acc))
@@ -3559,12 +3597,12 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
     };
     SegJobs sj{};
     if (!seq) {
-      CHG_TRY(out_bwd(a.dv[cur], true, true));
-      CHG_TRY(fused ? gates_mm() : gates(7));
-      CHG_TRY(bond_reduce(0, W4, true));
+      CHG_TRY(out_bwd(a.dv[cur], true, bond));
+      CHG_TRY(gates_mm());
+      if (bond) CHG_TRY(bond_reduce(0, W4, true));
       sj.j[sj.n++] = seg_job(N, g.edge_ptr, nullptr, a.dzv, 2 * D, 2 * D, a.AT, 8 * D);
       sj.j[sj.n++] = seg_job(N, g.edge_ptr, g.edge_rev, a.dzv, 2 * D, 2 * D, a.AT + 2 * D, 8 * D);
-      sj.j[sj.n++] = seg_job(N, g.bond_ptr, nullptr, a.DZ12, 8 * D, W4, a.AT + 4 * D, 8 * D);
+      if (bond) sj.j[sj.n++] = seg_job(N, g.bond_ptr, nullptr, a.DZ12, 8 * D, W4, a.AT + 4 * D, 8 * D);
       CHG_TRY(segsum_launch(sj, 4, st));
     } else {
       // Eq. (10), in reverse: the angle update read e^{t+1} (its bond terms
@@ -3583,19 +3621,23 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
         CHG_TRY(run_gemms(c, ps, st, "gemm_bond_bwd"));
         ps.clear();
       }
-      CHG_TRY(out_bwd(nullptr, false, true));
-      CHG_TRY(gates(2));
-      CHG_TRY(bond_reduce(0, 2 * D, true));
-      sj.j[sj.n++] = seg_job(N, g.bond_ptr, nullptr, a.DZ12, 8 * D, W4, a.AT + 4 * D, 8 * D);
-      CHG_TRY(segsum_launch(sj, 4, st));
-      GemmProblem p = gp(N, D, a.dvf, D);
-      seg(p, a.AT, 8 * D, 4 * D, 2 * D, Wbe, 2 * D, 1);
-      if (ang) seg(p, a.AT, 8 * D, 6 * D, 2 * D, Wan, 2 * D, 1);
-      p.res = a.dv[cur];
-      p.res_ld = D;
-      ps.push_back(p);
-      CHG_TRY(run_gemms(c, ps, st, "gemm_in_bwd"));
-      ps.clear();
+      if (bond) {
+        CHG_TRY(out_bwd(nullptr, false, true));
+        CHG_TRY(gates(2));
+        CHG_TRY(bond_reduce(0, 2 * D, true));
+        sj.j[sj.n++] = seg_job(N, g.bond_ptr, nullptr, a.DZ12, 8 * D, W4, a.AT + 4 * D, 8 * D);
+        CHG_TRY(segsum_launch(sj, 4, st));
+        GemmProblem p = gp(N, D, a.dvf, D);
+        seg(p, a.AT, 8 * D, 4 * D, 2 * D, Wbe, 2 * D, 1);
+        if (ang) seg(p, a.AT, 8 * D, 6 * D, 2 * D, Wan, 2 * D, 1);
+        p.res = a.dv[cur];
+        p.res_ld = D;
+        ps.push_back(p);
+        CHG_TRY(run_gemms(c, ps, st, "gemm_in_bwd"));
+        ps.clear();
+      } else {
+        a.dvf = a.dv[cur];  // nothing but the atom conv wrote or read v^{t+1} here
+      }
       CHG_TRY(out_bwd(a.dvf, true, false));
       CHG_TRY(gates(1));
       sj = SegJobs{};
@@ -3661,7 +3703,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
       seg(p, a.AT, 8 * D, 0, 2 * D, Wav, 2 * D, 1);
       seg(p, a.AT, 8 * D, 2 * D, 2 * D, Wav + D * 2 * D, 2 * D, 1);
       if (!seq) {
-        seg(p, a.AT, 8 * D, 4 * D, 2 * D, Wbe, 2 * D, 1);
+        if (bond) seg(p, a.AT, 8 * D, 4 * D, 2 * D, Wbe, 2 * D, 1);
         if (ang) seg(p, a.AT, 8 * D, 6 * D, 2 * D, Wan, 2 * D, 1);
       }
       p.res = dvo;
@@ -3671,17 +3713,19 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
     if (!fused) {
       GemmProblem p = gp(E, D, a.de[enx], D);
       seg(p, a.dzv, 2 * D, 0, 2 * D, Wav + 2 * D * 2 * D, 2 * D, 1);
-      p.res = a.de[ecur];
+      p.res = de_res;
       p.res_ld = D;
       ps.push_back(p);
-      p = gp(A, D, a.da[nx], D);
-      seg(p, a.dzae, 4 * D, 0, 2 * D, Wbe + 3 * D * 2 * D, 2 * D, 1);
-      if (ang) {
-        seg(p, a.dzae, 4 * D, 2 * D, 2 * D, Wan + 3 * D * 2 * D, 2 * D, 1);
-        p.res = a.da[cur];
-        p.res_ld = D;
+      if (bond) {
+        p = gp(A, D, a.da[nx], D);
+        seg(p, a.dzae, 4 * D, 0, 2 * D, Wbe + 3 * D * 2 * D, 2 * D, 1);
+        if (ang) {
+          seg(p, a.dzae, 4 * D, 2 * D, 2 * D, Wan + 3 * D * 2 * D, 2 * D, 1);
+          p.res = a.da[cur];
+          p.res_ld = D;
+        }
+        ps.push_back(p);
       }
-      ps.push_back(p);
     }
     {
       // fused: the atom rows' product shares the launch of the bond rows'
@@ -3690,7 +3734,7 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
         CHG_TRY(run_gemms(c, ps, st, "gemm_in_bwd"));
         ps.clear();
       }
-      GemmProblem p = gp(B, D, a.de[enx], D);
+      GemmProblem p = gp(bond ? B : 0, D, a.de[enx], D);
       p.c_rows = g.bond_edge;
       p.accumulate = 1;
       seg(p, a.DZ12, 8 * D, 0, 2 * D, Wbe + D * 2 * D, 2 * D, 1);
@@ -3717,6 +3761,11 @@ int backward_impl(Ctx& c, const float* Pflat, bool repack, const float* dE, cons
     ecur = enx;
   }
 
+  // a conservative readout of one layer does not see bonds and angles
+  if (cons && m.T == 1) {
+    CHG_TRY(fill(a.deb, B * D, 0.f, st));
+    CHG_TRY(fill(a.da[cur], A * D, 0.f, st));
+  }
   // embeddings
   if (wg) KLAUNCH(st, "k_embed_bwd_Z", k_embed_bwd_Z<<<94, 64 * kEmbZWaves, 0, st>>>((int)N, D, bt.Z, a.dv[cur], G + Lg.W_Z));
   {
@@ -3787,10 +3836,7 @@ int conservative_impl(Ctx& c, float* forces, float* stress, hipStream_t st) {
   const chgnet_graph& g = *c.graph;
   const chgnet_batch& bt = *c.batch;
   const int64_t N = m.N, S = m.S, E = m.E, B = m.B, A = m.A;
-  CHG_TRY(fill(a.dE, S, 1.f, st));
-  CHG_TRY(fill(a.dF, 3 * N, 0.f, st));
-  CHG_TRY(fill(a.dS, 9 * S, 0.f, st));
-  CHG_TRY(backward_impl(c, nullptr, false, a.dE, a.dF, a.dS, nullptr, nullptr, st, a.dft));
+  CHG_TRY(backward_impl(c, nullptr, false, nullptr, nullptr, nullptr, nullptr, nullptr, st, a.dft));
   const int p = c.hp->envelope_p;
   if (E > 0)
     KLAUNCH(st, "k_cons", k_cons_edges<<<(unsigned)cdiv(E, 256), 256, 0, st>>>((int)E, a.edge_len, a.edge_xhat, a.drbf_a,
