@@ -392,6 +392,12 @@ __device__ __forceinline__ void load_z(const float* __restrict__ z, int ldz, int
 // Columns per lane of the row-layout backward gate.
 constexpr int kBwdCpl = 8;
 
+// From this many bonds on the update's output linear is a launch of its own
+// at d = 64 too: in the message launch a wavefront multiplies its row lane by
+// lane, 64 broadcasts and 16 KB of weights a row, which on 36,000 bonds took
+// 68 us against 37 + 21 us apart; on 5,000 bonds the launch costs more than it
+// saves.
+constexpr int kFuseUpdBonds = 8192;
 enum GateFwdMode { FWD_ATOM = 0, FWD_BOND = 1, FWD_ANGLE = 2 };
 
 // Forward gate modes:
@@ -839,9 +845,9 @@ __global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs
         if (jb.mode == FWD_ATOM) gate_mm_row<D, FWD_ATOM>(jb, row, lr, Z, in, lnr);
         else if (jb.mode == FWD_BOND) gate_mm_row<D, FWD_BOND>(jb, row, lr, Z, in, lnr);
         else gate_mm_row<D, FWD_ANGLE>(jb, row, lr, Z, in, lnr);
-        // (issued before the rows are computed, into a second set of
-        // registers, the gathers made the launch 12 % slower at d = 64 and
-        // spill at d = 128)
+        // (issued before the rows are computed, or as soon as this tile's are
+        // added to z, the gathers made the launch 12-14 % slower at d = 64
+        // and spill at d = 128)
         if (i < nt) {
           gather(i);
           if (i + 1 < nt) index(i + 1);
@@ -3143,7 +3149,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     // angles (b, b2) of eb_b2 * phi_e
     // at d = 64 the same launch applies the output linears of the updates
     // (v' = v + m Wo + bo; e'_b = e_b + mu Wo + bo): a wavefront holds a row
-    const bool fuse_upd = D == 64;
+    const bool fuse_upd = D == 64 && B < kFuseUpdBonds;
     // rows of a consumer wavefront of the gates, whose runs it has summed
     const int run_rows = D == 64 ? Lanes<64, kMmCpl>::RPW : Lanes<128, kMmCpl>::RPW;
     auto messages = [&](int which) -> int {
