@@ -392,13 +392,12 @@ def mandatory_cost(tag, z):
     return None, None
 
 
-# rocprofv3 kernel symbols of each launch tag that has an algorithmic cost
-# (a tag's call may launch several kernels: tn_in launches its 64 x 128 and
-# its 64 x 64 wave-tile plans separately)
+# rocprofv3 kernel symbols of each launch tag that has an algorithmic cost (a
+# tag may stand for several kernels: the forward gate's tiles at d = 64)
 def tag_symbols(tag, d):
     return {
         "tn_in": ["k_tn<1>"],
-        "k_gate_fwd": ["k_gate_fwd_mm<%d>" % d],
+        "k_gate_fwd": ["k_gate_fwd_mm<64, 64>", "k_gate_fwd_mm<64, 96>"] if d == 64 else ["k_gate_fwd_mm<128, 32>"],
         "k_gate_bwd": ["k_gate_bwd_mm" if d == 64 else "k_gate_bwd_mm128"],
     }.get(tag)
 
@@ -435,10 +434,10 @@ def measured_traffic(workload, tag):
     data = json.loads(text[start + 7:text.index("```", start + 7)])
     if data.get("source_sha256") != source_digest():
         return None
-    # each kernel of the tag is launched once per call (those of a plan kind
-    # the workload has no product for are absent)
+    # a call launches one of the tag's kernels: mean over their launches
     ks = [data["kernels"][s] for s in syms if s in data["kernels"]]
-    return sum(k["fetch_bytes"] + k["write_bytes"] for k in ks) if ks else None
+    n = sum(k["dispatches"] for k in ks)
+    return sum((k["fetch_bytes"] + k["write_bytes"]) * k["dispatches"] for k in ks) / n if n else None
 
 
 def traffic_summary(fetch_csv, write_csv, workload, command):

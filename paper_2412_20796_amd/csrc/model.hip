@@ -412,9 +412,9 @@ enum GateFwdMode { FWD_ATOM = 0, FWD_BOND = 1, FWD_ANGLE = 2 };
 // tile is staged in LDS; each producer forms its rows x 32 slice of z with
 // 32x32x2 MFMAs (lane half h supplies k = 16h + i in step i of each 32-wide
 // k block) and writes it to the z tile; the consumers' row-layout gate then
-// reads z from LDS. d = 64: 64-row tiles, 4 producer and 8 consumer
-// wavefronts; d = 128: 32-row tiles, 8 producers (256 columns) and 8
-// consumers, 16 wavefronts of at most 128 VGPRs.
+// reads z from LDS. d = 64: 4 producers and 8 consumers on 64-row tiles, or 12
+// on 96-row tiles (kMmTallRows); d = 128: 32-row tiles, 8 producers (256
+// columns) and 8 consumers. 16 wavefronts have at most 128 VGPRs each.
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 struct GateMmJob {
@@ -438,6 +438,15 @@ struct GateMmJobs {
 };
 
 constexpr int kMmCpl = 8;
+
+// Rows of a d = 64 forward launch from which its tiles have 96 rows. The
+// launch waits for the consumers' gathers (a third of the matrix cores' time
+// and 2.3 TB/s of HBM on 4,096 atoms), so more of them in flight help: 12
+// consumers of 128 VGPRs instead of 8 of 168 took it from 248 to 210 us there
+// and from 81 to 67 us on 258,000 rows with z kept. With few tiles a block the
+// longer tile shows instead: inference of 1,600 atoms (250,000 rows) is 4 %
+// faster with 96 rows, of 800 the same, of 400 and fewer up to 2 % slower.
+constexpr int kMmTallRows = 131072;
 
 // Deal of the tiles of up to three jobs to the blocks of a launch. Blocks are
 // dealt to the 8 XCDs in turn; XCD x takes the x-th eighth of every job's
@@ -497,26 +506,23 @@ inline int xcd_grid(const int* ntiles, int n) {
 // launch), while the producers, with a tile of slack, lose nothing.
 constexpr int kConsumerPrio = 2;
 
-template <int D>
+template <int D, int R>
 struct MmCfg {
-  static constexpr int Rows = D == 64 ? 64 : 32;  // rows per tile
-  static constexpr int Prod = 2 * D / 32;         // producer waves: 32 z columns each
-  static constexpr int Cons = 8;                  // consumer waves
+  static constexpr int Rows = R;                          // rows per tile
+  static constexpr int Prod = 2 * D / 32;                 // producer waves: 32 z columns each
+  static constexpr int Cons = R / Lanes<D, kMmCpl>::RPW;  // consumer waves: one pass per tile
   static constexpr int Threads = 64 * (Prod + Cons);
   static constexpr int Xld = D + 4;
   static constexpr int Zld = 2 * D + 4;
   static constexpr int KB = D / 32;    // 32-deep k blocks
   static constexpr int RS = Rows / 32;  // 32-row subtiles
-  // x tile loads: every producer thread moves F floats of one row
-  static constexpr int F = Rows * D / (64 * Prod);
-  static constexpr int TPR = D / F;  // threads per x row
-  static_assert(Cons * Lanes<D, kMmCpl>::RPW == Rows, "one consumer pass per tile");
-  static_assert(F % 4 == 0 && Rows * TPR == 64 * Prod, "x tile split");
+  // x tile loads: float4s of a producer thread
+  static constexpr int V = R * D / 4 / (64 * Prod);
+  static_assert(R % 32 == 0 && V * 4 * 64 * Prod == R * D, "x tile split");
 };
-// kept for the backward gate kernel (d = 64 only)
-constexpr int kMmRows = MmCfg<64>::Rows;
-constexpr int kMmProducers = MmCfg<64>::Prod, kMmConsumers = MmCfg<64>::Cons;
-constexpr int kMmThreads = MmCfg<64>::Threads;
+// tiles and wavefronts of the backward gate kernel at d = 64
+constexpr int kMmRows = 64, kMmProducers = 4, kMmConsumers = 8;
+constexpr int kMmThreads = 64 * (kMmProducers + kMmConsumers);
 
 // the wavefront's LDS writes are visible to all its lanes
 __device__ __forceinline__ void wave_lds_sync() {
@@ -589,7 +595,7 @@ __device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr,
     // odd rows of the z tile hold the two 32-column halves of each 64-column
     // block swapped (written so by the producers): the two rows of a read
     // phase fall in different banks
-    const float* zr = Zs + lr * MmCfg<D>::Zld;
+    const float* zr = Zs + lr * (2 * D + 4);
     const int sw = (lr & 1) * 32;
 #pragma unroll
     for (int q = 0; q < CPL / 4; ++q) {
@@ -627,7 +633,7 @@ __device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr,
     return;
   }
   {
-    float* zr = Zs + lr * MmCfg<D>::Zld;
+    float* zr = Zs + lr * (2 * D + 4);
     const int sw = (lr & 1) * 32;
 #pragma unroll
     for (int q = 0; q < CPL / 4; ++q)
@@ -642,7 +648,7 @@ __device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr,
   for (int c = 0; c < CW; ++c) acc[c] = 0.f;
 #pragma unroll
   for (int r = 0; r < L::RPW; ++r) {
-    const float* zr = Zs + (lr0 + r) * MmCfg<D>::Zld;
+    const float* zr = Zs + (lr0 + r) * (2 * D + 4);
 #pragma unroll
     for (int c = 0; c < CW; ++c) acc[c] += zr[(64 * c + lane) ^ (((lr0 + r) & 1) * 32)];
     if ((ends >> (r * L::LPR)) & 1) {  // uniform over the wavefront
@@ -662,95 +668,94 @@ __device__ __forceinline__ void gate_mm_row(const GateMmJob& J, int row, int lr,
 // hands the buffers over. Producers and consumers run separate loops with
 // the same number of block barriers, so each keeps only its own state.
 
-// Producer pieces (threads 0 .. 64 Prod - 1). x tile loads: thread -> row
-// tid / TPR, F columns at F (tid % TPR); rows past `rows` read as zero.
-template <int D>
-__device__ __forceinline__ void mm_fetch_x(const float* __restrict__ x, int rows, int row0,
-                                           float4 (&v)[MmCfg<D>::F / 4]) {
-  using C = MmCfg<D>;
-  const int tid = threadIdx.x, row = row0 + tid / C::TPR, xc = C::F * (tid % C::TPR);
+// Producer pieces (threads 0 .. 64 Prod - 1). x tile loads: float4 q of a
+// thread is the tile's float4 tid + 64 Prod q, so that a wavefront reads 1 KB
+// in a row; rows past `rows` read as zero.
+template <int D, class C>
+__device__ __forceinline__ void mm_fetch_x(const float* __restrict__ x, int rows, int row0, float4 (&v)[C::V]) {
 #pragma unroll
-  for (int q = 0; q < C::F / 4; ++q) v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (row < rows) {
-    const float* p = x + (int64_t)row * D + xc;
-#pragma unroll
-    for (int q = 0; q < C::F / 4; ++q) v[q] = *reinterpret_cast<const float4*>(p + 4 * q);
+  for (int q = 0; q < C::V; ++q) {
+    const int c = threadIdx.x + 64 * C::Prod * q, row = row0 + c / (D / 4), xc = 4 * (c % (D / 4));
+    v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (row < rows) v[q] = *reinterpret_cast<const float4*>(x + (int64_t)row * D + xc);
   }
 }
-template <int D>
-__device__ __forceinline__ void mm_store_x(float* X, const float4 (&v)[MmCfg<D>::F / 4]) {
-  using C = MmCfg<D>;
-  const int tid = threadIdx.x, xr = tid / C::TPR, xc = C::F * (tid % C::TPR);
+template <int D, class C>
+__device__ __forceinline__ void mm_store_x(float* X, const float4 (&v)[C::V]) {
 #pragma unroll
-  for (int q = 0; q < C::F / 4; ++q) *reinterpret_cast<float4*>(&X[xr * C::Xld + xc + 4 * q]) = v[q];
+  for (int q = 0; q < C::V; ++q) {
+    const int c = threadIdx.x + 64 * C::Prod * q;
+    *reinterpret_cast<float4*>(&X[c / (D / 4) * C::Xld + 4 * (c % (D / 4))]) = v[q];
+  }
 }
 // the same x tile piece to global memory (rows past `rows` are skipped)
-template <int D>
-__device__ __forceinline__ void mm_copy_x(float* __restrict__ dst, int rows, int row0,
-                                          const float4 (&v)[MmCfg<D>::F / 4]) {
-  using C = MmCfg<D>;
-  const int tid = threadIdx.x, row = row0 + tid / C::TPR, xc = C::F * (tid % C::TPR);
-  if (row < rows) {
-    float* p = dst + (int64_t)row * D + xc;
+template <int D, class C>
+__device__ __forceinline__ void mm_copy_x(float* __restrict__ dst, int rows, int row0, const float4 (&v)[C::V]) {
 #pragma unroll
-    for (int q = 0; q < C::F / 4; ++q) {
+  for (int q = 0; q < C::V; ++q) {
+    const int c = threadIdx.x + 64 * C::Prod * q, row = row0 + c / (D / 4), xc = 4 * (c % (D / 4));
+    if (row < rows) {
       const v4f t = {v[q].x, v[q].y, v[q].z, v[q].w};
-      __builtin_nontemporal_store(t, reinterpret_cast<v4f*>(p + 4 * q));
+      __builtin_nontemporal_store(t, reinterpret_cast<v4f*>(dst + (int64_t)row * D + xc));
     }
   }
 }
 // B fragments of W columns [32 wave, 32 wave + 32) and their bias
-template <int D>
+template <class C>
 __device__ __forceinline__ void mm_load_w(const float* __restrict__ W, int ldw, const float* __restrict__ b, int wave,
-                                          float (&bfr)[MmCfg<D>::KB][16], float& bias) {
+                                          float (&bfr)[C::KB][16], float& bias) {
   const int lane = threadIdx.x & 63, h = lane >> 5, col = 32 * wave + (lane & 31);
 #pragma unroll
-  for (int kb = 0; kb < MmCfg<D>::KB; ++kb)
+  for (int kb = 0; kb < C::KB; ++kb)
 #pragma unroll
     for (int e = 0; e < 16; ++e) bfr[kb][e] = W[(int64_t)(32 * kb + 16 * h + e) * ldw + col];
   bias = b[col];
 }
 // z slice (Rows x 32 columns) of one producer wave, X -> Z
-template <int D>
-__device__ __forceinline__ void mm_tile(const float* X, float* Z, const float (&bfr)[MmCfg<D>::KB][16], float bias,
-                                        int wave) {
-  using C = MmCfg<D>;
+template <class C>
+__device__ __forceinline__ void mm_tile(const float* X, float* Z, const float (&bfr)[C::KB][16], float bias, int wave) {
   const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
-  // the 32-row subtiles are independent accumulation chains
-  v16f acc[C::RS];
+  // two 32-row subtiles at a time are independent accumulation chains; three
+  // would not fit 128 VGPRs
+  constexpr int SG = C::RS == 2 ? 2 : 1;
+#pragma unroll 1
+  for (int s0 = 0; s0 < C::RS; s0 += SG) {
+    v16f acc[SG];
 #pragma unroll
-  for (int s = 0; s < C::RS; ++s)
+    for (int s = 0; s < SG; ++s)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[s][e] = 0.f;
+      for (int e = 0; e < 16; ++e) acc[s][e] = 0.f;
 #pragma unroll
-  for (int kb = 0; kb < C::KB; ++kb) {
-    float af[C::RS][16];
+    for (int kb = 0; kb < C::KB; ++kb) {
+      float af[SG][16];
 #pragma unroll
-    for (int s = 0; s < C::RS; ++s) {
-      const float* ap = &X[(32 * s + l32) * C::Xld + 32 * kb + 16 * h];
+      for (int s = 0; s < SG; ++s) {
+        const float* ap = &X[(32 * (s0 + s) + l32) * C::Xld + 32 * kb + 16 * h];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 v = *reinterpret_cast<const float4*>(ap + 4 * q);
-        af[s][4 * q] = v.x; af[s][4 * q + 1] = v.y; af[s][4 * q + 2] = v.z; af[s][4 * q + 3] = v.w;
+        for (int q = 0; q < 4; ++q) {
+          const float4 v = *reinterpret_cast<const float4*>(ap + 4 * q);
+          af[s][4 * q] = v.x; af[s][4 * q + 1] = v.y; af[s][4 * q + 2] = v.z; af[s][4 * q + 3] = v.w;
+        }
       }
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int s = 0; s < SG; ++s)
+          acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[s][e], bfr[kb][e], acc[s], 0, 0, 0);
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
+    for (int s = 0; s < SG; ++s)
 #pragma unroll
-      for (int s = 0; s < C::RS; ++s)
-        acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[s][e], bfr[kb][e], acc[s], 0, 0, 0);
+      for (int e = 0; e < 16; ++e)
+        Z[(32 * (s0 + s) + 8 * (e >> 2) + 4 * h + (e & 3)) * C::Zld + ((32 * wave + l32) ^ ((e & 1) * 32))] =
+            acc[s][e] + bias;
   }
-#pragma unroll
-  for (int s = 0; s < C::RS; ++s)
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-      Z[(32 * s + 8 * (e >> 2) + 4 * h + (e & 3)) * C::Zld + ((32 * wave + l32) ^ ((e & 1) * 32))] = acc[s][e] + bias;
 }
 
 // One block per compute unit, walking its share of the jobs' tiles (XcdTiles).
-template <int D>
-__global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs J) {
-  using C = MmCfg<D>;
+template <int D, int R>
+__global__ void __launch_bounds__((MmCfg<D, R>::Threads), 1) k_gate_fwd_mm(GateMmJobs J) {
+  using C = MmCfg<D, R>;
   __shared__ __attribute__((aligned(16))) float Xs[2][C::Rows * C::Xld];
   __shared__ __attribute__((aligned(16))) float Zs[2][C::Rows * C::Zld];
   // LayerNorm parameters of every job: [job][gc, bc, gg, bg][d]
@@ -768,21 +773,21 @@ __global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs
   const int nt = T.tiles_of_block();
   if (nt == 0) return;
   if (wave < C::Prod) {
-    float4 xv[C::F / 4];
+    float4 xv[C::V];
     auto fetch_x = [&](int i) {
       int k;
       const int tile = T.tile(i, k);
-      mm_fetch_x<D>(J.j[k].x, J.j[k].rows, tile * C::Rows, xv);
+      mm_fetch_x<D, C>(J.j[k].x, J.j[k].rows, tile * C::Rows, xv);
     };
     auto copy_x = [&](int i) {
       int k;
       const int tile = T.tile(i, k);
-      if (J.j[k].xcopy) mm_copy_x<D>(J.j[k].xcopy, J.j[k].rows, tile * C::Rows, xv);
+      if (J.j[k].xcopy) mm_copy_x<D, C>(J.j[k].xcopy, J.j[k].rows, tile * C::Rows, xv);
     };
     int cur = -1;
     float bfr[C::KB][16], bias = 0.f;
     fetch_x(0);
-    mm_store_x<D>(Xs[0], xv);
+    mm_store_x<D, C>(Xs[0], xv);
     copy_x(0);
     if (nt > 1) fetch_x(1);
     __syncthreads();
@@ -792,14 +797,14 @@ __global__ void __launch_bounds__(MmCfg<D>::Threads, 1) k_gate_fwd_mm(GateMmJobs
         T.tile(i, k);
         if (k != cur) {
           cur = k;
-          mm_load_w<D>(J.j[k].W, J.j[k].ldw, J.j[k].bias, wave, bfr, bias);
+          mm_load_w<C>(J.j[k].W, J.j[k].ldw, J.j[k].bias, wave, bfr, bias);
         }
         if (i + 1 < nt) {
-          mm_store_x<D>(Xs[(i + 1) & 1], xv);
+          mm_store_x<D, C>(Xs[(i + 1) & 1], xv);
           copy_x(i + 1);
           if (i + 2 < nt) fetch_x(i + 2);
         }
-        mm_tile<D>(Xs[i & 1], Zs[i & 1], bfr, bias, wave);
+        mm_tile<C>(Xs[i & 1], Zs[i & 1], bfr, bias, wave);
       }
       __syncthreads();
     }
@@ -2840,7 +2845,9 @@ int pack_params(const ParamLayout& L, const ParamLayout& La, const PackTable& pk
 // Launch the fused forward gates of one layer: a persistent grid of one
 // block per compute unit.
 int gate_fwd_mm_launch(int D, GateMmJobs J, hipStream_t st) {
-  const int rows_per_tile = D == 64 ? MmCfg<64>::Rows : MmCfg<128>::Rows;
+  int64_t rows = 0;
+  for (int i = 0; i < J.n; ++i) rows += J.j[i].rows;
+  const int rows_per_tile = D == 128 ? 32 : rows >= kMmTallRows ? 96 : 64;
   GateMmJobs K{};
   int nt[3];
   for (int i = 0; i < J.n; ++i) {
@@ -2851,8 +2858,12 @@ int gate_fwd_mm_launch(int D, GateMmJobs J, hipStream_t st) {
   }
   const int grid = xcd_grid(nt, K.n);
   if (grid == 0) return CHGNET_OK;
-  if (D == 64) KLAUNCH(st, "k_gate_fwd", k_gate_fwd_mm<64><<<grid, MmCfg<64>::Threads, 0, st>>>(K));
-  else KLAUNCH(st, "k_gate_fwd", k_gate_fwd_mm<128><<<grid, MmCfg<128>::Threads, 0, st>>>(K));
+  if (rows_per_tile == 96)
+    KLAUNCH(st, "k_gate_fwd", k_gate_fwd_mm<64, 96><<<grid, MmCfg<64, 96>::Threads, 0, st>>>(K));
+  else if (rows_per_tile == 64)
+    KLAUNCH(st, "k_gate_fwd", k_gate_fwd_mm<64, 64><<<grid, MmCfg<64, 64>::Threads, 0, st>>>(K));
+  else
+    KLAUNCH(st, "k_gate_fwd", k_gate_fwd_mm<128, 32><<<grid, MmCfg<128, 32>::Threads, 0, st>>>(K));
   return CHGNET_OK;
 }
 
