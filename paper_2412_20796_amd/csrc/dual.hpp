@@ -263,8 +263,15 @@ __global__ void __launch_bounds__(256) kd_dz_bonds(int B, int D, int which, cons
 }
 
 // ---------------------------------------------------------------------------
-// Gated MLP (Sec. II-B (3)): phi = SiLU(LN_c(z_c)) * sigmoid(LN_g(z_g)), one
-// wavefront a row, d / 64 columns a lane.
+// Gated MLP (Sec. II-B (3)): phi = SiLU(LN_c(z_c)) * sigmoid(LN_g(z_g)). d / 4
+// adjacent lanes hold a row, four columns each, so a wavefront works on 256 / d
+// rows at a time with 16-byte accesses, and the LayerNorm sums (four a row
+// forward, eight more backward, each of values and tangents) are DPP steps
+// within 16 lanes. With a row a wavefront (4-byte accesses, six cross-lane
+// shuffles a sum) they were bound by the shuffles: on 85,000 edges and 86,000
+// angles (d = 64) backward 209 -> 96 us a launch and forward 166 -> 79 us, now
+// bound by memory. The launches are one resident round at 128 VGPRs, a few
+// values spilled; 138 to 144 VGPRs would leave a quarter of the blocks over.
 // ---------------------------------------------------------------------------
 constexpr int kDnMaxV = 2;  // d <= 128
 constexpr int kDnGateWaves = 4096;  // wavefronts of the gate kernels: one resident round, 4 a SIMD
@@ -295,78 +302,107 @@ struct DnGates {
   DnGate j[3];
 };
 
-template <int MV>
-__device__ __forceinline__ void dn_ln(const Dn (&z)[MV], int V, int D, Dn (&xh)[MV], Dn& rstd) {
-  Dn s{0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < MV; ++i)
-    if (i < V) s = s + z[i];
-  const Dn mu = (1.0f / D) * dn_wsum(s);
+template <int D>
+struct DnRow {
+  static constexpr int LPR = D / 4;     // lanes a row
+  static constexpr int RPW = 64 / LPR;  // rows of a wavefront
+  // sum over the lanes of a row
+  static __device__ __forceinline__ float sum(float x) {
+    x = rowsum<16>(x);
+    if (LPR == 32) x += __shfl_xor(x, 16, 64);
+    return x;
+  }
+  static __device__ __forceinline__ Dn sum(Dn x) { return {sum(x.v), sum(x.t)}; }
+};
+__device__ __forceinline__ void dn_load4(const float* __restrict__ p, float (&v)[4]) {
+  const float4 t = *reinterpret_cast<const float4*>(p);
+  v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+}
+// a parameter row's columns: aligned as floats only
+__device__ __forceinline__ void dn_param4(const float* __restrict__ p, float (&v)[4]) {
+  const f4u t = *reinterpret_cast<const f4u*>(p);
+  v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+}
+__device__ __forceinline__ void dn_store4(float* __restrict__ p, const float (&v)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+// LayerNorm parameters of a lane's columns
+struct DnLn {
+  float gc[4], bc[4], gg[4], bg[4];
+};
+__device__ __forceinline__ DnLn dn_ln_params(const DnGate& q, int c) {
+  DnLn l;
+  dn_param4(q.gc + c, l.gc);
+  dn_param4(q.bc + c, l.bc);
+  dn_param4(q.gg + c, l.gg);
+  dn_param4(q.bg + c, l.bg);
+  return l;
+}
+
+template <int D>
+__device__ __forceinline__ void dn_ln(const Dn (&z)[4], Dn (&xh)[4], Dn& rstd) {
+  const Dn mu = (1.0f / D) * DnRow<D>::sum((z[0] + z[1]) + (z[2] + z[3]));
   Dn q{0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < MV; ++i)
-    if (i < V) q = q + (z[i] - mu) * (z[i] - mu);
-  rstd = dn_recip(dn_sqrt((1.0f / D) * dn_wsum(q) + kLnEps));
+  for (int i = 0; i < 4; ++i) q = q + (z[i] - mu) * (z[i] - mu);
+  rstd = dn_recip(dn_sqrt((1.0f / D) * DnRow<D>::sum(q) + kLnEps));
 #pragma unroll
-  for (int i = 0; i < MV; ++i) xh[i] = (z[i] - mu) * rstd;
+  for (int i = 0; i < 4; ++i) xh[i] = (z[i] - mu) * rstd;
 }
 
 // Raw inputs of one forward row (lane's columns): z core/gate value and
 // tangent, and the gathered projection rows, summed only when the row is
 // computed, so that the loads of the next row are in flight meanwhile.
-template <int V>
 struct DnFwdRaw {
-  float z[4][V];
-  float a[3][2][V];
+  float z[4][4];
+  float a[3][2][4];
 };
-template <int V>
-__device__ __forceinline__ void dn_fwd_load(const DnGate& q, int64_t r, const int64_t (&ro)[3], int D, int lane,
-                                            DnFwdRaw<V>& x) {
+template <int D>
+__device__ __forceinline__ void dn_fwd_load(const DnGate& q, int64_t r, const int (&ro)[3], int c, DnFwdRaw& x) {
+  const float *zv = q.zv + r * q.ldzv + c, *zt = q.zt + r * 2 * D + c;
+  dn_load4(zv, x.z[0]);
+  dn_load4(zt, x.z[1]);
+  dn_load4(zv + D, x.z[2]);
+  dn_load4(zt + D, x.z[3]);
 #pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int64_t o = r * 2 * D + lane + 64 * i, ov = r * q.ldzv + lane + 64 * i;
-    x.z[0][i] = q.zv[ov];
-    x.z[1][i] = q.zt[o];
-    x.z[2][i] = q.zv[ov + D];
-    x.z[3][i] = q.zt[o + D];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (k >= q.nadd) break;
-      const int64_t c = ro[k] + lane + 64 * i;
-      x.a[k][0][i] = q.addt[k][c];
-      x.a[k][1][i] = q.addt[k][c + D];
-    }
+  for (int k = 0; k < 3; ++k) {
+    if (k >= q.nadd) break;
+    const float* a = q.addt[k] + (int64_t)ro[k] * 8 * D + c;
+    dn_load4(a, x.a[k][0]);
+    dn_load4(a + D, x.a[k][1]);
   }
 }
-__device__ __forceinline__ void dn_fwd_index(const DnGate& q, int64_t r, int D, int64_t (&ro)[3]) {
+__device__ __forceinline__ void dn_fwd_index(const DnGate& q, int64_t r, int (&ro)[3]) {
 #pragma unroll
-  for (int k = 0; k < 3; ++k) ro[k] = k < q.nadd ? (int64_t)q.idx[k][r] * 8 * D : 0;
+  for (int k = 0; k < 3; ++k) ro[k] = k < q.nadd ? q.idx[k][r] : 0;
 }
 
-// Forward of the gates: every wavefront walks the rows w, w + W, ... of each
-// job, loading row r + W (and the gather indices of r + 2W) before it
-// computes row r.
-template <int V>
-__global__ void __launch_bounds__(256) kd_gate_fwd(DnGates J) {
-  constexpr int D = 64 * V;
-  const int lane = threadIdx.x & 63;
-  const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), W = (int64_t)gridDim.x * 4;
+// Forward of the gates: every row slot walks the rows w, w + W, ... of each
+// job (W slots in the grid), loading row r + W (and the gather indices of r +
+// 2W) before it computes row r.
+template <int D>
+__global__ void __launch_bounds__(256, 4) kd_gate_fwd(DnGates J) {
+  using R = DnRow<D>;
+  const int lane = threadIdx.x & 63, c = 4 * (lane % R::LPR);
+  const int64_t w = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R::RPW + lane / R::LPR;
+  const int64_t W = (int64_t)gridDim.x * 4 * R::RPW;
   for (int job = 0; job < J.n; ++job) {
     const DnGate& q = J.j[job];
     if (w >= q.rows) continue;
-    int64_t ro[3], ron[3];
-    DnFwdRaw<V> cur, nxt;
-    dn_fwd_index(q, w, D, ro);
-    if (w + W < q.rows) dn_fwd_index(q, w + W, D, ron);
-    dn_fwd_load(q, w, ro, D, lane, cur);
+    const DnLn ln = dn_ln_params(q, c);
+    int ro[3], ron[3];
+    DnFwdRaw cur, nxt;
+    dn_fwd_index(q, w, ro);
+    if (w + W < q.rows) dn_fwd_index(q, w + W, ron);
+    dn_fwd_load<D>(q, w, ro, c, cur);
     for (int64_t r = w; r < q.rows; r += W) {
       if (r + W < q.rows) {
-        dn_fwd_load(q, r + W, ron, D, lane, nxt);
-        if (r + 2 * W < q.rows) dn_fwd_index(q, r + 2 * W, D, ron);
+        dn_fwd_load<D>(q, r + W, ron, c, nxt);
+        if (r + 2 * W < q.rows) dn_fwd_index(q, r + 2 * W, ron);
       }
-      Dn zc[V], zg[V], xc[V], xg[V], rc, rg;
+      Dn zc[4], zg[4], xc[4], xg[4], rc, rg;
 #pragma unroll
-      for (int i = 0; i < V; ++i) {
+      for (int i = 0; i < 4; ++i) {
         zc[i] = Dn{cur.z[0][i], cur.z[1][i]};
         zg[i] = Dn{cur.z[2][i], cur.z[3][i]};
 #pragma unroll
@@ -377,79 +413,75 @@ __global__ void __launch_bounds__(256) kd_gate_fwd(DnGates J) {
         }
       }
       if (q.nadd > 0) {
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
-          const int64_t o = r * 2 * D + lane + 64 * i;
-          q.zt[o] = zc[i].t;
-          q.zt[o + D] = zg[i].t;
-        }
+        float* zt = q.zt + r * 2 * D + c;
+        const float tc[4] = {zc[0].t, zc[1].t, zc[2].t, zc[3].t}, tg[4] = {zg[0].t, zg[1].t, zg[2].t, zg[3].t};
+        dn_store4(zt, tc);
+        dn_store4(zt + D, tg);
       }
-      dn_ln(zc, V, D, xc, rc);
-      dn_ln(zg, V, D, xg, rg);
+      dn_ln<D>(zc, xc, rc);
+      dn_ln<D>(zg, xg, rg);
+      float pv[4], pt[4];
 #pragma unroll
-      for (int i = 0; i < V; ++i) {
-        const int c = lane + 64 * i;
-        const Dn yc = q.gc[c] * xc[i] + q.bc[c];
-        const Dn yg = q.gg[c] * xg[i] + q.bg[c];
+      for (int i = 0; i < 4; ++i) {
+        const Dn yc = ln.gc[i] * xc[i] + ln.bc[i];
+        const Dn yg = ln.gg[i] * xg[i] + ln.bg[i];
         const Dn ph = yc * dn_sigm(yc) * dn_sigm(yg);
-        const int64_t o = r * D + c;
-        if (q.res_t) {
-          q.pt[o] = q.res_t[o] + ph.t;
-        } else {
-          q.pv[o] = ph.v;
-          q.pt[o] = ph.t;
-        }
+        pv[i] = ph.v;
+        pt[i] = ph.t;
       }
+      if (q.res_t) {
+        float a[4];
+        dn_load4(q.res_t + r * D + c, a);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pt[i] += a[i];
+      } else {
+        dn_store4(q.pv + r * D + c, pv);
+      }
+      dn_store4(q.pt + r * D + c, pt);
       cur = nxt;
     }
   }
 }
 
-// Backward of the gates: every wavefront walks the rows w, w + W, ... of each
-// job (W wavefronts in the grid), loading row r + W before it computes row
-// r, and keeps the tangents of its rows' LayerNorm parameter terms in
-// registers; it writes them once per job, as row w of lnp [W, 4d]:
-// dy_c xhat_c | dy_c | dy_g xhat_g | dy_g.
-template <int V>
+// Backward of the gates: every row slot walks the rows w, w + W, ... of each
+// job (W slots in the grid), loading row r + W before it computes row r, and
+// keeps the tangents of its rows' LayerNorm parameter terms in registers; a
+// wavefront adds its slots' and writes them once per job, as a row of lnp
+// [wavefronts, 4d]: dy_c xhat_c | dy_c | dy_g xhat_g | dy_g.
 struct DnBwdRaw {
-  float z[4][V];
-  float dp[2][V];
+  float z[4][4];
+  float dp[2][4];
 };
-template <int V>
-__device__ __forceinline__ void dn_bwd_load(const DnGate& q, int64_t r, int lane, DnBwdRaw<V>& x) {
-  constexpr int D = 64 * V;
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int64_t o = r * 2 * D + lane + 64 * i, op = r * D + lane + 64 * i, ov = r * q.ldzv + lane + 64 * i;
-    x.z[0][i] = q.zv[ov];
-    x.z[1][i] = q.zt[o];
-    x.z[2][i] = q.zv[ov + D];
-    x.z[3][i] = q.zt[o + D];
-    x.dp[0][i] = q.dpv[op];
-    x.dp[1][i] = q.dpt[op];
-  }
+template <int D>
+__device__ __forceinline__ void dn_bwd_load(const DnGate& q, int64_t r, int c, DnBwdRaw& x) {
+  const float *zv = q.zv + r * q.ldzv + c, *zt = q.zt + r * 2 * D + c;
+  dn_load4(zv, x.z[0]);
+  dn_load4(zt, x.z[1]);
+  dn_load4(zv + D, x.z[2]);
+  dn_load4(zt + D, x.z[3]);
+  dn_load4(q.dpv + r * D + c, x.dp[0]);
+  dn_load4(q.dpt + r * D + c, x.dp[1]);
 }
 
-template <int V>
-__device__ __forceinline__ void dn_gate_bwd_row(const DnGate& q, int64_t r, int lane, const DnBwdRaw<V>& x,
-                                                float (&acc)[4][V]) {
-  constexpr int D = 64 * V;
-  Dn zc[V], zg[V], xc[V], xg[V], rc, rg;
+template <int D>
+__device__ __forceinline__ void dn_gate_bwd_row(const DnGate& q, int64_t r, int col, const DnLn& ln, const DnBwdRaw& x,
+                                                float (&acc)[4][4]) {
+  using R = DnRow<D>;
+  Dn zc[4], zg[4], xc[4], xg[4], rc, rg;
 #pragma unroll
-  for (int i = 0; i < V; ++i) {
+  for (int i = 0; i < 4; ++i) {
     zc[i] = Dn{x.z[0][i], x.z[1][i]};
     zg[i] = Dn{x.z[2][i], x.z[3][i]};
   }
-  dn_ln(zc, V, D, xc, rc);
-  dn_ln(zg, V, D, xg, rg);
-  Dn gc[V], gg[V];
+  dn_ln<D>(zc, xc, rc);
+  dn_ln<D>(zg, xg, rg);
+  Dn gc[4], gg[4];
   Dn s1c{0.f, 0.f}, s2c{0.f, 0.f}, s1g{0.f, 0.f}, s2g{0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int c = lane + 64 * i;
+  for (int i = 0; i < 4; ++i) {
     const Dn dp{x.dp[0][i], x.dp[1][i]};
-    const Dn yc = q.gc[c] * xc[i] + q.bc[c];
-    const Dn yg = q.gg[c] * xg[i] + q.bg[c];
+    const Dn yc = ln.gc[i] * xc[i] + ln.bc[i];
+    const Dn yg = ln.gg[i] * xg[i] + ln.bg[i];
     const Dn sc = dn_sigm(yc), sg = dn_sigm(yg);
     const Dn dyc = dp * sg * (sc * (1.0f + yc * (1.0f - sc)));
     const Dn dyg = dp * (yc * sc) * sg * (1.0f - sg);
@@ -457,49 +489,60 @@ __device__ __forceinline__ void dn_gate_bwd_row(const DnGate& q, int64_t r, int 
     acc[1][i] += dyc.t;
     acc[2][i] += (dyg * xg[i]).t;
     acc[3][i] += dyg.t;
-    gc[i] = q.gc[c] * dyc;
-    gg[i] = q.gg[c] * dyg;
+    gc[i] = ln.gc[i] * dyc;
+    gg[i] = ln.gg[i] * dyg;
     s1c = s1c + gc[i];
     s2c = s2c + gc[i] * xc[i];
     s1g = s1g + gg[i];
     s2g = s2g + gg[i] * xg[i];
   }
   const float inv = 1.0f / D;
-  s1c = inv * dn_wsum(s1c);
-  s2c = inv * dn_wsum(s2c);
-  s1g = inv * dn_wsum(s1g);
-  s2g = inv * dn_wsum(s2g);
+  s1c = inv * R::sum(s1c);
+  s2c = inv * R::sum(s2c);
+  s1g = inv * R::sum(s1g);
+  s2g = inv * R::sum(s2g);
+  float cv[4], ct[4], gv[4], gt[4];
 #pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int64_t o = r * 2 * D + lane + 64 * i;
+  for (int i = 0; i < 4; ++i) {
     const Dn dc = rc * (gc[i] - s1c - xc[i] * s2c);
     const Dn dg = rg * (gg[i] - s1g - xg[i] * s2g);
-    q.dzv[o] = dc.v;
-    q.dzt[o] = dc.t;
-    q.dzv[o + D] = dg.v;
-    q.dzt[o + D] = dg.t;
+    cv[i] = dc.v;
+    ct[i] = dc.t;
+    gv[i] = dg.v;
+    gt[i] = dg.t;
   }
+  const int64_t o = r * 2 * D + col;
+  dn_store4(q.dzv + o, cv);
+  dn_store4(q.dzt + o, ct);
+  dn_store4(q.dzv + o + D, gv);
+  dn_store4(q.dzt + o + D, gt);
 }
 
-template <int V>
-__global__ void __launch_bounds__(256) kd_gate_bwd(DnGates J) {
-  constexpr int D = 64 * V;
-  const int lane = threadIdx.x & 63;
-  const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), W = (int64_t)gridDim.x * 4;
+template <int D>
+__global__ void __launch_bounds__(256, 4) kd_gate_bwd(DnGates J) {
+  using R = DnRow<D>;
+  const int lane = threadIdx.x & 63, c = 4 * (lane % R::LPR);
+  const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t w = wave * R::RPW + lane / R::LPR, W = (int64_t)gridDim.x * 4 * R::RPW;
   for (int k = 0; k < J.n; ++k) {
     const DnGate& q = J.j[k];
-    float acc[4][V] = {};
-    DnBwdRaw<V> cur, nxt;
-    if (w < q.rows) dn_bwd_load(q, w, lane, cur);
+    const DnLn ln = dn_ln_params(q, c);
+    float acc[4][4] = {};
+    DnBwdRaw cur, nxt;
+    if (w < q.rows) dn_bwd_load<D>(q, w, c, cur);
     for (int64_t r = w; r < q.rows; r += W) {
-      if (r + W < q.rows) dn_bwd_load(q, r + W, lane, nxt);
-      dn_gate_bwd_row(q, r, lane, cur, acc);
+      if (r + W < q.rows) dn_bwd_load<D>(q, r + W, c, nxt);
+      dn_gate_bwd_row<D>(q, r, c, ln, cur, acc);
       cur = nxt;
     }
 #pragma unroll
-    for (int i = 0; i < V; ++i)
+    for (int u = 0; u < 4; ++u) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) q.lnp[w * 4 * D + u * D + lane + 64 * i] = acc[u][i];
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int o = R::LPR; o < 64; o *= 2) acc[u][i] += __shfl_xor(acc[u][i], o, 64);
+      if (lane < R::LPR) dn_store4(q.lnp + wave * 4 * D + u * D + c, acc[u]);
+    }
   }
 }
 
@@ -861,13 +904,13 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
     if (fwd) {
       if (J.start[J.n] > 0)
       {
-        if (D == 64) KLAUNCH(st, "kd_gate_fwd", kd_gate_fwd<1><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
-        else KLAUNCH(st, "kd_gate_fwd", kd_gate_fwd<2><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
+        if (D == 64) KLAUNCH(st, "kd_gate_fwd", kd_gate_fwd<64><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
+        else KLAUNCH(st, "kd_gate_fwd", kd_gate_fwd<128><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
       }
     } else {
       // every wavefront writes its LayerNorm terms, also for jobs without rows
-      if (D == 64) KLAUNCH(st, "kd_gate_bwd", kd_gate_bwd<1><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
-      else KLAUNCH(st, "kd_gate_bwd", kd_gate_bwd<2><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
+      if (D == 64) KLAUNCH(st, "kd_gate_bwd", kd_gate_bwd<64><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
+      else KLAUNCH(st, "kd_gate_bwd", kd_gate_bwd<128><<<(unsigned)(kDnGateWaves / 4), 256, 0, st>>>(J));
     }
     return CHGNET_OK;
   };

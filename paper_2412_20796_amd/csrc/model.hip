@@ -20,6 +20,7 @@
 
 #include "common.hpp"
 #include "gemm.hpp"
+#include "split.hpp"
 
 namespace chg {
 
