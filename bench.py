@@ -133,7 +133,7 @@ def main():
         E, B, A = g.n_edges, g.n_bonds, g.n_angles
         rl, rows = roofline(prof, n, dict(N=b.n_atoms, E=E, B=B, A=A, S=b.n_struct, D=d, T=T,
                                           fused_bwd=not args.sequential, workload=args.workload,
-                                          R=hp.n_rbf, K=hp.n_fourier))
+                                          R=hp.n_rbf, K=hp.n_fourier, conservative=args.conservative))
         print(json.dumps({"launch_timing_steps": n, "roofline": rl, "kernels": rows}), flush=True)
         return
     for _ in range(max(args.warmup, 1)):
@@ -195,7 +195,8 @@ def main():
         out["roofline"], out["kernels"] = roofline(prof, args.steps, dict(N=b.n_atoms, E=E, B=B, A=A, S=S, D=d, T=T,
                                                                             fused_bwd=not args.sequential,
                                                                             workload=args.workload, R=hp.n_rbf,
-                                                                            K=hp.n_fourier))
+                                                                            K=hp.n_fourier,
+                                                                                                    conservative=args.conservative))
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(args.workload, args.cpu_sample, variant=args)
     print(json.dumps(out), flush=True)
@@ -265,6 +266,14 @@ def md_bench(args, bd, synth, dev):
     }
 
 
+def module_sum(z):
+    """Sum over the layers of per-module costs (atom conv, bond conv, angle
+    update): T, T and T - 1 of them, one bond conv and one angle update less
+    where only the energy's own inputs are run (conservative readout)."""
+    T, c = z["T"], 1 if z.get("conservative") else 0
+    return lambda atom, bond, angle: T * atom + max(T - c, 0) * bond + max(T - 1 - c, 0) * angle
+
+
 def algorithmic_cost(tag, z):
     """Algorithmic work of one step's launches of `tag`: ("mfma", flops) for
     the dense products, ("hbm", bytes) for gather/scatter/elementwise kernels.
@@ -278,6 +287,9 @@ def algorithmic_cost(tag, z):
     N, E, B, A, D, T = z["N"], z["E"], z["B"], z["A"], z["D"], z["T"]
     Tang = T - 1  # layers with an angle update
     f = 4  # bytes per fp32
+    mods = module_sum(z)
+    if z.get("conservative") and tag in ("gemm_in_bwd", "tn_in", "gemm_proj", "gemm_bond_bwd", "k_bond_bwd_reduce"):
+        return None, None  # counted below for the direct heads' modules
     if tag == "gemm_in_bwd" and z.get("fused_bwd"):
         # the edge and angle rows are formed by the fused gate backward; this
         # launch holds the atom rows and the bond rows (k = 8d, 6d last layer)
@@ -295,77 +307,63 @@ def algorithmic_cost(tag, z):
         # d = 128: the fused gate is bound by its product z = x W (+ b) of
         # every edge (d -> 2d) and, per angle, of the bond-conv and
         # angle-update gates (d -> 4d; d -> 2d in the last layer)
-        return "mfma", T * E * 4 * D * D + Tang * A * 8 * D * D + A * 4 * D * D
+        return "mfma", 4 * D * D * mods(E, A, A)
     if tag == "k_gate_fwd" and D == 64:
         # pre-activations formed in the kernel (d = 64): per edge x (d) and
         # e^a (d) in, z kept for the backward (2d), message (d) and the copy
         # of x into e^{t+1} (d) out; per angle and gate x (d) in, z (2d) and
         # output (d) out, the angle gate also reads a (d). Tables: per-atom
         # terms N x 8d (6d last layer), per-bond terms B x 8d (4d), e^b B x d.
-        lay = E * 6 * D + A * 9 * D + N * 8 * D + B * 9 * D
-        last = E * 6 * D + A * 4 * D + N * 6 * D + B * 5 * D
-        return "hbm", f * (Tang * lay + last)
+        return "hbm", f * D * mods(6 * E + 4 * N, 4 * A + 2 * N + 5 * B, 5 * A + 2 * N + 4 * B)
     if tag == "k_gate_bwd" and z.get("fused_bwd") and D != 64:
         # d = 128: the fused backward gate is bound by its input-gradient
         # product dX = dz W^T of every edge (2d -> d) and, per angle, of the
         # bond-conv and angle-update gates (2 x 2d -> d; one gate in the last
         # layer): the same flops as the forward product
-        return "mfma", T * E * 4 * D * D + Tang * A * 8 * D * D + A * 4 * D * D
+        return "mfma", 4 * D * D * mods(E, A, A)
     if tag == "k_gate_bwd" and z.get("fused_bwd"):
         # as below, plus the input gradients the kernel forms: per edge the
         # residual (d) in and de (d) out; per angle da (d) out and, in layers
         # with an angle update, the residual (d) in
-        lay = E * 9 * D + A * 12 * D + N * 9 * D + B * 10 * D
-        last = E * 9 * D + A * 6 * D + N * 7 * D + B * 6 * D
-        return "hbm", f * (Tang * lay + last)
+        return "hbm", f * D * mods(9 * E + 5 * N, 6 * A + 2 * N + 6 * B, 6 * A + 2 * N + 4 * B)
     if tag == "k_gate_bwd":
         # per edge: z (2d), e^a (d), d e^a (d) in; dz (2d), d e^a (d) out;
         # per angle and gate: z (2d) + upstream (d) in, dz (2d) out (the bond
         # gate's upstream is gathered, its t2 (d) written). Tables as in the
         # forward plus dm N x d, dmu B x d.
-        lay = E * 7 * D + A * 10 * D + N * 9 * D + B * 10 * D
-        last = E * 7 * D + A * 5 * D + N * 7 * D + B * 6 * D
-        return "hbm", f * (Tang * lay + last)
+        return "hbm", f * D * mods(7 * E + 5 * N, 5 * A + 2 * N + 6 * B, 5 * A + 2 * N + 4 * B)
     if tag == "k_bond_bwd_reduce":
         # dz read once from HBM (a row's second read, by its other bond, is
         # scheduled to hit L2), t2 read; DZ12 written
         return "hbm", f * (Tang * A * (4 * D + D) + A * (2 * D + D) + T * B * 8 * D)
-    # training through the conservative readout: the dual-number pass (value
-    # and tangent parts; a linear map costs twice its flops, the tangent-only
-    # maps once)
-    R, K = z.get("R", 31), z.get("K", 31)
+    # training through the conservative readout: the dual-number pass. The
+    # forward pass's values are reused, so forward maps cost their flops once
+    # (tangents); backward maps cost them twice.
+    R, K, DD = z.get("R", 31), z.get("K", 31), D * D
     if tag == "kd_gemm":
         emb = 2 * (2 * E * R * D + B * R * D + A * K * D) + 8 * E * D * R + 4 * B * D * R
-        heads = 4 * N * D * D + 8 * N * D * D
-        # per layer: projections (atom blocks 4 or 3, bond blocks 4 or 2), the
-        # edge and angle blocks, tangent updates; backward dm, dmu, the input
-        # gradients of atoms (S, 4 or 3 blocks of 2d), edges, angles and bonds (T)
-        lay = lambda ang: (8 * N * D * D * (4 if ang else 3) + 8 * B * D * D * (4 if ang else 2) + 8 * E * D * D
-                           + 8 * A * D * D * (2 if ang else 1) + 2 * N * D * D + 2 * B * D * D
-                           + 4 * N * D * D + 4 * B * D * D + 8 * N * D * D * (4 if ang else 3) + 8 * E * D * D
-                           + 8 * A * D * D * (2 if ang else 1) + 8 * B * D * D * (4 if ang else 2))
-        return "mfma", emb + heads + Tang * lay(True) + lay(False)
+        heads = 12 * N * DD
+        # by module: projections, the edge or angle block and the update
+        # forward; d m or d mu and the input gradients backward
+        return "mfma", emb + heads + DD * mods(10 * N + 4 * E + 20 * N + 8 * E,
+                                               4 * N + 10 * B + 4 * A + 20 * B + 8 * N + 8 * A,
+                                               4 * N + 8 * B + 4 * A + 16 * B + 8 * N + 8 * A)
     if tag == "kd_tn":
         # X_t^T Y_v + X_v^T Y_t of every weight: heads, output linears, the
         # gate blocks (atom blocks over atoms, bond blocks over bonds, edge
         # and angle blocks over their rows), the embedding
         emb = 8 * E * R * D + 4 * B * R * D + 4 * A * K * D
-        heads = 8 * N * D * D + 4 * N * D
-        lay = lambda ang: (4 * N * D * D + 4 * B * D * D + 16 * N * D * D + 8 * E * D * D
-                           + (8 * N * D * D + 16 * B * D * D + 8 * A * D * D) * (2 if ang else 1))
-        return "mfma", emb + heads + Tang * lay(True) + lay(False)
+        heads = 8 * N * DD + 4 * N * D
+        return "mfma", emb + heads + DD * mods(20 * N + 8 * E, 8 * N + 20 * B + 8 * A, 8 * N + 16 * B + 8 * A)
     if tag == "kd_gate_fwd":
-        # per row and gate: z (2d, both parts) in and out, phi (d, both
-        # parts) out (the angle update: a tangent in, a' tangent out);
-        # projection tables N x 8d and B x 8d, both parts, once
-        lay = lambda ang: (E * 10 * D + A * 10 * D + (A * 10 * D if ang else 0) + N * 16 * D
-                           + B * 16 * D * (1 if ang else 0.5))
-        return "hbm", f * (Tang * lay(True) + lay(False))
+        # per row and gate: z value (2d) in, z tangent (2d) in and out, phi
+        # (d, both parts) out (the angle update: a tangent in, a' tangent
+        # out); tangent projection tables once
+        return "hbm", f * D * mods(8 * E + 4 * N, 8 * A + 2 * N + 4 * B, 8 * A + 2 * N + 4 * B)
     if tag == "kd_gate_bwd":
         # per row and gate: z (2d) and d phi (d) in, dz (2d) out, both parts
         # (the LayerNorm parameter terms stay in registers)
-        lay = lambda ang: (E + A * (2 if ang else 1)) * 10 * D
-        return "hbm", f * (Tang * lay(True) + lay(False))
+        return "hbm", f * D * mods(10 * E, 10 * A, 10 * A)
     return None, None
 
 
@@ -382,13 +380,12 @@ def mandatory_cost(tag, z):
     bound, work = algorithmic_cost(tag, z)
     if bound == "mfma":
         return bound, work
-    N, E, B, A, D, T = z["N"], z["E"], z["B"], z["A"], z["D"], z["T"]
-    lay = E * 8 * D + B * 8 * D + A * (8 * D + 8)
-    last = E * 8 * D + B * 8 * D + A * (4 * D + 8)
+    E, B, A, D = z["E"], z["B"], z["A"], z["D"]
+    work = module_sum(z)(E * 8 * D, B * 8 * D + A * (4 * D + 8), A * 4 * D)
     if tag == "k_gate_fwd":
-        return "hbm", (T - 1) * lay + last
+        return "hbm", work
     if tag == "k_gate_bwd":
-        return "hbm", 2 * ((T - 1) * lay + last)
+        return "hbm", 2 * work
     return None, None
 
 
