@@ -930,9 +930,9 @@ int cons_grad_impl(Ctx& c, const float* dE, const float* dF, const float* dS, co
     // W_be2 | e_b W_an1 | e_b W_an2, from et); the edge and angle blocks into
     // z. The values are the forward pass's own (a.zv, a.zae), so only the
     // tangents are multiplied and gathered: on 40 crystals of 1,076 atoms the
-    // dual gates 221 -> 166 us a layer and half of the projections' launches'
-    // work (with the modules that no output depends on left out, the step went
-    // from 6.70 to 5.32 ms).
+    // dual gates 221 -> 166 us a layer (79 us since, see kd_gate_fwd) and half
+    // of the projections' launches' work (with the modules that no output
+    // depends on left out, the step went from 6.70 to 5.32 ms).
     auto project = [&](int which, const float* vt, const float* et) -> int {
       std::vector<GemmProblem> ps;
       const float* Wa[4] = {Wav, Wav + WB, Wbe, Wan};
