@@ -119,7 +119,8 @@ __device__ __forceinline__ void load_a(const GemmProblem& P, int ks, int64_t aro
   }
 }
 
-// the value that lane lr + 4 h holds, for both halves h of a wavefront
+// the value that lane lr + 4 h holds, for both halves h of a wavefront (all
+// lanes active, so that the lanes read from hold it)
 __device__ __forceinline__ int row_lane(int v, int lr, int h) {
   const int a = __builtin_amdgcn_readlane(v, lr), b = __builtin_amdgcn_readlane(v, lr + 4);
   return h ? b : a;
@@ -187,14 +188,18 @@ __device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, c
       }
       continue;
     }
-    // gathered or scattered rows, and the edges of C: rows past the end are
-    // clamped, columns past it do nothing
-    if (col >= P.N) continue;
+    // gathered or scattered rows, and the edges of C: rows and columns past
+    // the end are clamped and not stored
+    const bool in = col < P.N;
+    const int cl = min(col, P.N - 1);
+    auto row = [&](int j) { return r0 + 8 * (j >> 2) + 4 * h + (j & 3); };
+    auto row_at = [&](const int* rows, int v, int j) {
+      return rows ? row_lane(v, 8 * (j >> 2) + (j & 3), h) : min(row(j), P.M - 1);
+    };
     if (P.act == ACT_DSILU_MUL) {
       float m[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        m[j] = P.mul[(int64_t)min(r0 + 8 * (j >> 2) + 4 * h + (j & 3), P.M - 1) * P.mul_ld + col];
+      for (int j = 0; j < 16; ++j) m[j] = P.mul[(int64_t)min(row(j), P.M - 1) * P.mul_ld + cl];
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         const float sg = sigm(m[j]);
@@ -206,23 +211,23 @@ __device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, c
     if (P.res) {
       float m[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) m[j] = P.res[(int64_t)row_lane(rr, 8 * (j >> 2) + (j & 3), h) * P.res_ld + col];
+      for (int j = 0; j < 16; ++j) m[j] = P.res[(int64_t)row_at(P.res_rows, rr, j) * P.res_ld + cl];
 #pragma unroll
       for (int j = 0; j < 16; ++j) x[j] += m[j];
     }
     if (P.accumulate) {
       float m[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) m[j] = P.C[(int64_t)row_lane(cr, 8 * (j >> 2) + (j & 3), h) * P.ldc + col];
+      for (int j = 0; j < 16; ++j) m[j] = P.C[(int64_t)row_at(P.c_rows, cr, j) * P.ldc + cl];
 #pragma unroll
       for (int j = 0; j < 16; ++j) x[j] += m[j];
     }
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      const int row = r0 + 8 * (j >> 2) + 4 * h + (j & 3);
-      if (row >= P.M) continue;
-      if (P.C) P.C[(int64_t)row_lane(cr, 8 * (j >> 2) + (j & 3), h) * P.ldc + col] = x[j];
-      if (P.act == ACT_SILU_OUT) P.C2[(int64_t)row * P.ldc2 + col] = x[j] * sigm(x[j]);
+      const int64_t at = row_at(P.c_rows, cr, j);
+      if (!in || row(j) >= P.M) continue;
+      if (P.C) P.C[at * P.ldc + col] = x[j];
+      if (P.act == ACT_SILU_OUT) P.C2[(int64_t)row(j) * P.ldc2 + col] = x[j] * sigm(x[j]);
     }
   }
 }
