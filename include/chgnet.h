@@ -16,6 +16,8 @@
  *    call only enqueues work on `stream` and returns, except
  *    chgnet_build_graph, which waits once for the graph's sizes (see there).
  *  - Floating-point data are IEEE fp32; integer data are int32 unless noted.
+ *    Matrix products may take bits of their operands below 2^-126 as 0 (an
+ *    operand of at least 2^-110 in magnitude has none).
  *  - All matrices are row-major. A lattice is 3x3 with ROWS = lattice vectors,
  *    so Cartesian = fractional @ lattice.
  *  - No global data: calls are re-entrant as long as concurrent calls use

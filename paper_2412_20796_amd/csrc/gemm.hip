@@ -95,14 +95,17 @@ __device__ __forceinline__ int seg_of(const GemmProblem& P, int ks) {
 }
 
 // The sign that odd rows are multiplied with (see gemm.hpp): `flip_odd` for a
-// lane that holds row lane % 32 of A, `unflip` for value j of a 32 x 32
-// accumulator, which belongs to row 8 (j / 4) + 4 (lane / 32) + j % 4.
+// lane that holds row lane % 32 of A, `unflip` for a 32 x 32 accumulator,
+// whose value j belongs to row 8 (j / 4) + 4 (lane / 32) + j % 4.
 __device__ __forceinline__ void flip_odd(float (&v)[8], int lane) {
   const unsigned s = (unsigned)lane << 31;
 #pragma unroll
   for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(__float_as_uint(v[e]) ^ s);
 }
-__device__ __forceinline__ float unflip(float x, int j) { return (j & 1) ? -x : x; }
+__device__ __forceinline__ void unflip(v16f& acc) {
+#pragma unroll
+  for (int j = 1; j < 16; j += 2) acc[j] = -acc[j];
+}
 
 // this lane's eight A values of a step (its row, k = 16 step + 8 (lane / 32) ..)
 __device__ __forceinline__ void load_a(const GemmProblem& P, int ks, int64_t arow, int h, float (&v)[8]) {
@@ -116,6 +119,46 @@ __device__ __forceinline__ void load_a(const GemmProblem& P, int ks, int64_t aro
   } else {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = k + e < S.K ? p[e] : 0.f;
+  }
+}
+
+// 0 x over an accumulator's values, added to s: 0, or NaN where one is not
+// finite. An operand's value with a part that is not finite leaves its whole
+// row (left) or column (right) of the sums of products so, as part times 0 is
+// not finite either: a look at one accumulator and one value of its
+// neighbours finds both.
+__device__ __forceinline__ float zero_of(const v16f& x, float s) {
+  float t = 0.f;
+#pragma unroll
+  for (int j = 0; j < 16; j += 2) {
+    s = fmaf(x[j], 0.f, s);
+    t = fmaf(x[j + 1], 0.f, t);
+  }
+  return s + t;
+}
+__device__ __forceinline__ bool any_nan(float s) { return __ballot(s != 0.f) != 0; }
+
+// A wavefront's tile over the steps [lo, hi) with fp32 products, for a tile
+// whose split products are not all finite (see gemm.hpp).
+__device__ __forceinline__ void gemm_tile_fp32(const GemmProblem& P, int lo, int hi, int64_t arow, int c0, bool two,
+                                               int lane, v16f (&acc)[2]) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc[t][j] = 0.f;
+#pragma unroll 1
+  for (int ks = lo; ks < hi; ++ks) {
+    float a[8];
+    load_a(P, ks, arow, lane >> 5, a);
+    const GemmSeg& S = P.seg[seg_of(P, ks)];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (t == 1 && !two) break;
+      float b[8];
+      unsplit8(packed8(S.Bp + ((int64_t)(c0 / 32 + t) * S.bnt + ks - S.ks0) * kPackTile + lane), b);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc[t], 0, 0, 0);
+    }
   }
 }
 
@@ -146,7 +189,7 @@ __device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, c
     const int col = c0 + 32 * t + c;
     float x[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = unflip(acc[t][j], j);
+    for (int j = 0; j < 16; ++j) x[j] = acc[t][j];
     if (plain) {
       // rows at a fixed distance: one offset a lane, the rest uniform
       if (P.act == ACT_DSILU_MUL) {
@@ -287,10 +330,12 @@ __global__ void __launch_bounds__(256, KS <= 2 ? 4 : 3) k_gemm_p(GemmPArgs args)
     const int r = min(t * 32 + (lane & 31), P.M - 1);
     return P.a_rows ? P.a_rows[r] : r;
   };
-  float a[KS][8];
+  // A steps in flight: more registers for the eight of KS = 8 would spill
+  constexpr int RA = KS < 4 ? KS : 4;
+  float a[RA][8];
   int64_t ar = row_of(tile);
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
+  for (int ks = 0; ks < RA; ++ks)
     if (ks < nks) load_a(P, ks, ar, h, a[ks]);
   int buf = 0;
   load_b(0);
@@ -300,7 +345,10 @@ __global__ void __launch_bounds__(256, KS <= 2 ? 4 : 3) k_gemm_p(GemmPArgs args)
   if (P.bias)
 #pragma unroll
     for (int t = 0; t < 2; ++t) bias[t] = P.bias[min(c0 + 32 * t + (lane & 31), P.N - 1)];
-  auto put = [&](const v16f (&acc)[2]) {
+  auto put = [&](v16f (&acc)[2]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) unflip(acc[t]);
+    if (any_nan(zero_of(acc[0], 0.f * acc[1][0]))) gemm_tile_fp32(P, 0, nks, row_of(tile), c0, two, lane, acc);
     if (two) {
       gemm_put<2>(P, tile * 32, c0, acc, bias, lane);
     } else {
@@ -342,11 +390,14 @@ __global__ void __launch_bounds__(256, KS <= 2 ? 4 : 3) k_gemm_p(GemmPArgs args)
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         if (ks >= nks) break;
-        flip_odd(a[ks], lane);
-        const Split8 x = split8(a[ks]);
-        load_a(P, ks, arn, h, a[ks]);
+        flip_odd(a[ks % RA], lane);
+        const Split8 x = split8(a[ks % RA]);
+        // the next step that takes these registers, of this tile or the next
+        if (KS > RA && ks + RA < nks) load_a(P, ks + RA, ar, h, a[ks % RA]);
+        else load_a(P, ks % RA, arn, h, a[ks % RA]);
         mul(Bs, ks, x, acc);
       }
+      ar = arn;
       put(acc);
     } else {
       for (int k0 = 0; k0 < nks; k0 += KS) {
@@ -434,6 +485,9 @@ __global__ void __launch_bounds__(512, 2) k_gemm_k(GemmBatch batch) {
       if (ks + 1 < hi) compute(1);
     }
   }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) unflip(acc[u]);
+  if (any_nan(zero_of(acc[0], 0.f * acc[1][0]))) gemm_tile_fp32(P, lo, hi, arow, n0, two, lane, acc);
   if constexpr (WK == 1) {
     if (r0 >= P.M) return;
     float bias[2] = {0.f, 0.f};
@@ -453,7 +507,7 @@ __global__ void __launch_bounds__(512, 2) k_gemm_k(GemmBatch batch) {
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) my[(8 * (j >> 2) + 4 * h + (j & 3)) * kGwLd + 32 * u + c] = unflip(acc[u][j], j);
+    for (int j = 0; j < 16; ++j) my[(8 * (j >> 2) + 4 * h + (j & 3)) * kGwLd + 32 * u + c] = acc[u][j];
   __syncthreads();
   // wave-ordered sum of each tile's WK partials, epilogue with row-contiguous
   // 4-column pieces: 32 rows x 16 pieces per tile
@@ -499,7 +553,7 @@ __global__ void __launch_bounds__(256) k_pack_split(PackArgs A, const float* __r
     const int k = k0 + e;
     v[e] = n < N && k < K ? src[M.src + (T ? (int64_t)n * M.cols + k : (int64_t)k * M.cols + n)] : 0.f;
   }
-  const Split8 x = split8(v);
+  const Split8 x = split8_all(v);
   uint4* o = out + tile * kPackTile + lane;
   o[0] = __builtin_bit_cast(uint4, x.h);
   o[64] = __builtin_bit_cast(uint4, x.m);
@@ -666,25 +720,12 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
       }
     }
   };
-  // the whole steps of the range, through a ring of NB register buffers with
-  // constant indices (a step past the last loads the last one again)
+  // the rows left after the range's whole steps: clamped into the range, those
+  // past it zeroed (the clamped X row as well, so that a value that is not
+  // finite does not reach the sum)
   const int nf = rhi > rlo ? (rhi - rlo) / 16 : 0;
-  if (nf > 0) {
-    auto step = [&](int s) { return rlo + 16 * min(s, nf - 1); };
-#pragma unroll
-    for (int b = 0; b < NB - 1; ++b) fetch(step(b), b);
-    for (int s = 0; s < nf; s += NB) {
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        fetch(step(s + b + NB - 1), (b + NB - 1) % NB);
-        if (s + b < nf) compute(b);
-      }
-    }
-  }
-  // the rows left: clamped into the range, those past it zeroed (the clamped
-  // X row as well, so that a value that is not finite does not reach the sum)
-  const int g = rlo + 16 * nf;
-  if (g < rhi) {
+  auto fetch_rest = [&]() {
+    const int g = rlo + 16 * nf;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int r = min(g + 8 * h + i, rhi - 1), at = r - rlo;
@@ -698,7 +739,51 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
 #pragma unroll
       for (int u = 0; u < VY; ++u) yf[0][i][u] = in ? yf[0][i][u] : 0.f;
     }
+  };
+  const bool rest = rlo + 16 * nf < rhi;
+  // the whole steps, through a ring of NB register buffers with constant
+  // indices (a step past the last loads the last one again)
+  if (nf > 0) {
+    auto step = [&](int s) { return rlo + 16 * min(s, nf - 1); };
+#pragma unroll
+    for (int b = 0; b < NB - 1; ++b) fetch(step(b), b);
+    for (int s = 0; s < nf; s += NB) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        fetch(step(s + b + NB - 1), (b + NB - 1) % NB);
+        if (s + b < nf) compute(b);
+      }
+    }
+  }
+  if (rest) {
+    fetch_rest();
     compute(0);
+  }
+  if (HASX) {
+    float z = 0.f * acc[0][VY - 1][0];
+#pragma unroll
+    for (int v = 0; v < VX; ++v) z = zero_of(acc[v][0], z);
+    if (any_nan(z)) {  // with fp32 products (see gemm.hpp)
+#pragma unroll
+      for (int v = 0; v < VX; ++v)
+#pragma unroll
+        for (int u = 0; u < VY; ++u)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) acc[v][u][j] = 0.f;
+#pragma unroll 1
+      for (int s = 0; s < nf + (rest ? 1 : 0); ++s) {
+        if (s < nf) fetch(rlo + 16 * s, 0);
+        else fetch_rest();
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int v = 0; v < VX; ++v)
+#pragma unroll
+            for (int u = 0; u < VY; ++u)
+              acc[v][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(__float_as_uint(xf[0][i][v]) ^ flip),
+                                                               yf[0][i][u], acc[v][u], 0, 0, 0);
+      }
+    }
   }
   // the row-index tables share this LDS: every wavefront is past its rows
   if (RIDX) __syncthreads();

@@ -18,13 +18,18 @@ namespace chg {
 // left out are below 2^-26 of |x y|, less than the rounding of one fp32
 // product, and a 16-deep step rounds its sum fewer times than a chain of fp32
 // multiply-adds does. Six bf16 passes take 6/16 of the fp32 matrix cores'
-// time. (An infinite operand gives NaN, not an infinity.)
+// time.
 // These matrix cores cut the bits of a small addend that fall below the sum
 // towards minus infinity, half a last place on average: nothing in one
 // element, but the same sign in every element, so that a gradient summed over
 // 50,000 rows was off by 2e-6 of its size where fp32 products gave 7e-7.
 // Odd rows are therefore multiplied with -1 and their results turned back,
 // which gives their errors the other sign.
+// A part of an infinite x, or of a finite one above the largest bf16 number
+// (3.39e38), is not finite. A wavefront looks at its tile when it is done and
+// forms one with a value that is not finite again with fp32 products, so that
+// the range and the infinities are those of fp32. (Of operands below 2^-110
+// the bits under 2^-126 are lost.)
 //
 // The weights are split once a pass: a matrix is packed, as B (k, n) =
 // W[k][n] and, for backward passes, as W[n][k], into tiles of 16 k x 32

@@ -26,7 +26,10 @@ __device__ __forceinline__ unsigned bf16_pair(float a, float b, float& ra, float
   return u;
 }
 
-// x = h + m + l exactly: h = bf16(x), m = bf16(x - h), l = x - h - m
+// x = h + m + l: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m). Exact for
+// |x| from 2^-110 (below, l may be under 2^-126, which the matrix cores take
+// as 0) up to the largest bf16 number, 3.39e38 (above, h is infinite and m is
+// not a number).
 __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
   uint4 h, m, l;
   unsigned* hp = reinterpret_cast<unsigned*>(&h);
@@ -42,6 +45,36 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
     lp[q] = bf16_pair(r0 - a, r1 - b, c, d);
   }
   return Split8{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+// The same for operands laid out once (the weights), for which h is cut and not
+// rounded where it would be infinite, and the other parts of an infinite value
+// are 0: x = h + m + l up to the largest fp32 number, and for infinities.
+__device__ __forceinline__ Split8 split8_all(const float (&x)[8]) {
+  bool big = false;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) big = big || !(fabsf(x[q]) < 3.39e38f);
+  if (!big) return split8(x);
+  uint4 h, m, l;
+  unsigned short* hp = reinterpret_cast<unsigned short*>(&h);
+  unsigned short* mp = reinterpret_cast<unsigned short*>(&m);
+  unsigned short* lp = reinterpret_cast<unsigned short*>(&l);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const float hv = __uint_as_float(__float_as_uint(x[q]) & 0xffff0000u);
+    const float r = isinf(x[q]) ? 0.f : x[q] - hv;
+    float mv, z0, z1;
+    hp[q] = (unsigned short)(__float_as_uint(hv) >> 16);
+    mp[q] = (unsigned short)bf16_pair(r, r, mv, z0);
+    lp[q] = (unsigned short)bf16_pair(r - mv, r - mv, z0, z1);
+  }
+  return Split8{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+// the values back from their parts
+__device__ __forceinline__ void unsplit8(const Split8& p, float (&x)[8]) {
+#pragma unroll
+  for (int q = 0; q < 8; ++q) x[q] = ((float)p.h[q] + (float)p.m[q]) + (float)p.l[q];
 }
 
 // a lane's part of a packed tile: three planes of 64 16-byte pieces

@@ -1,0 +1,81 @@
+"""Products of fp32 operands split into bf16 parts: the range, operands and
+weights above the largest bf16 number (3.39e38) and infinite ones, on few rows
+and on enough for the launches that keep the weights in LDS."""
+import numpy as np
+import pytest
+
+from oracle import model as om
+from paper_2412_20796_amd import synth
+from test_gpu_model import _dev, _setup, bd  # noqa: F401 (fixture)
+
+pytestmark = pytest.mark.gpu
+
+BIG = np.float32(3.4e38)
+
+
+def _one_atom(d):
+    b = synth.Batch(np.array([0, 1], np.int32), np.zeros((1, 3), np.float32),
+                    (np.eye(3, dtype=np.float32) * np.float32(2.9))[None], np.array([14], np.int32))
+    return b, synth.make_params(d, 1, seed=(61, 1, d)), om.layout(om.HParams(d=d, n_layers=1))[0]
+
+
+def _grad_w3(bd, setup, b, p, off, d):
+    hp, db, g, ws = setup
+    bd.forward(hp, db, g, p, ws)
+    z = lambda *s: _dev(np.zeros(s, np.float32))
+
+    def run(dE):
+        grad = bd.backward(hp, db, g, p, _dev(np.array([dE], np.float32)), z(1, 3), z(1, 3, 3), ws)
+        return grad.cpu().numpy()[off:off + d].copy()
+
+    return run
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_operand_near_the_top_of_the_range(bd, d):
+    b, params, lay = _one_atom(d)
+    run = _grad_w3(bd, _setup(bd, b, d, 1), b, _dev(params), lay["E_W3"][0], d)
+    a = run(1.0)  # h + m + l of the activations times one: exact
+    assert (a != 0).all()
+    big = run(BIG)
+    assert np.all(np.abs(big / (a.astype(np.float64) * float(BIG)) - 1) <= 2.0 ** -22)
+    assert np.array_equal(run(np.inf), np.where(a > 0, np.inf, -np.inf).astype(np.float32))
+    assert np.array_equal(run(-np.inf), np.where(a > 0, -np.inf, np.inf).astype(np.float32))
+    assert np.isnan(run(np.nan)).all()
+
+
+@pytest.mark.parametrize("S", [2, 18])
+def test_weights_near_the_top_of_the_range(bd, S):
+    """d = 128 heads with one weight of the force head's output layer at
+    3.4e38, and one of the energy head's infinite."""
+    d, k = 128, 37
+    b = synth.random_crystals(seed=620, n_struct=S, n_lo=3 if S == 2 else 50, n_hi=6 if S == 2 else 50, rho=(0.09, 0.1))
+    params = synth.make_params(d, 1, seed=(62, 1))
+    lay = om.layout(om.HParams(d=d, n_layers=1))[0]
+    view = {n: params[o:o + int(np.prod(s))].reshape(s) for n, (o, s) in lay.items()}
+    for h in "EF":
+        # activation k small and negative for every row: silu(-7 +- 0.1)
+        view[h + "_W2"][:, k] *= 0.01
+        view[h + "_b2"][k] = -7
+        view[h + "_W3"][:] = 0
+        view[h + "_b3"][:] = 0
+    hp, db, g, ws = _setup(bd, b, d, 1)
+    tiles = -(-g.n_edges // 32) - 2 * (-b.n_atoms // 32)
+    print("E", g.n_edges, "tiles", tiles)
+    assert (tiles >= 2048) == (S > 2)
+
+    def run(wE, wF):
+        view["E_W3"][k, 0], view["F_W3"][k, 0] = wE, wF
+        E, F, _ = bd.forward(hp, db, g, _dev(params), ws, save_for_backward=False)
+        return E.cpu().numpy(), F.cpu().numpy().astype(np.float64)
+
+    E1, F1 = run(1.0, 1.0)
+    assert (E1 < 0).all()
+    E2, F2 = run(-np.inf, BIG)
+    assert (E2 == np.inf).all()
+    # forces are linear in the output layer: two roundings of a scalar an edge apart
+    ref = F1 * float(BIG)
+    assert np.isfinite(F2).all()
+    assert np.abs(F2 - ref).max() <= 1e-5 * np.abs(ref).max()
+    E3, _ = run(float(BIG), 1.0)
+    assert np.all(np.abs(E3 / (E1.astype(np.float64) * float(BIG)) - 1) <= 1e-5)
