@@ -107,6 +107,20 @@ __device__ __forceinline__ void unflip(v16f& acc) {
   for (int j = 1; j < 16; j += 2) acc[j] = -acc[j];
 }
 
+// acc += x y over 16 k; `only`: the one step of its sum, with the small terms
+// in an accumulator of their own (see gemm.hpp)
+__device__ __forceinline__ void mul_step(const Split8& x, const Split8& y, bool only, v16f& acc) {
+  if (!only) {
+    mfma_split(x, y, acc, acc);
+    return;
+  }
+  v16f lo;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) lo[j] = 0.f;
+  mfma_split(x, y, acc, lo);
+  acc += lo;
+}
+
 // this lane's eight A values of a step (its row, k = 16 step + 8 (lane / 32) ..)
 __device__ __forceinline__ void load_a(const GemmProblem& P, int ks, int64_t arow, int h, float (&v)[8]) {
   const GemmSeg& S = P.seg[seg_of(P, ks)];
@@ -372,8 +386,8 @@ __global__ void __launch_bounds__(256, KS <= 2 ? 4 : 3) k_gemm_p(GemmPArgs args)
   };
   auto mul = [&](const uint4* B, int ks, const Split8& x, v16f (&acc)[2]) {
     const uint4* b0 = B + ks * kPackTile + lane;
-    mfma_split(x, packed8(b0), acc[0]);
-    if (two) mfma_split(x, packed8(b0 + KS * kPackTile), acc[1]);
+    mul_step(x, packed8(b0), nks == 1, acc[0]);
+    if (two) mul_step(x, packed8(b0 + KS * kPackTile), nks == 1, acc[1]);
   };
   // (DEEP: every wavefront runs the block's rounds; a tile past the end is
   // clamped rows, not stored)
@@ -439,7 +453,7 @@ constexpr int kGwWaves = 8;
 constexpr int kGwLd = 64 + 4;
 
 template <int WK>
-__global__ void __launch_bounds__(512, 2) k_gemm_k(GemmBatch batch) {
+__global__ void __launch_bounds__(512, 4) k_gemm_k(GemmBatch batch) {
   __shared__ __attribute__((aligned(16))) float slot[WK > 1 ? kGwWaves * 32 * kGwLd : 4];
   const GemmProblem& P = batch.p[blockIdx.z];
   constexpr int TPB = kGwWaves / WK;  // row tiles per block
@@ -473,8 +487,8 @@ __global__ void __launch_bounds__(512, 2) k_gemm_k(GemmBatch batch) {
   auto compute = [&](int q) {
     flip_odd(a[q], lane);
     const Split8 x = split8(a[q]);
-    mfma_split(x, as_split8(b[q][0]), acc[0]);
-    if (two) mfma_split(x, as_split8(b[q][1]), acc[1]);
+    mul_step(x, as_split8(b[q][0]), hi - lo == 1, acc[0]);
+    if (two) mul_step(x, as_split8(b[q][1]), hi - lo == 1, acc[1]);
   };
   if (r0 < P.M) {
     if (lo < hi) fetch(lo, 0);
@@ -586,8 +600,12 @@ struct TnLaunch {
 // vectors. Both
 // operands are split into three bf16 parts and multiplied on the bf16 matrix
 // cores (see gemm.hpp; odd wavefronts multiply -X, so that the one-sided
-// rounding cancels in the block's sum). The next steps' rows are loaded while
-// a step is multiplied. The four wavefronts of a block take consecutive
+// rounding cancels in the block's sum; a range's last step, of fewer than 16
+// rows, which may be its only one, keeps the small terms apart: in every step
+// that took 242 registers for 181, no block of the kernels this one overlaps
+// with fitted beside it, and its launches went from 266 to 362 us a step on 40
+// crystals of 1,076 atoms). The next steps' rows are loaded while a step is
+// multiplied. The four wavefronts of a block take consecutive
 // quarters of the block's rows; their tiles are added in wave order in LDS.
 // A problem with a bias row also sums the Y columns (the bias gradient of a
 // layer whose weight gradient is X^T Y).
@@ -693,7 +711,8 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
     }
   };
   const unsigned flip = (unsigned)(wave & 1) << 31;
-  auto compute = [&](int b) {
+  // (last: the range's last step, of fewer than 16 rows)
+  auto compute = [&](int b, bool last) {
     if (colsum) {
 #pragma unroll
       for (int u = 0; u < VY; ++u)
@@ -716,7 +735,7 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
         for (int i = 0; i < 8; ++i) t[i] = yf[b][i][u];
         const Split8 y = split8(t);
 #pragma unroll
-        for (int v = 0; v < VX; ++v) mfma_split(xs[v], y, acc[v][u]);
+        for (int v = 0; v < VX; ++v) mul_step(xs[v], y, last, acc[v][u]);
       }
     }
   };
@@ -751,13 +770,13 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         fetch(step(s + b + NB - 1), (b + NB - 1) % NB);
-        if (s + b < nf) compute(b);
+        if (s + b < nf) compute(b, false);
       }
     }
   }
   if (rest) {
     fetch_rest();
-    compute(0);
+    compute(0, true);
   }
   if (HASX) {
     float z = 0.f * acc[0][VY - 1][0];

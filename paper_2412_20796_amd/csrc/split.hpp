@@ -85,14 +85,15 @@ __device__ __forceinline__ Split8 as_split8(const uint4 (&p)[3]) {
   return Split8{__builtin_bit_cast(bf16x8, p[0]), __builtin_bit_cast(bf16x8, p[1]), __builtin_bit_cast(bf16x8, p[2])};
 }
 
-// acc += x y over 16 k, the small terms first
-__device__ __forceinline__ void mfma_split(const Split8& x, const Split8& y, f32x16& acc) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.l, y.h, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.h, y.l, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.m, y.m, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.m, y.h, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.h, y.m, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.h, y.h, acc, 0, 0, 0);
+// hi + lo += x y over 16 k: the products of the leading parts, whose bits the
+// sum keeps, and the others, small terms first (hi and lo may be one)
+__device__ __forceinline__ void mfma_split(const Split8& x, const Split8& y, f32x16& hi, f32x16& lo) {
+  lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.l, y.h, lo, 0, 0, 0);
+  lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.h, y.l, lo, 0, 0, 0);
+  lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.m, y.m, lo, 0, 0, 0);
+  lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.m, y.h, lo, 0, 0, 0);
+  lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.h, y.m, lo, 0, 0, 0);
+  hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.h, y.h, hi, 0, 0, 0);
 }
 
 }  // namespace chg
