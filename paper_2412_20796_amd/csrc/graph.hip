@@ -12,6 +12,7 @@
 // E, B, A back.
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -1104,7 +1105,10 @@ __global__ void __launch_bounds__(256) k_cand_count(CandArgs A, int* __restrict_
     edge_count[i] = ne;
     bond_count[i] = nb;
     const float dx = ri[0] - A.ref[3 * i], dy = ri[1] - A.ref[3 * i + 1], dz = ri[2] - A.ref[3 * i + 2];
-    disp2[i] = dx * dx + dy * dy + dz * dz;
+    // a position that is not a number has moved too far (a maximum would drop
+    // it): the list is then built again, which refuses it
+    const float d2 = dx * dx + dy * dy + dz * dz;
+    disp2[i] = d2 <= FLT_MAX ? d2 : INFINITY;
   }
 }
 

@@ -199,3 +199,22 @@ def test_md_replica_batch_with_skin(bd):
     v0, inv_m, ref = _guarded_case(b, params, d, T, 3, 2.0, range(60, 80))
     got, cand = _md_on_stream(bd, b, params, v0, inv_m, 2.0, [3], d, T, skin=0.4)
     _compare(got, ref, "replicas md with skin")
+
+
+@pytest.mark.parametrize("skin", [0.0, 0.5])
+@pytest.mark.parametrize("which", ["one", "all"])
+def test_md_refuses_positions_that_are_not_numbers(bd, skin, which):
+    """A trajectory with velocities that are not numbers ends with an error,
+    with a full search every step and with a candidate list, and leaves the
+    state at the last completed step."""
+    b = synth.random_crystals(seed=17, n_struct=2, n_lo=5, n_hi=9)
+    v0 = np.full((b.n_atoms, 3), 1e-3, np.float32)
+    v0[3 if which == "one" else slice(None)] = np.nan
+    hp, db, ws = bd.hparams(d=64, n_layers=2), bd.DeviceBatch.from_host(b), bd.Workspace()
+    vel = _dev(v0)
+    with pytest.raises(bd.ChgnetError) as e:
+        bd.md(hp, db, bd.DeviceGraph(b.n_atoms, 2048, 256, 2048), _dev(synth.make_params(64, 2, seed=(17, 1))), vel,
+              _dev(np.full(b.n_atoms, 0.05, np.float32)), 0.5, 4, ws, skin=skin)
+    assert e.value.code == bd.CHGNET_EINVAL
+    assert np.array_equal(db.pos.cpu().numpy(), b.pos)
+    assert np.array_equal(vel.cpu().numpy(), v0, equal_nan=True)
