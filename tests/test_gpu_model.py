@@ -68,17 +68,18 @@ def test_step_parity_workloads(bd, name):
     _check_step(bd, b, params, targets, d, T, name)
 
 
-def test_step_parity_wide_weight_gradient_tiles(bd, monkeypatch):
-    """The 64 x 128 wave tiles of the weight-gradient products, which the
-    library takes only for large launches, forced on small batches (d = 64
-    and d = 128, gathered and plain rows, bias column sums): full step
-    parity against the oracle."""
-    monkeypatch.setenv("CHGNET_TN_WIDE_MIN_UNITS", "0")
-    b, params, targets, d, T = synth.workload_inputs("triclinic40")
-    _check_step(bd, b, params, targets, d, T, "triclinic40-wide")
-    b = synth.random_crystals(seed=11, n_struct=3, n_lo=4, n_hi=12)
-    _check_step(bd, b, synth.make_params(128, 2, seed=(7, 1, 2)), synth.make_targets(b, seed=(7, 2, 2)), 128, 2,
-                "d128-wide")
+@pytest.mark.parametrize("d,n", [(64, 1), (64, 2), (64, 15), (64, 16), (64, 17), (64, 63), (64, 65), (128, 1),
+                                 (128, 17), (128, 33)])
+def test_step_parity_weight_gradient_rows(bd, d, n):
+    """Weight gradients over few rows: a wavefront takes 16 rows of a chunk of
+    64 at these sizes, so the atoms' products run on one row, on a whole step,
+    on a last step of 1 or 15 rows, with wavefronts that have none, and on a
+    second chunk of one row; the edges', bonds' and angles' on other
+    remainders, with gathered rows (bonds) and without, 64-column tiles and
+    the basis's 31 rows: full step parity against the oracle."""
+    b = synth.random_crystals(seed=900 + n, n_struct=1, n_lo=n, n_hi=n, rho=(0.08, 0.09))
+    _check_step(bd, b, synth.make_params(d, 2, seed=(7, 1, n)), synth.make_targets(b, seed=(7, 2, n)), d, 2,
+                "%d atoms" % n)
 
 
 def test_step_parity_random_small_batches(bd):
@@ -295,8 +296,8 @@ def test_adam_kernel_on_its_own_gradient(bd):
 @pytest.mark.parametrize("name", ["triclinic40", "wide128"])
 def test_bitwise_reproducible(bd, name):
     """Two steps on the same inputs give bitwise the same loss and gradient
-    (every sum in a fixed order; wide128 runs the d = 128 kernels, the
-    64 x 128 weight-gradient tiles and the SiLU head GEMM)."""
+    (every sum in a fixed order; wide128 runs the d = 128 kernels and the
+    weight-gradient chunks of 2,048 rows)."""
     b, params, targets, d, T = synth.workload_inputs(name)
     hp, db, g, ws = _setup(bd, b, d, T)
     p = _dev(params)
@@ -308,14 +309,10 @@ def test_bitwise_reproducible(bd, name):
     assert np.array_equal(g1, g2.cpu().numpy())
 
 
-@pytest.mark.parametrize("wide", ["default", "0"])
-def test_profile_counts_launches_by_tag(bd, monkeypatch, wide):
+def test_profile_counts_launches_by_tag(bd):
     """chgnet_profile_start/stop: one training step of T layers reports the
-    fused gate launches, one weight-gradient launch per layer under tn_in
-    (also where the 64 x 128 and 64 x 64 wave-tile kernels both run) and
+    fused gate launches, one weight-gradient launch per layer under tn_in and
     positive times; profiling changes no result."""
-    if wide != "default":
-        monkeypatch.setenv("CHGNET_TN_WIDE_MIN_UNITS", wide)
     b, params, targets, d, T = synth.workload_inputs("triclinic40")
     hp, db, g, ws = _setup(bd, b, d, T)
     p = _dev(params)
