@@ -74,12 +74,6 @@ __device__ __forceinline__ Dn dn_srbf_df(Dn d, float f, float inv_c, int p) {
   const Dn x = inv_c * d;
   return (sqrtf(2.0f * inv_c) * inv_c) * (dn_cos(f * x) * dn_envelope(x, p));
 }
-__device__ __forceinline__ float dn_wsum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-__device__ __forceinline__ Dn dn_wsum(Dn x) { return {dn_wsum(x.v), dn_wsum(x.t)}; }
 
 // ---------------------------------------------------------------------------
 // Tangents of the geometry and the bases.

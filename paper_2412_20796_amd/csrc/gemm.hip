@@ -18,8 +18,6 @@
 
 namespace chg {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
 namespace {
 
 __device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + __expf(-x)); }
