@@ -114,6 +114,9 @@ __device__ __forceinline__ void edge_vector(int i, int j, const int* __restrict_
 // lengths back). Bound by latency on few atoms, by the sines on many; under
 // the profiler 23 -> 13 us on one 8-atom cell, 37 -> 17 us on 40 crystals of
 // 1,076 atoms, 78 -> 49 us on 128 of 5,541 (both launches against one).
+// Few atoms with long rows (a bond cutoff of 6 or 9 A in a small cell: 12,000
+// or 92,000 angles an atom) leave the chip idle so, and gridDim.y blocks share
+// an atom's passes over its edges, bonds and angles (geom_split).
 struct GeomArgs {
   int S, D, R, K, p;
   float inv_ca, inv_cb;
@@ -126,6 +129,13 @@ constexpr int kGeomBonds = 256;  // bonds whose vectors are kept in LDS (more ar
 
 // Fourier rows longer than 32 (K > 32) go straight out; others through LDS
 constexpr int kGeomAngles = 128;
+
+// Blocks an atom: one block takes two passes of the average atom, as long as
+// the launch has no more than 1,024 blocks, four a compute unit.
+inline int geom_split(int64_t N, int64_t E, int64_t A) {
+  const int64_t passes = cdiv(std::max(cdiv(A, kGeomAngles), cdiv(E, 256)), N);
+  return (int)std::max<int64_t>(1, std::min(cdiv(passes, 2), 1024 / N));
+}
 
 __global__ void __launch_bounds__(256) k_geom(GeomArgs g) {
   __shared__ float dl[256], pl[256];
@@ -146,21 +156,25 @@ __global__ void __launch_bounds__(256) k_geom(GeomArgs g) {
     lo = nlo;
   }
   const int s = lo;
-  if (tid < g.D) g.v0[(int64_t)i * g.D + tid] = g.WZ[(int64_t)(z - 1) * g.D + tid];
-  if (tid == 0) g.atom_struct[i] = s;
+  const int part = blockIdx.y, parts = gridDim.y;
+  if (part == 0) {
+    if (tid < g.D) g.v0[(int64_t)i * g.D + tid] = g.WZ[(int64_t)(z - 1) * g.D + tid];
+    if (tid == 0) g.atom_struct[i] = s;
+  }
   const float* L = g.lattice + 9 * s;
   // bonds: their vectors first, so that the angles wait for nothing else
-  for (int q = tid; q < k; q += 256) {
+  for (int q = tid; q < (part == 0 ? k : min(k, kGeomBonds)); q += 256) {
     const int e = g.bond_edge[b0 + q];
     double r[3];
     edge_vector(i, g.edge_dst[e], g.edge_img + 3 * e, L, g.pos, r);
     if (q < kGeomBonds)
 #pragma unroll
       for (int c = 0; c < 3; ++c) rb[q][c] = r[c];
-    g.bond_src[b0 + q] = i;
+    if (part == 0) g.bond_src[b0 + q] = i;
   }
+  __syncthreads();
   // edges
-  for (int base = e0; base < e1; base += 256) {
+  for (int base = e0 + 256 * part; base < e1; base += 256 * parts) {
     const int e = base + tid;
     if (e < e1) {
       double r[3];
@@ -183,7 +197,7 @@ __global__ void __launch_bounds__(256) k_geom(GeomArgs g) {
     __syncthreads();
   }
   // bond basis rows
-  for (int base = 0; base < k; base += 256) {
+  for (int base = 256 * part; base < k; base += 256 * parts) {
     const int q = base + tid;
     if (q < k) {
       double r[3];
@@ -212,7 +226,7 @@ __global__ void __launch_bounds__(256) k_geom(GeomArgs g) {
   const int64_t a0 = g.angle_ptr[b0];
   const int M = (g.K - 1) / 2;
   const bool staged = g.K <= 32;
-  for (int base = 0; base < na; base += kGeomAngles) {
+  for (int base = kGeomAngles * part; base < na; base += kGeomAngles * parts) {
     const int x = base + tid;
     if (tid < kGeomAngles && x < na) {
       const int p = x / (k - 1), q0 = x - p * (k - 1), q = q0 < p ? q0 : q0 + 1;
@@ -3066,7 +3080,7 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     ga.atom_struct = a.atom_struct; ga.edge_src = a.edge_src; ga.bond_src = a.bond_src;
     ga.ang_b1 = a.ang_b1; ga.ang_b2 = a.ang_b2; ga.ang_ctr = a.ang_ctr;
     ga.v0 = a.v[0]; ga.edge_len = a.edge_len; ga.edge_xhat = a.edge_xhat; ga.rbf_a = a.rbf_a; ga.rbf_b = a.rbf_b; ga.ft = a.ft;
-    KLAUNCH(st, "k_geom", k_geom<<<(unsigned)N, 256, 0, st>>>(ga));
+    KLAUNCH(st, "k_geom", k_geom<<<dim3((unsigned)N, geom_split(N, E, A)), 256, 0, st>>>(ga));
   }
   {
     std::vector<GemmProblem> ps;
