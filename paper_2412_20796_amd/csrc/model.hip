@@ -410,9 +410,12 @@ constexpr int kBwdCpl = 8;
 // From this many bonds on the update's output linear is a launch of its own
 // at d = 64 too: in the message launch a wavefront multiplies its row lane by
 // lane, 64 broadcasts and 16 KB of weights a row, which on 36,000 bonds took
-// 68 us against 37 + 21 us apart; on 5,000 bonds the launch costs more than it
-// saves.
-constexpr int kFuseUpdBonds = 8192;
+// 68 us against 37 + 21 us apart; on few bonds the launch costs more than it
+// saves. A forward pass of four layers, in one launch and apart: 193 and 201
+// us of 1,100 bonds, 317 and 325 of 4,500, 377 and 381 of 6,800, 490 and 496 of
+// 9,200, 564 and 561 of 11,200, 652 and 647 of 13,300, 818 and 801 of 18,300,
+// 1,520 and 1,473 of 36,500.
+constexpr int kFuseUpdBonds = 10240;
 enum GateFwdMode { FWD_ATOM = 0, FWD_BOND = 1, FWD_ANGLE = 2 };
 
 // Forward gate modes:
