@@ -919,10 +919,13 @@ void carve(Arena& ar, int64_t N, int64_t S, GraphScratch& g) {
 }
 
 // The calling thread's pinned record for the sizes (allocated on its first
-// use): the scan kernel writes it directly, with no copy after it.
+// use): the scan kernel writes it directly, with no copy after it, on every
+// device that the thread builds graphs on.
 int pinned_info(GraphInfo*& out) {
   thread_local GraphInfo* pinned = nullptr;
-  if (!pinned) CHG_HIP(hipHostMalloc(reinterpret_cast<void**>(&pinned), sizeof(GraphInfo), hipHostMallocDefault));
+  if (!pinned)
+    CHG_HIP(hipHostMalloc(reinterpret_cast<void**>(&pinned), sizeof(GraphInfo),
+                          hipHostMallocPortable | hipHostMallocMapped));
   out = pinned;
   return CHGNET_OK;
 }
