@@ -189,9 +189,11 @@ int chgnet_build_graph_noalloc(const chgnet_hparams* hp, const chgnet_batch* bat
  * hp->sequential): energy [S] (total energy of each crystal), forces [N,3],
  * stress [S,3,3] and, if hp->magmom, magnetic moments magmom [N] (may be NULL
  * when not wanted; must be NULL without the head). `graph` must hold a graph
- * of `batch` (n_edges/n_bonds/n_angles set; angle_b2 may be NULL). The
- * activations always stay in `ws` for chgnet_backward (save_for_backward is
- * accepted for compatibility and ignored). */
+ * of `batch` (n_edges/n_bonds/n_angles set; angle_b2 may be NULL). With
+ * save_for_backward the activations stay in `ws` for chgnet_backward. With 0
+ * those that only it reads are not kept (the outputs are the same bits) and
+ * no chgnet_backward may follow until a forward that saves; the conservative
+ * readout keeps them in either case. */
 int chgnet_forward(const chgnet_hparams* hp, const chgnet_batch* batch, const chgnet_graph* graph,
                    const float* params, float* energy, float* forces, float* stress, float* magmom,
                    int save_for_backward, void* ws, size_t ws_bytes, void* stream);
@@ -200,7 +202,8 @@ int chgnet_forward(const chgnet_hparams* hp, const chgnet_batch* batch, const ch
  * sum(dE*energy) + sum(dF*forces) + sum(dS*stress) (+ sum(dM*magmom) with
  * the head; dM [N] may be NULL, meaning zero; it must be NULL without the
  * head), using the activations of the preceding chgnet_forward on the same ws,
- * batch, graph and params. Positions and lattices are not differentiated.
+ * batch, graph and params, made with save_for_backward. Positions and
+ * lattices are not differentiated.
  * d|x|/dx is taken as 0 at x = 0. With hp->conservative the forces and
  * stresses are the derivatives of the energy, and their terms differentiate
  * those derivatives (second derivatives). */

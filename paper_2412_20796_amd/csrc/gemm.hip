@@ -295,12 +295,15 @@ __device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, c
 // the weights once and run without a further barrier; deeper ones (DEEP) take
 // them KS steps at a time through two LDS buffers, the next steps loaded
 // straight into LDS while these are multiplied, one barrier a chunk.
-// At k = 64 bound by the bytes of C, at k = 128 and more by the matrix cores
-// and the latency of a chunk. Against the fp32 matrix cores with both operands
-// staged through LDS, kernel time: a layer's bond projections of 4,096 atoms
-// (36,300 x 512 x 64) 51 -> 37 us, its embeddings 115 -> 82 us; wide128's
-// launches of k = 128 92-170 -> 84 us; the Eq. 10 block's input gradients (k
-// = 256) 151 -> 136 us. Blocks: three a compute unit (four for KS = 2); with
+// Bound by the latency of the rows of A and of the stores: the two wavefronts
+// a SIMD that are there on average wait for memory half of their time (0.47 to
+// 0.60 of it by the counters), while the matrix cores are 6 % (k = 64) to 17 %
+// (k = 256) busy, the vector unit issues in 17 to 30 % of the cycles and 1.8
+// to 2.4 TB/s move. Against the fp32 matrix cores with both operands staged
+// through LDS, kernel time: a layer's bond projections of 4,096 atoms (36,300
+// x 512 x 64) 52 -> 40 us, its embeddings 115 -> 84 us; wide128's launches of
+// k = 128 92-170 -> 89 us; the Eq. 10 block's input gradients (k = 256) of 64
+// cells 145 -> 119 us. Blocks: three a compute unit (four for KS = 2); with
 // registers for four at KS = 4 the epilogue spilled (37 -> 66 us).
 struct GemmPArgs {
   GemmBatch b;

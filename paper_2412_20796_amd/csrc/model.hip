@@ -4078,8 +4078,9 @@ int md_entry(const chgnet_hparams* hp, const chgnet_batch* batch, chgnet_graph* 
   // only through its sizes (the arrays are read from memory, the workspace
   // layout follows the sizes), so once two consecutive steps have the same
   // sizes that part is captured into a HIP graph and replayed while they
-  // stay the same. Not with the conservative readout (its backward forks a
-  // second stream), a null stream or per-launch timing.
+  // stay the same. Not on a null stream, with per-launch timing, or with the
+  // conservative readout (its launches too are on `st` alone, but they have
+  // not been measured captured).
   const bool can_capture = st != nullptr && !prof_active() && !hp->conservative;
   hipGraphExec_t exec = nullptr;
   int64_t exec_sizes[3] = {-1, -1, -1}, prev[3] = {-1, -1, -1};
