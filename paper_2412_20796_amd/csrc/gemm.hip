@@ -303,8 +303,8 @@ __device__ __forceinline__ void gemm_put(const GemmProblem& P, int r0, int c0, c
 // through LDS, kernel time: a layer's bond projections of 4,096 atoms (36,300
 // x 512 x 64) 52 -> 40 us, its embeddings 115 -> 84 us; wide128's launches of
 // k = 128 92-170 -> 89 us; the Eq. 10 block's input gradients (k = 256) of 64
-// cells 145 -> 119 us. Blocks: three a compute unit (four for KS = 2); with
-// registers for four at KS = 4 the epilogue spilled (37 -> 66 us).
+// cells 145 -> 119 us. Blocks: three a compute unit (four for KS = 1, 2);
+// with registers for four at KS = 4 the epilogue spilled (37 -> 66 us).
 struct GemmPArgs {
   GemmBatch b;
   int block0[kMaxGemmProblems + 1];  // first block of each problem (multiples of 8)
@@ -387,8 +387,8 @@ __global__ void __launch_bounds__(256, KS <= 2 ? 4 : 3) k_gemm_p(GemmPArgs args)
   };
   auto mul = [&](const uint4* B, int ks, const Split8& x, v16f (&acc)[2]) {
     const uint4* b0 = B + ks * kPackTile + lane;
-    mul_step(x, packed8(b0), nks == 1, acc[0]);
-    if (two) mul_step(x, packed8(b0 + KS * kPackTile), nks == 1, acc[1]);
+    mul_step(x, packed8(b0), KS == 1, acc[0]);
+    if (two) mul_step(x, packed8(b0 + KS * kPackTile), KS == 1, acc[1]);
   };
   // (DEEP: every wavefront runs the block's rounds; a tile past the end is
   // clamped rows, not stored)
@@ -454,7 +454,7 @@ constexpr int kGwWaves = 8;
 constexpr int kGwLd = 64 + 4;
 
 template <int WK>
-__global__ void __launch_bounds__(512, 4) k_gemm_k(GemmBatch batch) {
+__global__ void __launch_bounds__(512, 2) k_gemm_k(GemmBatch batch) {
   __shared__ __attribute__((aligned(16))) float slot[WK > 1 ? kGwWaves * 32 * kGwLd : 4];
   const GemmProblem& P = batch.p[blockIdx.z];
   constexpr int TPB = kGwWaves / WK;  // row tiles per block
@@ -485,13 +485,17 @@ __global__ void __launch_bounds__(512, 4) k_gemm_k(GemmBatch batch) {
       for (int pl = 0; pl < 3; ++pl) b[q][t][pl] = src[64 * pl];
     }
   };
-  auto compute = [&](int q) {
+  auto compute = [&](int q, bool only = false) {
     flip_odd(a[q], lane);
     const Split8 x = split8(a[q]);
-    mul_step(x, as_split8(b[q][0]), hi - lo == 1, acc[0]);
-    if (two) mul_step(x, as_split8(b[q][1]), hi - lo == 1, acc[1]);
+    mul_step(x, as_split8(b[q][0]), only, acc[0]);
+    if (two) mul_step(x, as_split8(b[q][1]), only, acc[1]);
   };
-  if (r0 < P.M) {
+  if (r0 < P.M && hi - lo == 1) {
+    // apart from the loop, whose second set of operands it does not need
+    fetch(lo, 0);
+    compute(0, true);
+  } else if (r0 < P.M) {
     if (lo < hi) fetch(lo, 0);
     for (int ks = lo; ks < hi; ks += 2) {
       if (ks + 1 < hi) fetch(ks + 1, 1);
@@ -1098,6 +1102,17 @@ int gemm_launch(const GemmBatch& b, hipStream_t st, const char* tag) {
   if (q.n == 0) return CHGNET_OK;
   const unsigned gy = (unsigned)cdiv(maxN, 64);
   if (tiles >= 2048) {
+    // sums of one step have an instantiation of their own (see mul_step)
+    const int ones = (int)std::count_if(q.p, q.p + q.n, [](const GemmProblem& p) { return p.nks == 1; });
+    if (ones > 0 && ones < q.n) {
+      GemmBatch part[2] = {};
+      for (int i = 0; i < q.n; ++i) {
+        GemmBatch& to = part[q.p[i].nks == 1];
+        to.p[to.n++] = q.p[i];
+      }
+      CHG_TRY(gemm_launch(part[0], st, tag));
+      return gemm_launch(part[1], st, tag);
+    }
     // one resident round of blocks (four or three a compute unit), dealt to
     // the problems by their steps, row workers in multiples of 8 (one per XCD)
     const bool deep = maxks > 8;
@@ -1113,7 +1128,8 @@ int gemm_launch(const GemmBatch& b, hipStream_t st, const char* tag) {
       A.block0[i + 1] = A.block0[i] + (int)(cdiv(workers, 8) * 8 * ncol);
     }
     const unsigned grid = (unsigned)A.block0[q.n];
-    if (maxks <= 2) KLAUNCH(st, tag, k_gemm_p<2, false><<<grid, 256, 0, st>>>(A));
+    if (maxks == 1) KLAUNCH(st, tag, k_gemm_p<1, false><<<grid, 256, 0, st>>>(A));
+    else if (maxks == 2) KLAUNCH(st, tag, k_gemm_p<2, false><<<grid, 256, 0, st>>>(A));
     else if (maxks <= 4) KLAUNCH(st, tag, k_gemm_p<4, false><<<grid, 256, 0, st>>>(A));
     else if (!deep) KLAUNCH(st, tag, k_gemm_p<8, false><<<grid, 256, 0, st>>>(A));
     else KLAUNCH(st, tag, k_gemm_p<4, true><<<grid, 256, 0, st>>>(A));

@@ -36,6 +36,7 @@ def _params(hp, seed):
 
 
 @pytest.mark.parametrize("R,K,d,S", [(1, 1, 64, 2), (16, 17, 64, 3), (33, 63, 64, 2), (64, 15, 128, 2), (33, 63, 64, 24),
+                                     (2, 31, 64, 24), (16, 15, 64, 24), (31, 3, 128, 12),
                                      (48, 33, 128, 12)])
 def test_step_parity(bd, R, K, d, S):
     b = synth.random_crystals(seed=500 + R, n_struct=S, n_lo=5, n_hi=8 if S < 4 else 30)
