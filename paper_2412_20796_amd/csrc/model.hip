@@ -120,6 +120,7 @@ __device__ __forceinline__ void edge_vector(int i, int j, const int* __restrict_
 struct GeomArgs {
   int S, D, R, K, p;
   float inv_ca, inv_cb;
+  double r_atom, r_bond;
   const int *atom_ptr, *Z, *edge_ptr, *edge_dst, *edge_img, *bond_ptr, *bond_edge, *angle_ptr;
   const float *pos, *lattice, *WZ, *freq_a, *freq_b;
   int *atom_struct, *edge_src, *bond_src, *ang_b1, *ang_b2, *ang_ctr;
@@ -184,7 +185,8 @@ __global__ void __launch_bounds__(256) k_geom(GeomArgs g) {
       g.edge_src[e] = i;
       g.edge_len[e] = d;
       for (int c = 0; c < 3; ++c) g.edge_xhat[3 * e + c] = (float)(r[c] / dd);
-      dl[tid] = d * g.inv_ca;
+      // (rounded once: the functions' arguments share its error)
+      dl[tid] = (float)(dd / g.r_atom);
       pl[tid] = srbf_pre(d, g.inv_ca, g.p);
     }
     __syncthreads();
@@ -208,9 +210,9 @@ __global__ void __launch_bounds__(256) k_geom(GeomArgs g) {
         const int e = g.bond_edge[b0 + q];
         edge_vector(i, g.edge_dst[e], g.edge_img + 3 * e, L, g.pos, r);
       }
-      const float d = (float)sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
-      dl[tid] = d * g.inv_cb;
-      pl[tid] = srbf_pre(d, g.inv_cb, g.p);
+      const double dd = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+      dl[tid] = (float)(dd / g.r_bond);
+      pl[tid] = srbf_pre((float)dd, g.inv_cb, g.p);
     }
     __syncthreads();
     const int nk = min(256, k - base);
@@ -3077,6 +3079,8 @@ int forward_impl(Ctx& c, const float* Pflat, float* energy, float* forces, float
     ga.p = c.hp->envelope_p;
     ga.inv_ca = 1.0f / c.hp->r_atom;
     ga.inv_cb = 1.0f / c.hp->r_bond;
+    ga.r_atom = c.hp->r_atom;
+    ga.r_bond = c.hp->r_bond;
     ga.atom_ptr = bt.atom_ptr; ga.Z = bt.Z; ga.edge_ptr = g.edge_ptr; ga.edge_dst = g.edge_dst; ga.edge_img = g.edge_img;
     ga.bond_ptr = g.bond_ptr; ga.bond_edge = g.bond_edge; ga.angle_ptr = g.angle_ptr;
     ga.pos = bt.pos; ga.lattice = bt.lattice; ga.WZ = P + L.W_Z; ga.freq_a = P + L.f_a; ga.freq_b = P + L.f_b;
