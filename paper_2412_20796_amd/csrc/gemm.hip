@@ -137,8 +137,9 @@ __device__ __forceinline__ void load_a(const GemmProblem& P, int ks, int64_t aro
 // 0 x over an accumulator's values, added to s: 0, or NaN where one is not
 // finite. An operand's value with a part that is not finite leaves its whole
 // row (left) or column (right) of the sums of products so, as part times 0 is
-// not finite either: a look at one accumulator and one value of its
-// neighbours finds both.
+// not finite either: a look at one accumulator and one value of its neighbour
+// finds both. The neighbour's other values may be infinite on their own, where
+// a product of leading parts overflows (rounded up, by 2^-8 at most).
 __device__ __forceinline__ float zero_of(const v16f& x, float s) {
   float t = 0.f;
 #pragma unroll
@@ -147,6 +148,12 @@ __device__ __forceinline__ float zero_of(const v16f& x, float s) {
     t = fmaf(x[j + 1], 0.f, t);
   }
   return s + t;
+}
+__device__ __forceinline__ float zero_of_next(const v16f& x, float s) {
+  float m = 0.f;
+#pragma unroll
+  for (int j = 0; j < 16; j += 2) m = fmaxf(fmaxf(fabsf(x[j]), fabsf(x[j + 1])), m);
+  return fmaf(x[0], 0.f, fmaf(m, 0.f, s));
 }
 __device__ __forceinline__ bool any_nan(float s) { return __ballot(s != 0.f) != 0; }
 
@@ -363,7 +370,7 @@ __global__ void __launch_bounds__(256, KS <= 2 ? 4 : 3) k_gemm_p(GemmPArgs args)
   auto put = [&](v16f (&acc)[2]) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) unflip(acc[t]);
-    if (any_nan(zero_of(acc[0], 0.f * acc[1][0]))) gemm_tile_fp32(P, 0, nks, row_of(tile), c0, two, lane, acc);
+    if (any_nan(zero_of(acc[0], zero_of_next(acc[1], 0.f)))) gemm_tile_fp32(P, 0, nks, row_of(tile), c0, two, lane, acc);
     if (two) {
       gemm_put<2>(P, tile * 32, c0, acc, bias, lane);
     } else {
@@ -506,7 +513,7 @@ __global__ void __launch_bounds__(512, 2) k_gemm_k(GemmBatch batch) {
   }
 #pragma unroll
   for (int u = 0; u < 2; ++u) unflip(acc[u]);
-  if (any_nan(zero_of(acc[0], 0.f * acc[1][0]))) gemm_tile_fp32(P, lo, hi, arow, n0, two, lane, acc);
+  if (any_nan(zero_of(acc[0], zero_of_next(acc[1], 0.f)))) gemm_tile_fp32(P, lo, hi, arow, n0, two, lane, acc);
   if constexpr (WK == 1) {
     if (r0 >= P.M) return;
     float bias[2] = {0.f, 0.f};
@@ -784,9 +791,12 @@ __device__ __forceinline__ void tn_wave(const TnPlan& Q, int chunk, int m0, int 
     compute(0, true);
   }
   if (HASX) {
-    float z = 0.f * acc[0][VY - 1][0];
+    float z = 0.f;
 #pragma unroll
-    for (int v = 0; v < VX; ++v) z = zero_of(acc[v][0], z);
+    for (int v = 0; v < VX; ++v) {
+      z = zero_of(acc[v][0], z);
+      if (VY > 1) z = zero_of_next(acc[v][VY - 1], z);
+    }
     if (any_nan(z)) {  // with fp32 products (see gemm.hpp)
 #pragma unroll
       for (int v = 0; v < VX; ++v)

@@ -47,6 +47,36 @@ def test_operand_near_the_top_of_the_range(bd, d):
     assert np.isnan(run(np.nan)).all()
 
 
+def test_result_near_the_top_of_the_range(bd):
+    """Products just below the largest fp32 number, whose operands' leading
+    parts multiply to more, in every column of a weight gradient."""
+    d, k = 64, 21
+    b, params, lay = _one_atom(d)
+    view = {n: params[o:o + int(np.prod(s))].reshape(s) for n, (o, s) in lay.items()}
+    # activation k of the first layer is about 40 and the second layer does not
+    # see it: the factors stay well inside the range
+    view["E_b1"][k] = 40
+    view["E_W2"][k] = 0
+    hp, db, g, ws = _setup(bd, b, d, 1)
+    z = lambda *s: _dev(np.zeros(s, np.float32))
+    off = lay["E_W2"][0]
+    w3 = view["E_W3"].copy()
+
+    def run(p, dE):
+        bd.forward(hp, db, g, p, ws)
+        grad = bd.backward(hp, db, g, p, _dev(np.array([dE], np.float32)), z(1, 3), z(1, 3, 3), ws)
+        return grad.cpu().numpy()[off:off + d * d].reshape(d, d)[k].astype(np.float64)
+
+    for n in range(d):
+        view["E_W3"][:] = 1e-3 * w3
+        view["E_W3"][n] = 1000
+        p = _dev(params)
+        one = run(p, 1.0)
+        dE = np.float32(float(np.finfo(np.float32).max) * (1 - 2.0 ** -12) / abs(one[n]))
+        got, want = run(p, dE), one * float(dE)
+        assert np.all(np.abs(got / want - 1) <= 2.0 ** -21), (n, got[n], want[n])
+
+
 @pytest.mark.parametrize("S", [2, 18])
 def test_weights_near_the_top_of_the_range(bd, S):
     """d = 128 heads with one weight of the force head's output layer at
